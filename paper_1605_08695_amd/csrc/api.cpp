@@ -271,7 +271,7 @@ size_t tfk_conv2d_workspace_bytes(int32_t op, tfk_nhwc xd, int32_t cout, tfk_win
     ConvShape s{xd.n, xd.h, xd.w, xd.c, oh, ow, cout, p.kh, p.kw, p.stride_h, p.stride_w, p.pad_top, p.pad_left};
     const int dti = dt == TFK_F32 ? 0 : 1;
     // (the fused ReLU backward sums its bias gradient per channel: no flattening there)
-    if (op == 3) return conv_bwd_data_relu_ws_bytes(dti, s, xd.pixel_stride);
+    if (op == 3) return conv_bwd_data_relu_ws_want(dti, s, xd.pixel_stride);
     int64_t xs = xd.pixel_stride;
     fold_full_window(s, xs);
     if (op == 0) return std::max(conv_fold_applies(dti, s) ? conv_fold_ws_bytes(0, s) : 0,
@@ -409,12 +409,18 @@ tfk_status tfk_conv2d_bwd_input_relu_bwd(const void *dy, tfk_nhwc dyd, const voi
     const int64_t xs = xd.pixel_stride;      // (not flattened: the bias gradient is per channel)
     const size_t need = conv_bwd_data_relu_ws_bytes(dti, s, xs);
     TRY(check_ws(ws, ws_bytes, need));
-    if (overlap(ws, (int64_t)need, dy, yb) || overlap(ws, (int64_t)need, w, wb) || overlap(ws, (int64_t)need, y, xb) ||
-        overlap(ws, (int64_t)need, dpre, xb) || overlap(ws, (int64_t)need, dbias, bb))
-        return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
+    const auto hits = [&](size_t bytes) {
+        return overlap(ws, (int64_t)bytes, dy, yb) || overlap(ws, (int64_t)bytes, w, wb) ||
+               overlap(ws, (int64_t)bytes, y, xb) || overlap(ws, (int64_t)bytes, dpre, xb) ||
+               overlap(ws, (int64_t)bytes, dbias, bb);
+    };
+    if (hits(need)) return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
+    // (beyond the required bytes the workspace is used only where it holds all that is wanted)
+    const size_t want = conv_bwd_data_relu_ws_want(dti, s, xs);
+    const size_t use = ws_bytes >= want && !hits(want) ? want : need;
     BiasPartials bp{nullptr, 0};
     TRY(hip_status(launch_conv_bwd_data_relu(dti, dy, dyd.pixel_stride ? dyd.pixel_stride : dyd.c, w, dpre, xs, y,
-                                             beta, dbias, (float *)ws, s, st, dbias ? nullptr : &bp),
+                                             beta, dbias, (float *)ws, use, s, st, dbias ? nullptr : &bp),
                    "conv2d_bwd_input_relu_bwd"));
     if (dbias == nullptr) note_partials(bp.part, bp.rows);
     return ok();

@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256, 1) void band_fwd_kernel(const BandArgs a) {
     // padded taps, channels and rows), copied straight to LDS: copy i covers rows 8 i .. 8 i + 7.
     for (int i = wave; i < a.nks * 4; i += 4) {
         const int m = 8 * i + (lane >> 3);
-        const int ch = (lane & 7) ^ kmajor_swz<64>(m);
+        const int ch = (lane & 7) ^ kmajor_swz<bf16_t, 64>(m);
         const int c = m & 3;
         uint32_t kh, kw;
         a.dKwp.divmod((uint32_t)(m >> 2), kh, kw);
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256, 1) void band_fwd_kernel(const BandArgs a) {
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
                     const int row = 16 * x + 4 * (ld & 3);
-                    fi[x] = lds_tr_pair(filt + kmajor_off<64>(k, row), filt + kmajor_off<64>(k + 4, row));
+                    fi[x] = lds_tr_pair(filt + kmajor_off<bf16_t, 64>(k, row), filt + kmajor_off<bf16_t, 64>(k + 4, row));
                 }
             };
             auto mma = [&](const U4 (&fi)[4], const U4 (&fj)[4]) __attribute__((always_inline)) {
@@ -334,7 +334,7 @@ __device__ __forceinline__ void band_fwd_reg_body(const BandArgs &a, unsigned ch
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
             const int row = 16 * x + 4 * (ld & 3);
-            fw[kk][x] = lds_tr_pair(xb0 + kmajor_off<64>(k, row), xb0 + kmajor_off<64>(k + 4, row));
+            fw[kk][x] = lds_tr_pair(xb0 + kmajor_off<bf16_t, 64>(k, row), xb0 + kmajor_off<bf16_t, 64>(k + 4, row));
         }
     }
     wait_barrier<0>();                              // every wave holds its filter: the staging area is free
@@ -497,7 +497,7 @@ __global__ __launch_bounds__(256, 1) void band_fwd_reg_kernel(const BandArgs a) 
     // transposing-read swizzle, staged over both band buffers: copy i covers rows 8 i .. 8 i + 7.
     for (int i = wave; i < KS * 4; i += 4) {
         const int m = 8 * i + (lane >> 3);
-        const int ch = (lane & 7) ^ kmajor_swz<64>(m);
+        const int ch = (lane & 7) ^ kmajor_swz<bf16_t, 64>(m);
         const int c = m & 3;
         uint32_t kh, kw;
         a.dKwp.divmod((uint32_t)(m >> 2), kh, kw);
@@ -556,7 +556,7 @@ __global__ __launch_bounds__(NW * 64, 1) void band_bwf_kernel(const BandArgs a) 
         const bf16_t *base = a.dy + ((int64_t)n * a.OH + oh0) * a.OW * a.ys + co0;
         const int i = wave + NW * j;
         const int k = 8 * i + (lane >> 3);
-        const int ch = (lane & 7) ^ kmajor_swz<64>(k);
+        const int ch = (lane & 7) ^ kmajor_swz<bf16_t, 64>(k);
         const bool ok = k < pb && co0 + ch * 8 < a.K;
         dma16(ok ? (const void *)(base + (int64_t)k * a.ys + ch * 8) : (const void *)g_zero_chunk,
               buf + 1024 * i);
@@ -610,7 +610,7 @@ __global__ __launch_bounds__(NW * 64, 1) void band_bwf_kernel(const BandArgs a) 
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
                 const int row = 16 * x + 4 * (ld & 3);
-                fi[x] = lds_tr_pair(dc + kmajor_off<64>(k0, row), dc + kmajor_off<64>(k0 + 4, row));
+                fi[x] = lds_tr_pair(dc + kmajor_off<bf16_t, 64>(k0, row), dc + kmajor_off<bf16_t, 64>(k0 + 4, row));
             }
         };
         auto load_x = [&](const int (&pbase)[2], int y) __attribute__((always_inline)) -> U4 {

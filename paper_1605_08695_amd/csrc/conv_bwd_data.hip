@@ -15,10 +15,10 @@ static Igemm2Tile bwd_data_tiles(int ni, int mj, int zdim) {
 
 // Rows of bias-gradient partials of the fused ReLU-backward epilogue: one per block and wave
 // column of the pipelined kernel's grid.
-static int relu_partial_rows(const ConvShape &s) {
+static int relu_partial_rows(int dt, const ConvShape &s) {
     const int mj = s.N * ((s.H + s.sh - 1) / s.sh) * ((s.W + s.sw - 1) / s.sw);
     const int z = s.sh * s.sw;
-    const Igemm2Tile t = bwd_data_tiles(s.C, mj, z);
+    const Igemm2Tile t = dt == 0 ? igemm2_tiles_f32(s.C) : bwd_data_tiles(s.C, mj, z);
     return z * ((mj + t.bj - 1) / t.bj) * (t.nw / 2);
 }
 
@@ -98,11 +98,27 @@ static hipError_t conv_bwd_data_t(const void *dy, int64_t dys, const void *w, vo
             if (relu_y != nullptr) {
                 a.relu_y = relu_y;
                 a.db_part = ws;
-                a.db_rows = relu_partial_rows(s);
+                a.db_rows = relu_partial_rows(1, s);
                 *db_parts = a.db_rows;
                 *db_at = ws;
             }
             if (!igemm2_launch<DIR_BWD_DATA>(a, mj, z, bwd_data_tiles(a.NI, mj, z), st)) return hipErrorInvalidValue;
+            return hipGetLastError();
+        }
+    }
+    if constexpr (sizeof(T) == 4) {
+        if (vi && vj && s.C % EPC == 0 && dxs % EPC == 0 && aligned16p(dx) &&
+            (relu_y == nullptr || aligned16p(relu_y)) &&
+            igemm2_fits(a, (int64_t)s.KH * s.KW * s.C * s.K * 4, span_bytes((int64_t)s.N * s.OH * s.OW, dys, s.K, 4))) {
+            if (relu_y != nullptr) {
+                a.relu_y = relu_y;
+                a.db_part = ws;
+                a.db_rows = relu_partial_rows(0, s);
+                *db_parts = a.db_rows;
+                *db_at = ws;
+            }
+            if (!igemm2_launch_f32<DIR_BWD_DATA>(a, mj, s.sh * s.sw, igemm2_tiles_f32(a.NI), st))
+                return hipErrorInvalidValue;
             return hipGetLastError();
         }
     }
@@ -116,16 +132,25 @@ size_t conv_bwd_data_relu_ws_bytes(int dt, const ConvShape &s, int64_t dxs) {
     relu_bwd_plan(dt, (int64_t)s.N * s.H * s.W, s.C, dxs, &G, &ppb);
     const size_t fallback = (size_t)G * s.C * sizeof(float);
     if (dt != 1) return fallback;
-    return std::max({fallback, (size_t)relu_partial_rows(s) * s.C * sizeof(float), split_ws_bytes(dt, s, true)});
+    return std::max({fallback, (size_t)relu_partial_rows(1, s) * s.C * sizeof(float), split_ws_bytes(dt, s, true)});
+}
+
+// The fp32 kernel's partials may take more than the workspace that the unfused pair needs: the
+// query asks for them, and a call given less runs the pair.
+size_t conv_bwd_data_relu_ws_want(int dt, const ConvShape &s, int64_t dxs) {
+    const size_t need = conv_bwd_data_relu_ws_bytes(dt, s, dxs);
+    return dt == 0 ? std::max(need, (size_t)relu_partial_rows(0, s) * s.C * sizeof(float)) : need;
 }
 
 hipError_t launch_conv_bwd_data_relu(int dt, const void *dy, int64_t dys, const void *w, void *dpre, int64_t dxs,
-                                     const void *y, float beta, float *db, float *ws, const ConvShape &s,
-                                     hipStream_t st, BiasPartials *defer) {
+                                     const void *y, float beta, float *db, float *ws, size_t ws_bytes,
+                                     const ConvShape &s, hipStream_t st, BiasPartials *defer) {
     int parts = 0;
     float *db_at = nullptr;
-    if (dt == 1 && ((uintptr_t)y & 7) == 0) {
-        const hipError_t e = conv_bwd_data_t<bf16_t>(dy, dys, w, dpre, dxs, beta, s, st, ws, y, &parts, &db_at);
+    if (dt == 1 ? ((uintptr_t)y & 7) == 0 : ws_bytes >= conv_bwd_data_relu_ws_want(dt, s, dxs)) {
+        const hipError_t e = dt == 1
+            ? conv_bwd_data_t<bf16_t>(dy, dys, w, dpre, dxs, beta, s, st, ws, y, &parts, &db_at)
+            : conv_bwd_data_t<float>(dy, dys, w, dpre, dxs, beta, s, st, ws, y, &parts, &db_at);
         if (e != hipSuccess) return e;
         if (parts > 0) {
             if (defer != nullptr) {

@@ -11,6 +11,8 @@ struct BwfPlan {
     Igemm2Tile t;      // configuration of the pipelined bf16 kernel
 };
 
+BwfPlan bwf_plan_f32(const ConvShape &s);
+
 // Tiles and split-K of one bwd-filter launch, chosen from sweeps over the AlexNet/VGG
 // shapes: 128 x 128 tiles (even for 192 output channels, where the second channel tile
 // is half empty) and the pixel reduction split into as many parts as keep the blocks within
@@ -23,6 +25,7 @@ struct BwfPlan {
 // forward pass, need more registers here than two waves per SIMD have and spill.)
 BwfPlan bwf_plan(int dt, const ConvShape &s, bool v2) {
     BwfPlan p;
+    if (dt == 0 && v2) return bwf_plan_f32(s);
     const int bk = dt == 0 ? 32 : 64;
     const int m = s.KH * s.KW * s.C;
     // output channels a multiple of 64 but not of 128 (AlexNet conv2's 192): 64-channel tiles leave
@@ -48,6 +51,22 @@ BwfPlan bwf_plan(int dt, const ConvShape &s, bool v2) {
     sp = std::min<int64_t>(sp, 4096);
     const int64_t per = (ktiles + sp - 1) / sp;                 // K tiles per split
     p.k_split = (int)(per * bk);
+    p.splits = (int)((ktiles + per - 1) / per);
+    return p;
+}
+
+// fp32: 64 x 64 (32 x 64) tiles, splits that fill one round of three blocks per CU, and at most as
+// many as the register-staged kernel's plan, whose partials size the workspace.
+BwfPlan bwf_plan_f32(const ConvShape &s) {
+    BwfPlan p;
+    p.t = igemm2_tiles_f32(s.K);
+    p.bi = p.t.bi;
+    p.bj = p.t.bj;
+    const int tiles = ((s.K + p.bi - 1) / p.bi) * ((s.KH * s.KW * s.C + p.bj - 1) / p.bj);
+    const int64_t ktiles = ((int64_t)s.N * s.OH * s.OW + 31) / 32;
+    int64_t sp = std::min<int64_t>(std::max(1, 768 / tiles), bwf_plan(0, s, false).splits);
+    const int64_t per = (ktiles + sp - 1) / sp;
+    p.k_split = (int)(per * 32);
     p.splits = (int)((ktiles + per - 1) / per);
     return p;
 }
@@ -96,12 +115,10 @@ static hipError_t conv_bwd_filter_t(const void *x, int64_t xs, const void *dy, i
     hipError_t e;
     BwfPlan p;
     bool v2 = false;
-    if constexpr (sizeof(T) == 2) {
-        if (vi && vj && igemm2_fits(a, span_bytes((int64_t)s.N * s.OH * s.OW, dys, s.K),
-                                    span_bytes((int64_t)s.N * s.H * s.W, xs, s.C))) {
-            p = bwf_plan(dti, s, true);
-            v2 = p.splits > 1 || aligned16p(dw);
-        }
+    if (vi && vj && igemm2_fits(a, span_bytes((int64_t)s.N * s.OH * s.OW, dys, s.K, sizeof(T)),
+                                span_bytes((int64_t)s.N * s.H * s.W, xs, s.C, sizeof(T)))) {
+        p = bwf_plan(dti, s, true);
+        v2 = p.splits > 1 || aligned16p(dw);
     }
     if (v2) {
         a.out = p.splits > 1 ? ws : (void *)dw;
@@ -109,7 +126,9 @@ static hipError_t conv_bwd_filter_t(const void *x, int64_t xs, const void *dy, i
         // (each XCD runs a contiguous range of a split's tiles: they read the same pixel range of
         // x and dy, from one L2; AlexNet conv2-5: 232 -> 228 us)
         a.xcd_order = 1;
-        e = igemm2_launch<DIR_BWD_FILTER>(a, m, p.splits, p.t, st) ? hipGetLastError() : hipErrorInvalidValue;
+        const bool done = sizeof(T) == 4 ? igemm2_launch_f32<DIR_BWD_FILTER>(a, m, p.splits, p.t, st)
+                                         : igemm2_launch<DIR_BWD_FILTER>(a, m, p.splits, p.t, st);
+        e = done ? hipGetLastError() : hipErrorInvalidValue;
     } else {
         p = bwf_plan(dti, s, false);
         a.out = p.splits > 1 ? ws : (void *)dw;

@@ -61,6 +61,13 @@ static hipError_t conv_fwd_t(const void *x, int64_t xs, const void *w, void *y, 
             return hipGetLastError();
         }
     }
+    if constexpr (sizeof(T) == 4) {
+        if (vi && vj && ys % EPC == 0 && aligned16p(y) &&
+            igemm2_fits(a, (int64_t)s.KH * s.KW * s.C * s.K * 4, span_bytes((int64_t)s.N * s.H * s.W, xs, s.C, 4))) {
+            if (!igemm2_launch_f32<DIR_FWD>(a, mj, 1, igemm2_tiles_f32(a.NI), st)) return hipErrorInvalidValue;
+            return hipGetLastError();
+        }
+    }
     return igemm_launch<T, DIR_FWD>(a, mj, 1, vi, vj, st);
 }
 

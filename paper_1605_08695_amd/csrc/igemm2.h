@@ -1,4 +1,4 @@
-// Pipelined bf16 implicit-GEMM convolution for gfx950 (all three directions).
+// Pipelined implicit-GEMM convolution for gfx950 (all three directions, bf16 and fp32).
 //
 // Same GEMM views as igemm.h (I side = output channels, J side = rows), but
 // built for latency hiding on CDNA4:
@@ -10,11 +10,10 @@
 //    given the chunk that belongs at its LDS slot, as a 32-bit byte offset into
 //    its operand; out-of-range chunks get an offset past the operand's end,
 //    which the buffer range check turns into zeros.
-//  * A ring of three LDS stages: the copies of K-tile t+2 are in flight while
-//    the MFMAs consume tile t.  Each stage is a separate LDS object and the
-//    loop is unrolled by three, so the compiler can see which stage an LDS
-//    read touches and only waits for the copies it depends on
-//    (s_waitcnt vmcnt(n) with n = the copies of the next tile).
+//  * A ring of NS LDS stages (two to four): the copies of K-tiles t+1 .. t+NS-1 are
+//    in flight while the MFMAs consume tile t.  Each stage is a separate LDS
+//    object and the loop is unrolled by NS; a step waits only for the copies of
+//    its own tile (s_waitcnt vmcnt(n) with n = the copies of the later tiles).
 //  * Operands whose memory is k-contiguous (im2col rows of x, the dy gather
 //    and the filter in bwd-input) are kept as [row][k] with 16-byte chunks
 //    XOR-swizzled by (row & 7) and read with ds_read_b128.  Operands that are
@@ -23,10 +22,13 @@
 //    in memory, with chunks swizzled by k (kmajor_swz); the MFMA fragment (eight
 //    consecutive k of one row per lane) is assembled by two ds_read_b64_tr_b16
 //    transposing reads.  No operand is transposed in registers.
+//  * fp32 keeps the same byte layouts with 32-element K-tiles (16-byte chunks of four);
+//    a k-major fragment is four 4-byte reads, whose swizzle by (k >> 2) puts the four
+//    16-lane groups of a read (k-rows four apart) on different banks.
 //
-// Requirements (checked by the launcher): bf16, every gathered 16-byte chunk
+// Requirements (checked by the launcher): every gathered 16-byte chunk
 // is aligned and lies within one pixel's channels (channel counts and pixel
-// strides multiples of 8, 16-byte aligned bases), both operands span fewer
+// strides multiples of 8 (bf16) or 4 (fp32), 16-byte aligned bases), both operands span fewer
 // than 2^31 bytes and the filter has at most 31 rows and 31 columns.
 #pragma once
 #include <type_traits>
@@ -124,19 +126,39 @@ __device__ __forceinline__ U4 lds_tr_pair(const unsigned char *p0, const unsigne
 // group by one chunk pair and bit 3 of k the second group by two, which keeps every chunk
 // inside its aligned group of eight.  32-row k-rows are 64 bytes: the 4 k-rows of a group already
 // cover every bank once, and bit 3 of k moves the second group to the other chunk pair.
-template <int R>
+//
+// fp32: a fragment read touches 16 consecutive rows (64 bytes, four chunks) of the k-rows
+// 4g + e, g = 0..3 the lane group; (k >> 2) & 3 moves each group to its own 64 bytes of the
+// banks (32-row tiles, whose k-rows are 128 bytes, have two such places: two groups share one).
+template <typename T, int R>
 __device__ __forceinline__ int kmajor_swz(int k) {
-    static_assert(R == 32 || R == 64 || R == 128 || R == 192 || R == 256, "k-major tile rows");
-    if constexpr (R == 32) return ((k >> 3) & 1) << 1;
-    else if constexpr (R == 64) return ((k & 3) ^ ((k >> 3) & 1)) << 1;
-    else if constexpr (R != 192) return ((k & 3) << 1) ^ (((k >> 3) & 1) << 3);
-    else return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+    if constexpr (sizeof(T) == 4) {
+        static_assert(R == 32 || R % 64 == 0, "k-major tile rows");
+        return R == 32 ? ((k >> 2) & 1) << 2 : ((k >> 2) & 3) << 2;
+    } else {
+        static_assert(R == 32 || R == 64 || R == 128 || R == 192 || R == 256, "k-major tile rows");
+        if constexpr (R == 32) return ((k >> 3) & 1) << 1;
+        else if constexpr (R == 64) return ((k & 3) ^ ((k >> 3) & 1)) << 1;
+        else if constexpr (R != 192) return ((k & 3) << 1) ^ (((k >> 3) & 1) << 3);
+        else return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
+    }
 }
 
-// Byte offset of element (k, row) of a k-major tile with R rows (row a multiple of 4).
-template <int R>
+// Byte offset of element (k, row) of a k-major tile with R rows (bf16: row a multiple of 4).
+template <typename T, int R>
 __device__ __forceinline__ int kmajor_off(int k, int row) {
-    return k * (R * 2) + (((row >> 3) ^ kmajor_swz<R>(k)) << 4) + ((row & 7) << 1);
+    if constexpr (sizeof(T) == 4) return k * (R * 4) + (((row >> 2) ^ kmajor_swz<T, R>(k)) << 4) + ((row & 3) << 2);
+    else return k * (R * 2) + (((row >> 3) ^ kmajor_swz<T, R>(k)) << 4) + ((row & 7) << 1);
+}
+
+// Four consecutive k (from k4, a multiple of 4) of one row of an fp32 k-major tile with R rows.
+template <int R>
+__device__ __forceinline__ U4 lds_k4(const unsigned char *tile, int k4, int row) {
+    // (the swizzle is the same for the four k)
+    const uint32_t *p = reinterpret_cast<const uint32_t *>(tile + kmajor_off<float, R>(k4, row));
+    U4 r;
+    r.x = p[0]; r.y = p[R]; r.z = p[2 * R]; r.w = p[3 * R];
+    return r;
 }
 
 // Workgroups are dealt to the 8 XCDs of the chip round-robin by linear id, and each XCD
@@ -154,9 +176,10 @@ __device__ __forceinline__ int xcd_order(int linear, int total) {
 // SIMD runs two waves: one 8-wave block per CU, or two 4-wave blocks per CU when NS
 // stages fit twice in the 160 KiB of LDS.  Two independent blocks keep a CU's MFMAs busy
 // while the other block waits at its barrier for a slow copy.
-template <int DIR, int BI, int BJ, int NW, int NS>
+template <typename T, int DIR, int BI, int BJ, int NW, int NS>
 __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
-    constexpr int BK = 64;
+    constexpr int ES = sizeof(T), EPC = 16 / ES;      // element bytes, elements per 16-byte chunk
+    constexpr int BK = 8 * EPC;
     constexpr int WGJ = NW / 2;                       // wave grid 2 (I) x NW/2 (J)
     constexpr bool TI = DIR != DIR_BWD_DATA;          // I operand kept k-major
     constexpr bool TJ = DIR == DIR_BWD_FILTER;        // J operand kept k-major
@@ -165,13 +188,14 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     constexpr int WI = BI / 2, WJ = BJ / WGJ;
     constexpr int MI = WI / 16, MJ = WJ / 16;
     static_assert(NW == 4 || NW == 8, "waves");
-    static_assert(NS == 2 || NS == 3, "stages");
+    static_assert(NS >= 2 && NS <= 4, "stages");
     static_assert(NLI >= 1 && NLJ >= 1 && MI >= 1 && MJ >= 1, "tile");
     static_assert(NS * SB <= 160 * 1024, "LDS");
 
     __shared__ __attribute__((aligned(1024))) unsigned char lds0[SB];
     __shared__ __attribute__((aligned(1024))) unsigned char lds1[SB];
-    __shared__ __attribute__((aligned(1024))) unsigned char lds2[NS == 3 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds2[NS >= 3 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds3[NS >= 4 ? SB : 16];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -241,7 +265,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
         return;
     }
     const int nk = k_end > k_beg ? (k_end - k_beg + BK - 1) / BK : 0;
-    // K-tile order (see below): with 64 | channels and several taps the tiles are visited
+    // K-tile order (see below): with BK | channels and several taps the tiles are visited
     // channel-chunk outer, tap inner, and a split-K range [k_beg, k_end) then counts positions
     // in that order; the tile addresses come from the position, not from k_beg.
     bool perm = false;
@@ -273,21 +297,21 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     // I operand: byte offset of each copy at K-tile 0 (k-major: + kt * BK * ldI2 per tile;
     // BWD_DATA filter rows ci: + the tile's tap and channel offset)
     uint32_t ivo[NLI];
-    const uint32_t ldI2 = 2u * (uint32_t)((DIR == DIR_FWD) ? (int64_t)a.K : a.ys);
+    const uint32_t ldI2 = (uint32_t)ES * (uint32_t)((DIR == DIR_FWD) ? (int64_t)a.K : a.ys);
     if constexpr (TI) {
-        constexpr int CPR = BI / 8;
+        constexpr int CPR = BI / EPC;
 #pragma unroll
         for (int r = 0; r < NLI; ++r) {
             const int pos = (wave * NLI + r) * 64 + lane;
             const int krow = pos / CPR;
-            const int co = i0 + ((pos % CPR) ^ kmajor_swz<BI>(krow)) * 8;
-            ivo[r] = (uint32_t)(k_addr + krow) * ldI2 + 2u * (uint32_t)co;
+            const int co = i0 + ((pos % CPR) ^ kmajor_swz<T, BI>(krow)) * EPC;
+            ivo[r] = (uint32_t)(k_addr + krow) * ldI2 + (uint32_t)ES * (uint32_t)co;
         }
     } else {
 #pragma unroll
         for (int r = 0; r < NLI; ++r) {
             const int ci = i0 + 8 * (wave * NLI + r) + (lane >> 3);
-            ivo[r] = (uint32_t)ci * 2u * (uint32_t)a.K;
+            ivo[r] = (uint32_t)ci * (uint32_t)ES * (uint32_t)a.K;
         }
     }
 
@@ -298,7 +322,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     // per tile, and the byte offset and (dh, dw) displacement of its chunk's filter tap.
     uint32_t jvo[NLJ], jnh[NLJ], jnw[NLJ], tvo[NLJ];
     int ohs[NLJ], ows[NLJ], fdh[NLJ], fdw[NLJ];
-    const uint32_t xs2 = 2u * (uint32_t)a.xs, ys2 = 2u * (uint32_t)a.ys;
+    const uint32_t xs2 = (uint32_t)ES * (uint32_t)a.xs, ys2 = (uint32_t)ES * (uint32_t)a.ys;
     if constexpr (!TJ) {
         const int Hlim = (DIR == DIR_FWD) ? a.H : a.OH;
         const int Wlim = (DIR == DIR_FWD) ? a.W : a.OW;
@@ -320,7 +344,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
                 const int ow = (int)owu, oh = (int)ohu;
                 y0 = oh * a.sh - a.pt;     // tap kh reads row y0 + kh
                 x0 = ow * a.sw - a.pl;
-                jvo[r] = (uint32_t)(((((int64_t)n * a.H + y0) * a.W + x0) * a.xs) * 2);
+                jvo[r] = (uint32_t)(((((int64_t)n * a.H + y0) * a.W + x0) * a.xs) * ES);
                 hlo = max(0, -y0); hhi = min(KHp, Hlim - y0);
                 wlo = max(0, -x0); whi = min(KWp, Wlim - x0);
             } else {
@@ -330,7 +354,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
                 const int n = t / Hp;
                 y0 = th + offh;            // tap jh reads dy row y0 - jh
                 x0 = tw + offw;
-                jvo[r] = (uint32_t)(((((int64_t)n * a.OH + y0) * a.OW + x0) * a.ys) * 2);
+                jvo[r] = (uint32_t)(((((int64_t)n * a.OH + y0) * a.OW + x0) * a.ys) * ES);
                 hlo = max(0, y0 - Hlim + 1); hhi = min(KHp, y0 + 1);
                 wlo = max(0, x0 - Wlim + 1); whi = min(KWp, x0 + 1);
             }
@@ -341,26 +365,26 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     uint32_t adv_base = 0, adv_d1 = 0, adv_d2 = 0;
     int adv_w = 0, adv_h = 0, lim_w = 0, lim_h = 0;
     if constexpr (TJ) {
-        constexpr int CPR = BJ / 8;
+        constexpr int CPR = BJ / EPC;
 #pragma unroll
         for (int r = 0; r < NLJ; ++r) {
             const int pos = (wave * NLJ + r) * 64 + lane;
             const int krow = pos / CPR;
-            const int c = (pos % CPR) ^ kmajor_swz<BJ>(krow);
-            const int r0 = j0 + c * 8;
+            const int c = (pos % CPR) ^ kmajor_swz<T, BJ>(krow);
+            const int r0 = j0 + c * EPC;
             const int rr = r0 < MJ_ext ? r0 : 0;
             uint32_t t, ci, kh, kw;
             a.dC.divmod((uint32_t)rr, t, ci);
             a.dKW.divmod(t, kh, kw);
             fdw[r] = (int)kw - a.pl;
             fdh[r] = (int)kh - a.pt;
-            tvo[r] = (uint32_t)(((((int64_t)fdh[r] * a.W + fdw[r]) * a.xs) + (int64_t)ci) * 2);
+            tvo[r] = (uint32_t)(((((int64_t)fdh[r] * a.W + fdw[r]) * a.xs) + (int64_t)ci) * ES);
             uint32_t q, ow, n, oh;
             a.dOW.divmod((uint32_t)(k_beg + krow), q, ow);
             a.dOH.divmod(q, n, oh);
             ohs[r] = (int)oh * a.sh;
             ows[r] = (int)ow * a.sw;
-            jvo[r] = (uint32_t)(((((int64_t)n * a.H + ohs[r]) * a.W + ows[r]) * a.xs) * 2);
+            jvo[r] = (uint32_t)(((((int64_t)n * a.H + ohs[r]) * a.W + ows[r]) * a.xs) * ES);
         }
         // BK pixels = dn images + ah rows + aw columns (ah < OH, aw < OW); adding them to
         // (oh, ow) wraps each coordinate at most once.
@@ -369,9 +393,9 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
         adv_w = aw * a.sw; lim_w = a.OW * a.sw;
         adv_h = ah * a.sh; lim_h = a.OH * a.sh;
         const int64_t hw = (int64_t)a.H * a.W;
-        adv_base = (uint32_t)(((int64_t)dn * hw + (int64_t)ah * a.sh * a.W + (int64_t)aw * a.sw) * a.xs * 2);
-        adv_d1 = (uint32_t)(((int64_t)a.sh * a.W - (int64_t)a.OW * a.sw) * a.xs * 2);   // column wrap
-        adv_d2 = (uint32_t)((hw - (int64_t)a.OH * a.sh * a.W) * a.xs * 2);              // row wrap
+        adv_base = (uint32_t)(((int64_t)dn * hw + (int64_t)ah * a.sh * a.W + (int64_t)aw * a.sw) * a.xs * ES);
+        adv_d1 = (uint32_t)(((int64_t)a.sh * a.W - (int64_t)a.OW * a.sw) * a.xs * ES);   // column wrap
+        adv_d2 = (uint32_t)((hw - (int64_t)a.OH * a.sh * a.W) * a.xs * ES);              // row wrap
     }
     // k decomposition of this lane's chunk for [row][k] operands.  FWD J: k = (kh, kw, ci)
     // over (KH, KW, C); BWD_DATA: k = (jh, jw, co) over (KHp, KWp, K).
@@ -379,7 +403,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     if constexpr (DIR == DIR_FWD) { dInner = a.dC; dMid = a.dKW; }
     if constexpr (DIR == DIR_BWD_DATA) { dInner = a.dK; dMid.init((uint32_t)(KWp > 0 ? KWp : 1)); }
 
-    // K-tile order.  With 64 | channels, every 64-wide K-tile lies inside one filter tap,
+    // K-tile order.  With BK | channels, every K-tile lies inside one filter tap,
     // and the tiles are visited channel-chunk outer, tap inner: consecutive tiles then read
     // the same input rows shifted by one tap, which stay in L1/L2.  issue() is called for
     // kt = 0, 1, 2, ... in order, so the (chunk, tap) position advances by one per call; the
@@ -405,14 +429,14 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
         if constexpr (DIR != DIR_BWD_FILTER) {
             if (perm) {
                 kq0 = perm_kh; kq1 = perm_kw;
-                kq2 = perm_cc * BK + dchunk * 8;
+                kq2 = perm_cc * BK + dchunk * EPC;
                 kt = (perm_kh * KWp + perm_kw) * perm_CC + perm_cc;
                 if (++perm_kw == KWp) {
                     perm_kw = 0;
                     if (++perm_kh == KHp) { perm_kh = 0; ++perm_cc; }
                 }
             } else {
-                const int k = k_beg + kt * BK + dchunk * 8;
+                const int k = k_beg + kt * BK + dchunk * EPC;
                 kin = k < k_end;
                 uint32_t t;
                 dInner.divmod((uint32_t)k, t, kq2);
@@ -427,7 +451,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
         } else {
             // BWD_DATA filter: w[rh + sh*jh][rw + sw*jw][ci][co..]
             const uint32_t tap = (uint32_t)(rh + a.sh * (int)kq0) * (uint32_t)a.KW + (uint32_t)(rw + a.sw * (int)kq1);
-            const uint32_t koff = kin ? (tap * (uint32_t)a.C * (uint32_t)a.K + kq2) * 2u : kBad;
+            const uint32_t koff = kin ? (tap * (uint32_t)a.C * (uint32_t)a.K + kq2) * (uint32_t)ES : kBad;
 #pragma unroll
             for (int r = 0; r < NLI; ++r) bdma16(rsI, ivo[r] + koff, stI + (wave * NLI + r) * 1024);
         }
@@ -450,8 +474,8 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
             }
         } else {
             uint32_t koff;
-            if constexpr (DIR == DIR_FWD) koff = (kq0 * (uint32_t)a.W + kq1) * xs2 + kq2 * 2u;
-            else koff = kq2 * 2u - (kq0 * (uint32_t)a.OW + kq1) * ys2;
+            if constexpr (DIR == DIR_FWD) koff = (kq0 * (uint32_t)a.W + kq1) * xs2 + kq2 * (uint32_t)ES;
+            else koff = kq2 * (uint32_t)ES - (kq0 * (uint32_t)a.OW + kq1) * ys2;
             const uint32_t khe = kin ? kq0 : 31u;
 #pragma unroll
             for (int r = 0; r < NLJ; ++r) {
@@ -480,10 +504,12 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
 #pragma unroll
             for (int x = 0; x < MI; ++x) {
                 const int rb = wi * WI + x * 16;
-                if constexpr (TI) {
+                if constexpr (TI && ES == 4) {
+                    fi[x] = lds_k4<BI>(stI, 16 * s + 4 * lg, rb + ld);
+                } else if constexpr (TI) {
                     const int k = 32 * s + 8 * lg + (ld >> 2);
                     const int row = rb + 4 * (ld & 3);
-                    fi[x] = lds_tr_pair(stI + kmajor_off<BI>(k, row), stI + kmajor_off<BI>(k + 4, row));
+                    fi[x] = lds_tr_pair(stI + kmajor_off<T, BI>(k, row), stI + kmajor_off<T, BI>(k + 4, row));
                 } else {
                     const int row = rb + ld;
                     fi[x] = *reinterpret_cast<const U4 *>(stI + lds_off(row, 4 * s + lg));
@@ -492,10 +518,12 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
 #pragma unroll
             for (int y = 0; y < MJ; ++y) {
                 const int rb = wj * WJ + y * 16;
-                if constexpr (TJ) {
+                if constexpr (TJ && ES == 4) {
+                    fj[y] = lds_k4<BJ>(stJ, 16 * s + 4 * lg, rb + ld);
+                } else if constexpr (TJ) {
                     const int k = 32 * s + 8 * lg + (ld >> 2);
                     const int row = rb + 4 * (ld & 3);
-                    fj[y] = lds_tr_pair(stJ + kmajor_off<BJ>(k, row), stJ + kmajor_off<BJ>(k + 4, row));
+                    fj[y] = lds_tr_pair(stJ + kmajor_off<T, BJ>(k, row), stJ + kmajor_off<T, BJ>(k + 4, row));
                 } else {
                     const int row = rb + ld;
                     fj[y] = *reinterpret_cast<const U4 *>(stJ + lds_off(row, 4 * s + lg));
@@ -504,19 +532,21 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
 #pragma unroll
             for (int x = 0; x < MI; ++x)
 #pragma unroll
-                for (int y = 0; y < MJ; ++y) Mfma<bf16_t>::run(acc[x][y], fi[x], fj[y]);
+                for (int y = 0; y < MJ; ++y) Mfma<T>::run(acc[x][y], fi[x], fj[y]);
         }
         // Schedule: the fragment reads of the first sub-step, then the MFMAs of the first
         // sub-step alternating with the reads of the second, then its MFMAs -- so the LDS
         // latency of the second sub-step hides under MFMAs (about 2 % on the AlexNet layers).
-        constexpr int RD = (TI ? 2 : 1) * MI + (TJ ? 2 : 1) * MJ;     // LDS reads per sub-step
+        constexpr int RK = ES == 4 ? 4 : 2;                             // LDS reads per k-major fragment
+        constexpr int RD = (TI ? RK : 1) * MI + (TJ ? RK : 1) * MJ;     // LDS reads per sub-step
+        constexpr int NM = (ES == 4 ? 4 : 1) * MI * MJ;                 // MFMAs per sub-step
         __builtin_amdgcn_sched_group_barrier(0x100, RD, 0);             // DS reads
 #pragma unroll
-        for (int q = 0; q < MI * MJ; ++q) {
+        for (int q = 0; q < NM; ++q) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);          // one MFMA
             if (q < RD) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, MI * MJ, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, NM, 0);
     };
 
     // One pipeline step on stage S = kt % NS: wait for tile kt (the copies of the later
@@ -524,15 +554,14 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     // (every wave has passed the barrier, so none still reads it) with tile kt + NS - 1.
     auto stage = [&](auto S_) __attribute__((always_inline)) -> unsigned char * {
         constexpr int S = decltype(S_)::value % NS;
-        return S == 0 ? lds0 : (S == 1 ? lds1 : lds2);
+        return S == 0 ? lds0 : (S == 1 ? lds1 : (S == 2 ? lds2 : lds3));
     };
     auto step = [&](auto S_, int kt) __attribute__((always_inline)) {
         constexpr int S = decltype(S_)::value;
-        if constexpr (NS == 3) {
-            if (kt + 1 < nk) wait_barrier<NL>(); else wait_barrier<0>();
-        } else {
-            wait_barrier<0>();
-        }
+        // (the copies of the min(NS - 2, nk - 1 - kt) tiles after kt that are already issued)
+        if (NS >= 4 && kt + 2 < nk) wait_barrier<(NS - 2) * NL>();
+        else if (NS >= 3 && kt + 1 < nk) wait_barrier<NL>();
+        else wait_barrier<0>();
         if (kt + NS - 1 < nk) issue(kt + NS - 1, stage(std::integral_constant<int, S + NS - 1>{}));
         if constexpr (DIR != DIR_BWD_FILTER) {
             // A CU runs two blocks of a launch side by side, and issue arbitration favours the
@@ -570,15 +599,18 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
 
     if (nk > 0) {
         issue(0, lds0);
-        if (NS == 3 && nk > 1) issue(1, lds1);
+        if (NS >= 3 && nk > 1) issue(1, lds1);
+        if (NS >= 4 && nk > 2) issue(2, lds2);
         int kt = 0;
         for (; kt + NS <= nk; kt += NS) {
             step(std::integral_constant<int, 0>{}, kt);
             step(std::integral_constant<int, 1>{}, kt + 1);
-            if constexpr (NS == 3) step(std::integral_constant<int, 2>{}, kt + 2);
+            if constexpr (NS >= 3) step(std::integral_constant<int, 2>{}, kt + 2);
+            if constexpr (NS >= 4) step(std::integral_constant<int, 3>{}, kt + 3);
         }
         if (kt < nk) step(std::integral_constant<int, 0>{}, kt);
-        if (NS == 3 && kt + 1 < nk) step(std::integral_constant<int, 1>{}, kt + 1);
+        if (NS >= 3 && kt + 1 < nk) step(std::integral_constant<int, 1>{}, kt + 1);
+        if (NS >= 4 && kt + 2 < nk) step(std::integral_constant<int, 2>{}, kt + 2);
     }
 
     // ------------------------------------------------------------ epilogue
@@ -589,7 +621,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     // forward with a fused max-pool: the band's bf16 outputs are staged in LDS (channels of the
     // first half of the tile in lds0, of the second in lds1, [row][channel]) once every wave has
     // finished reading the operand stages
-    constexpr bool kPoolFits = DIR == DIR_FWD && BJ * BI <= 128 * (BI + BJ) && BI % 4 == 0;
+    constexpr bool kPoolFits = ES == 2 && DIR == DIR_FWD && BJ * BI <= 128 * (BI + BJ) && BI % 4 == 0;
     const bool pooled = kPoolFits && banded && a.pool_y != nullptr;
     constexpr int HC = BI / 2;                        // channels per staging half
     if (pooled) __syncthreads();
@@ -646,7 +678,36 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
             }
             if constexpr (DIR == DIR_BWD_FILTER) {
                 float *o = reinterpret_cast<float *>(a.out) + rowoff + i;
-                *reinterpret_cast<f32x4_t *>(o) = v;          // NI % 8 == 0 and rows 16-byte aligned
+                *reinterpret_cast<f32x4_t *>(o) = v;          // NI % 4 == 0 and rows 16-byte aligned
+            } else if constexpr (ES == 4) {
+                float *o = reinterpret_cast<float *>(a.out) + rowoff + i;
+                f32x4_t r = v;
+                if constexpr (DIR == DIR_BWD_DATA) {
+                    if (a.beta != 0.f) {
+                        const f32x4_t old = *reinterpret_cast<const f32x4_t *>(o);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) r[q] += a.beta * old[q];
+                    }
+                    if (relu) {
+                        const f32x4_t yy = *reinterpret_cast<const f32x4_t *>(
+                            reinterpret_cast<const float *>(a.relu_y) + rowoff + i);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            r[q] = yy[q] > 0.f ? r[q] : 0.f;
+                            cs[x][q] += r[q];
+                        }
+                    }
+                }
+                if constexpr (DIR == DIR_FWD) {
+                    if (a.bias != nullptr) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float b = r[q] + bq[x][q];
+                            r[q] = b > 0.f ? b : 0.f;
+                        }
+                    }
+                }
+                *reinterpret_cast<f32x4_t *>(o) = r;
             } else {
                 bf16_t *o = reinterpret_cast<bf16_t *>(a.out) + rowoff + i;
                 float r4[4] = {v[0], v[1], v[2], v[3]};

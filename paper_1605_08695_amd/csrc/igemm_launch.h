@@ -80,9 +80,31 @@ static inline Igemm2Tile igemm2_tiles_narrow(int ni, int mj, int zdim) {
     return igemm2_tiles(ni, mj, zdim);
 }
 
-template <int DIR, int BI, int BJ, int NW, int NS>
+// fp32 tiles.  The fp32 matrix rate is a sixteenth of bf16's, so small tiles already keep the
+// matrix cores busy (a 32 x 32 wave tile takes 1024 matrix cycles per K tile against 64 cycles of
+// its own LDS reads) and give small layers the most blocks: 64 x 64 tiles, or 32 x 64 where 64-row
+// tiles would compute a sixth or more of their rows for nothing (at most 32 channels, 96, 160).
+// 16 x 28 x 28 x 96 -> 128, 3 x 3: forward 36 us with 64 x 64, 64 x 128 or 128 x 64 tiles, 64 with
+// 128 x 128 (register-staged kernel: 80); its input gradient 44 us with 32 x 64, 51 with 64 x 64
+// (register-staged kernel with its separate ReLU backward: 106).
+static inline Igemm2Tile igemm2_tiles_f32(int ni) {
+    const int r32 = (ni + 31) / 32 * 32, r64 = (ni + 63) / 64 * 64;
+    return (r64 - r32) * 6 >= r64 ? Igemm2Tile{32, 64, 4, 3} : Igemm2Tile{64, 64, 4, 3};
+}
+
+template <typename T, int DIR, int BI, int BJ, int NW, int NS>
 static void igemm2_go(const IgArgs &a, dim3 grid, hipStream_t st) {
-    hipLaunchKernelGGL((igemm2_kernel<DIR, BI, BJ, NW, NS>), grid, dim3(NW * 64), 0, st, a);
+    hipLaunchKernelGGL((igemm2_kernel<T, DIR, BI, BJ, NW, NS>), grid, dim3(NW * 64), 0, st, a);
+}
+
+template <int DIR>
+static bool igemm2_launch_f32(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipStream_t st) {
+    a.tiles_i = (a.NI + t.bi - 1) / t.bi;
+    const dim3 grid((unsigned)(a.tiles_i * ((mj + t.bj - 1) / t.bj)), 1, (unsigned)zdim);
+    if (t.bj != 64 || t.nw != 4 || t.ns != 3) return false;
+    if (t.bi == 32) { igemm2_go<float, DIR, 32, 64, 4, 3>(a, grid, st); return true; }
+    if (t.bi == 64) { igemm2_go<float, DIR, 64, 64, 4, 3>(a, grid, st); return true; }
+    return false;
 }
 
 // Launches one of the compiled configurations; false if t is not one of them.
@@ -93,43 +115,43 @@ static bool igemm2_launch(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipS
     const dim3 grid((unsigned)(a.tiles_i * tiles_j), 1, (unsigned)zdim);
     const int key = ((t.bi / 64) << 12) | ((t.bj / 64) << 8) | (t.nw << 4) | t.ns;
     if (t.bi == 32 && t.bj == 128 && t.nw == 4 && t.ns == 2) {
-        igemm2_go<DIR, 32, 128, 4, 2>(a, grid, st);
+        igemm2_go<bf16_t, DIR, 32, 128, 4, 2>(a, grid, st);
         return true;
     }
     if (t.bi == 128 && t.bj == 96 && t.nw == 4 && t.ns == 2) {
         // (96-row k-major tiles are not laid out: forward and bwd-input only)
         if constexpr (DIR == DIR_BWD_FILTER) return false;
-        else { igemm2_go<DIR, 128, 96, 4, 2>(a, grid, st); return true; }
+        else { igemm2_go<bf16_t, DIR, 128, 96, 4, 2>(a, grid, st); return true; }
     }
     if (t.bj == 192 && t.nw == 4 && t.ns == 2) {
         // (192-row J tiles: the forward row bands of a fused max-pool and 64-channel forward
         // tiles; 192-row k-major tiles are not laid out)
         if constexpr (DIR == DIR_BWD_FILTER) return false;
         else {
-            if (t.bi == 64) { igemm2_go<DIR, 64, 192, 4, 2>(a, grid, st); return true; }
-            if (t.bi == 128) { igemm2_go<DIR, 128, 192, 4, 2>(a, grid, st); return true; }
-            if (t.bi == 192) { igemm2_go<DIR, 192, 192, 4, 2>(a, grid, st); return true; }
+            if (t.bi == 64) { igemm2_go<bf16_t, DIR, 64, 192, 4, 2>(a, grid, st); return true; }
+            if (t.bi == 128) { igemm2_go<bf16_t, DIR, 128, 192, 4, 2>(a, grid, st); return true; }
+            if (t.bi == 192) { igemm2_go<bf16_t, DIR, 192, 192, 4, 2>(a, grid, st); return true; }
             return false;
         }
     }
     if (t.bi == 192 && t.bj == 96 && t.nw == 4 && t.ns == 2) {
         if constexpr (DIR == DIR_BWD_FILTER) return false;
-        else { igemm2_go<DIR, 192, 96, 4, 2>(a, grid, st); return true; }
+        else { igemm2_go<bf16_t, DIR, 192, 96, 4, 2>(a, grid, st); return true; }
     }
     if (t.bi == 192 && t.bj == 128 && t.nw == 4 && t.ns == 2) {
         // (the filter-gradient direction does not fit these tiles in its registers)
         if constexpr (DIR == DIR_BWD_FILTER) return false;
-        else { igemm2_go<DIR, 192, 128, 4, 2>(a, grid, st); return true; }
+        else { igemm2_go<bf16_t, DIR, 192, 128, 4, 2>(a, grid, st); return true; }
     }
     switch (key) {
-    case (1 << 12) | (2 << 8) | (8 << 4) | 3: igemm2_go<DIR, 64, 128, 8, 3>(a, grid, st); return true;
-    case (1 << 12) | (4 << 8) | (8 << 4) | 3: igemm2_go<DIR, 64, 256, 8, 3>(a, grid, st); return true;
-    case (2 << 12) | (2 << 8) | (8 << 4) | 3: igemm2_go<DIR, 128, 128, 8, 3>(a, grid, st); return true;
-    case (2 << 12) | (4 << 8) | (8 << 4) | 3: igemm2_go<DIR, 128, 256, 8, 3>(a, grid, st); return true;
-    case (2 << 12) | (2 << 8) | (4 << 4) | 2: igemm2_go<DIR, 128, 128, 4, 2>(a, grid, st); return true;
-    case (1 << 12) | (2 << 8) | (4 << 4) | 3: igemm2_go<DIR, 64, 128, 4, 3>(a, grid, st); return true;
-    case (1 << 12) | (2 << 8) | (4 << 4) | 2: igemm2_go<DIR, 64, 128, 4, 2>(a, grid, st); return true;
-    case (1 << 12) | (4 << 8) | (4 << 4) | 2: igemm2_go<DIR, 64, 256, 4, 2>(a, grid, st); return true;
+    case (1 << 12) | (2 << 8) | (8 << 4) | 3: igemm2_go<bf16_t, DIR, 64, 128, 8, 3>(a, grid, st); return true;
+    case (1 << 12) | (4 << 8) | (8 << 4) | 3: igemm2_go<bf16_t, DIR, 64, 256, 8, 3>(a, grid, st); return true;
+    case (2 << 12) | (2 << 8) | (8 << 4) | 3: igemm2_go<bf16_t, DIR, 128, 128, 8, 3>(a, grid, st); return true;
+    case (2 << 12) | (4 << 8) | (8 << 4) | 3: igemm2_go<bf16_t, DIR, 128, 256, 8, 3>(a, grid, st); return true;
+    case (2 << 12) | (2 << 8) | (4 << 4) | 2: igemm2_go<bf16_t, DIR, 128, 128, 4, 2>(a, grid, st); return true;
+    case (1 << 12) | (2 << 8) | (4 << 4) | 3: igemm2_go<bf16_t, DIR, 64, 128, 4, 3>(a, grid, st); return true;
+    case (1 << 12) | (2 << 8) | (4 << 4) | 2: igemm2_go<bf16_t, DIR, 64, 128, 4, 2>(a, grid, st); return true;
+    case (1 << 12) | (4 << 8) | (4 << 4) | 2: igemm2_go<bf16_t, DIR, 64, 256, 4, 2>(a, grid, st); return true;
     default: return false;
     }
 }
@@ -149,10 +171,10 @@ static inline int gemm_split_plan(int ni, int mj, int64_t kred, int *k_split) {
     return (int)((ktiles + per - 1) / per);
 }
 
-// Bytes from the first element of a pixel-major bf16 operand to the end of its last
-// pixel's channels.
-static inline int64_t span_bytes(int64_t pixels, int64_t stride, int64_t ch) {
-    return pixels > 0 ? ((pixels - 1) * stride + ch) * 2 : 0;
+// Bytes from the first element of a pixel-major operand (es bytes per element) to the end of its
+// last pixel's channels.
+static inline int64_t span_bytes(int64_t pixels, int64_t stride, int64_t ch, int64_t es = 2) {
+    return pixels > 0 ? ((pixels - 1) * stride + ch) * es : 0;
 }
 
 // The pipelined kernel addresses each operand with 32-bit byte offsets (offsets from 2^31

@@ -1,0 +1,103 @@
+"""Convolution kernels at the sizes where their dispatch changes, against the CPU oracle: every
+direction, the fused forward and input-gradient epilogues, channel-slice views, and workspaces of
+the smallest accepted size."""
+import ctypes
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1605_08695_amd import ops
+from paper_1605_08695_amd._lib import load
+from tests.gpu_parity import assert_close, f64, say
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _mk(shape, dtype, rng, scale=1.0):
+    return torch.from_numpy(rng.standard_normal(shape) * scale).to(dtype).to(DEV)
+
+
+def _check_all(name, dtype, N, H, W, C, K, KH, KW, s, pads, wide=0):
+    """Forward + bias + ReLU, filter gradient, input gradient (beta 0 and 1) and its fused ReLU
+    backward of one convolution; ``wide`` > 0 makes y / dy and x / dx channel slices."""
+    say("conv path case", name, dtype)
+    rng = np.random.default_rng(zlib.crc32(name.encode()))
+    xb = torch.from_numpy(np.maximum(rng.standard_normal((N, H, W, C + wide)), 0.0)).to(dtype).to(DEV)
+    x = xb[..., wide:]
+    w = _mk((KH, KW, C, K), dtype, rng, np.sqrt(2.0 / (KH * KW * C)))
+    bias = torch.from_numpy(rng.standard_normal(K) * 0.5).to(torch.float32).to(DEV)
+    pre = oracle.conv2d_fwd(f64(x), f64(w), (s, s), pads)
+    yb = torch.full(pre.shape[:3] + (K + wide,), 7.0, dtype=dtype, device=DEV)
+    y = ops.conv2d_fwd_bias_relu(x, w, bias, s, pads, y=yb[..., wide:])
+    torch.cuda.synchronize()
+    assert_close(f64(y), oracle.bias_relu_fwd(pre, f64(bias)), dtype, label="fwd")
+    assert bool(torch.all(yb[..., :wide] == 7.0))
+    dy = _mk(pre.shape[:3] + (K + wide,), dtype, rng)[..., wide:]
+    dw = ops.conv2d_bwd_filter(x, dy, (KH, KW), s, pads)
+    torch.cuda.synchronize()
+    assert_close(f64(dw), oracle.conv2d_bwd_filter(f64(x), f64(dy), (KH, KW), (s, s), pads), torch.float32, dtype,
+                 label="filter gradient")
+    for beta in (0.0, 1.0):
+        db_ = torch.full((N, H, W, C + wide), 0.5, dtype=dtype, device=DEV)
+        dx = db_[..., wide:]
+        old = f64(dx)
+        ops.conv2d_bwd_input(dy, w, dx, s, pads, beta=beta)
+        dpb = torch.full((N, H, W, C + wide), 0.5, dtype=dtype, device=DEV)
+        dp, db = ops.conv2d_bwd_input_relu_bwd(dy, w, x, dpb[..., wide:], s, pads, beta=beta)
+        torch.cuda.synchronize()
+        g = oracle.conv2d_bwd_input(f64(dy), f64(w), tuple(x.shape), (s, s), pads, dx=old, beta=beta)
+        assert_close(f64(dx), g, dtype, label="input gradient beta=%g" % beta)
+        ref_dp, ref_db = oracle.bias_relu_bwd(f64(x), g)
+        assert_close(f64(dp), ref_dp, dtype, label="fused dpre beta=%g" % beta)
+        assert_close(f64(db), ref_db, torch.float32, dtype, label="fused db beta=%g" % beta)
+        assert bool(torch.all(db_[..., :wide] == 0.5)) and bool(torch.all(dpb[..., :wide] == 0.5))
+
+
+# N, H, W, C, K, KH, KW, stride, pads, extra channels of the buffers
+F32_CASES = [
+    ("f32_c4_k4", 1, 5, 7, 4, 4, 3, 3, 1, (1, 1, 1, 1), 0),
+    ("f32_c12_k20", 2, 9, 8, 12, 20, 3, 3, 1, (1, 1, 1, 1), 4),             # multiples of 4, not of 8
+    ("f32_c96_k100_s2", 2, 15, 14, 96, 100, 3, 3, 2, (0, 0, 0, 0), 0),      # 32-row tiles, stride phases
+    ("f32_c64_k68", 3, 8, 11, 64, 68, 1, 3, 1, (0, 0, 1, 1), 8),            # 64-row tiles and a remainder
+    ("f32_c160_k32_tail", 1, 13, 5, 160, 32, 5, 1, 1, (2, 2, 0, 0), 0),     # 65 pixels: one past a tile
+    ("f32_1x1_k1_tile", 1, 8, 8, 32, 64, 1, 1, 1, (0, 0, 0, 0), 0),         # one reduction tile
+    ("f32_2tiles", 1, 8, 8, 40, 32, 1, 1, 1, (0, 0, 0, 0), 0),              # two, the second partial
+    ("f32_c6_k10", 2, 6, 5, 6, 10, 3, 3, 1, (1, 1, 1, 1), 0),               # register-staged kernel
+]
+
+
+@pytest.mark.parametrize("case", F32_CASES, ids=[c[0] for c in F32_CASES])
+def test_conv_f32_paths(case):
+    name, N, H, W, C, K, KH, KW, s, pads, wide = case
+    _check_all(name, torch.float32, N, H, W, C, K, KH, KW, s, pads, wide)
+
+
+def test_conv_f32_relu_bwd_least_workspace():
+    """A workspace that holds the unfused pair's partials but not the fused kernel's is accepted
+    and gives the same gradient (the bias gradient up to the order of its fp32 sums)."""
+    lib = load()
+    rng = np.random.default_rng(5)
+    N, H, W, C, K = 8, 28, 28, 96, 64
+    y = torch.from_numpy(np.maximum(rng.standard_normal((N, H, W, C)), 0.0)).float().to(DEV)
+    w, dy = _mk((3, 3, C, K), torch.float32, rng, 0.05), _mk((N, H, W, K), torch.float32, rng)
+    want = ops.conv2d_workspace_bytes(3, y, K, 3, 3, 1, (1, 1, 1, 1))
+    least = ops.bias_relu_bwd_workspace_bytes(y)
+    assert least <= want
+    out = []
+    for nbytes in (want, least):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+        dp, db = torch.empty_like(y), torch.empty(C, dtype=torch.float32, device=DEV)
+        rc = lib.tfk_conv2d_bwd_input_relu_bwd(
+            ops._ptr(dy), ops.nhwc(dy), ops._ptr(w), ops.window(3, 3, 1, (1, 1, 1, 1)), 0, ops._ptr(y), ops._ptr(dp),
+            ops.nhwc(y), ctypes.c_float(0.0), ops._ptr(db), ops._ptr(ws), nbytes, ops._stream(None))
+        assert rc == 0
+        torch.cuda.synchronize()
+        out.append((dp, db))
+    assert torch.equal(out[0][0], out[1][0])
+    # N H W = 6272 terms of one fp32 sum each side: 2 * 6272 * 2^-24 of the sum of magnitudes at most
+    bound = 2 * N * H * W * 2.0 ** -24 * f64(out[0][0].abs()).sum(axis=(0, 1, 2))
+    assert np.all(np.abs(f64(out[0][1]) - f64(out[1][1])) <= bound)
