@@ -9,16 +9,25 @@ namespace tfk {
 // 74.8 -> 71.3 us back to back, but the sustained two-stream step slower, 0.694 -> 0.705 ms, where
 // the filter gradient of the other stream shares the GPU with it; GoogLeNet and Inception-v3
 // steps are the same either way.)
-static Igemm2Tile bwd_data_tiles(int ni, int mj, int zdim) {
-    return igemm2_tiles_narrow(ni, mj, zdim);
+static Igemm2Tile bwd_data_tiles(int dt, int ni, int mj, int zdim) {
+    return dt == 0 ? igemm2_tiles_f32(ni, mj, zdim) : igemm2_tiles_narrow(ni, mj, zdim);
+}
+
+// Tiles of the kernel fused with the ReLU backward, whose partial sums of the bias gradient (a row
+// per block and wave column) go to the workspace: the rule's, where the workspace holds their
+// rows (`all`), else without the tiles of fewer than 96 pixels (twice as many rows as 64 x 128).
+static Igemm2Tile relu_tiles(int dt, int ni, int mj, int zdim, bool all) {
+    Igemm2Tile t = bwd_data_tiles(dt, ni, mj, zdim);
+    if (dt == 1 && !all && t.bj < 96) t = Igemm2Tile{64, 128, 4, 2};
+    return t;
 }
 
 // Rows of bias-gradient partials of the fused ReLU-backward epilogue: one per block and wave
 // column of the pipelined kernel's grid.
-static int relu_partial_rows(int dt, const ConvShape &s) {
+static int relu_partial_rows(int dt, const ConvShape &s, bool all) {
     const int mj = s.N * ((s.H + s.sh - 1) / s.sh) * ((s.W + s.sw - 1) / s.sw);
     const int z = s.sh * s.sw;
-    const Igemm2Tile t = dt == 0 ? igemm2_tiles_f32(s.C) : bwd_data_tiles(s.C, mj, z);
+    const Igemm2Tile t = relu_tiles(dt, s.C, mj, z, all);
     return z * ((mj + t.bj - 1) / t.bj) * (t.nw / 2);
 }
 
@@ -48,7 +57,7 @@ size_t conv_bwd_data_ws_bytes(int dt, const ConvShape &s) { return split_ws_byte
 template <typename T>
 static hipError_t conv_bwd_data_t(const void *dy, int64_t dys, const void *w, void *dx, int64_t dxs, float beta,
                                   const ConvShape &s, hipStream_t st, float *ws, const void *relu_y = nullptr,
-                                  int *db_parts = nullptr, float **db_at = nullptr) {
+                                  bool all = true, int *db_parts = nullptr, float **db_at = nullptr) {
     constexpr int EPC = Elem<T>::kPerChunk;
     IgArgs a;
     fill_geom(a, s);
@@ -74,7 +83,7 @@ static hipError_t conv_bwd_data_t(const void *dy, int64_t dys, const void *w, vo
                 a.k_split = ks;
                 a.split_stride = (int64_t)mj * a.NI;
                 a.out = ws;
-                if (!igemm2_launch<DIR_BWD_DATA>(a, mj, sp, bwd_data_tiles(a.NI, mj, sp), st))
+                if (!igemm2_launch<DIR_BWD_DATA>(a, mj, sp, bwd_data_tiles(1, a.NI, mj, sp), st))
                     return hipErrorInvalidValue;
                 const hipError_t e = hipGetLastError();
                 if (e != hipSuccess) return e;
@@ -98,11 +107,12 @@ static hipError_t conv_bwd_data_t(const void *dy, int64_t dys, const void *w, vo
             if (relu_y != nullptr) {
                 a.relu_y = relu_y;
                 a.db_part = ws;
-                a.db_rows = relu_partial_rows(1, s);
+                a.db_rows = relu_partial_rows(1, s, all);
                 *db_parts = a.db_rows;
                 *db_at = ws;
             }
-            if (!igemm2_launch<DIR_BWD_DATA>(a, mj, z, bwd_data_tiles(a.NI, mj, z), st)) return hipErrorInvalidValue;
+            const Igemm2Tile t = relu_y != nullptr ? relu_tiles(1, a.NI, mj, z, all) : bwd_data_tiles(1, a.NI, mj, z);
+            if (!igemm2_launch<DIR_BWD_DATA>(a, mj, z, t, st)) return hipErrorInvalidValue;
             return hipGetLastError();
         }
     }
@@ -113,11 +123,11 @@ static hipError_t conv_bwd_data_t(const void *dy, int64_t dys, const void *w, vo
             if (relu_y != nullptr) {
                 a.relu_y = relu_y;
                 a.db_part = ws;
-                a.db_rows = relu_partial_rows(0, s);
+                a.db_rows = relu_partial_rows(0, s, true);
                 *db_parts = a.db_rows;
                 *db_at = ws;
             }
-            if (!igemm2_launch_f32<DIR_BWD_DATA>(a, mj, s.sh * s.sw, igemm2_tiles_f32(a.NI), st))
+            if (!igemm2_launch_f32<DIR_BWD_DATA>(a, mj, s.sh * s.sw, bwd_data_tiles(0, a.NI, mj, s.sh * s.sw), st))
                 return hipErrorInvalidValue;
             return hipGetLastError();
         }
@@ -132,14 +142,13 @@ size_t conv_bwd_data_relu_ws_bytes(int dt, const ConvShape &s, int64_t dxs) {
     relu_bwd_plan(dt, (int64_t)s.N * s.H * s.W, s.C, dxs, &G, &ppb);
     const size_t fallback = (size_t)G * s.C * sizeof(float);
     if (dt != 1) return fallback;
-    return std::max({fallback, (size_t)relu_partial_rows(1, s) * s.C * sizeof(float), split_ws_bytes(dt, s, true)});
+    return std::max({fallback, (size_t)relu_partial_rows(1, s, false) * s.C * sizeof(float), split_ws_bytes(dt, s, true)});
 }
 
-// The fp32 kernel's partials may take more than the workspace that the unfused pair needs: the
-// query asks for them, and a call given less runs the pair.
+// The rule's tiles (and fp32's fused kernel) may leave more partials than the workspace must hold:
+// the query asks for room for them, and a call given less takes other tiles (fp32: the unfused pair).
 size_t conv_bwd_data_relu_ws_want(int dt, const ConvShape &s, int64_t dxs) {
-    const size_t need = conv_bwd_data_relu_ws_bytes(dt, s, dxs);
-    return dt == 0 ? std::max(need, (size_t)relu_partial_rows(0, s) * s.C * sizeof(float)) : need;
+    return std::max(conv_bwd_data_relu_ws_bytes(dt, s, dxs), (size_t)relu_partial_rows(dt, s, true) * s.C * sizeof(float));
 }
 
 hipError_t launch_conv_bwd_data_relu(int dt, const void *dy, int64_t dys, const void *w, void *dpre, int64_t dxs,
@@ -147,10 +156,11 @@ hipError_t launch_conv_bwd_data_relu(int dt, const void *dy, int64_t dys, const 
                                      const ConvShape &s, hipStream_t st, BiasPartials *defer) {
     int parts = 0;
     float *db_at = nullptr;
-    if (dt == 1 ? ((uintptr_t)y & 7) == 0 : ws_bytes >= conv_bwd_data_relu_ws_want(dt, s, dxs)) {
+    const bool all = ws_bytes >= conv_bwd_data_relu_ws_want(dt, s, dxs);
+    if (dt == 1 ? ((uintptr_t)y & 7) == 0 : all) {
         const hipError_t e = dt == 1
-            ? conv_bwd_data_t<bf16_t>(dy, dys, w, dpre, dxs, beta, s, st, ws, y, &parts, &db_at)
-            : conv_bwd_data_t<float>(dy, dys, w, dpre, dxs, beta, s, st, ws, y, &parts, &db_at);
+            ? conv_bwd_data_t<bf16_t>(dy, dys, w, dpre, dxs, beta, s, st, ws, y, all, &parts, &db_at)
+            : conv_bwd_data_t<float>(dy, dys, w, dpre, dxs, beta, s, st, ws, y, all, &parts, &db_at);
         if (e != hipSuccess) return e;
         if (parts > 0) {
             if (defer != nullptr) {

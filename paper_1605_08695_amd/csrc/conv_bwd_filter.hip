@@ -31,10 +31,16 @@ BwfPlan bwf_plan(int dt, const ConvShape &s, bool v2) {
     // output channels a multiple of 64 but not of 128 (AlexNet conv2's 192): 64-channel tiles leave
     // none empty (128-channel ones would compute a quarter of the rows for nothing), and three of
     // their 48 KiB blocks fit a CU, so the splits fill one round of three (conv2: 95 -> 90 us)
-    const bool by64 = v2 && s.K > 64 && s.K % 128 != 0 && s.K % 64 == 0;
+    // Small products (up to 10 GFLOP): 64 x 64 tiles with three LDS stages; their splits reduce to
+    // fewer, shorter partials and their blocks overlap better (14 x 14 x 512 -> 128, 1 x 1, batch 128:
+    // 17.0 -> 14.3 us; 28 x 28 x 192 -> 176, batch 128: 28.2 -> 21.5; 8 x 28 x 28 x 192 -> 96: 13.2 -> 9.4; at
+    // 11.3 GFLOP, 14 x 14 x 112 -> 224, 3 x 3, batch 128: 28.7 against 31.0)
+    const bool small = v2 && s.K > 32 && 2.0 * m * s.K * ((double)s.N * s.OH * s.OW) <= 1e10;
+    const bool by64 = v2 && !small && s.K > 64 && s.K % 128 != 0 && s.K % 64 == 0;
     if (v2) {
-        p.t = s.K > 64 && !by64 ? Igemm2Tile{128, 128, 4, 2}
-                                : (s.K > 32 ? Igemm2Tile{64, 128, 4, 2} : Igemm2Tile{32, 128, 4, 2});
+        p.t = small ? Igemm2Tile{64, 64, 4, 3}
+                    : (s.K > 64 && !by64 ? Igemm2Tile{128, 128, 4, 2}
+                                         : (s.K > 32 ? Igemm2Tile{64, 128, 4, 2} : Igemm2Tile{32, 128, 4, 2}));
         p.bi = p.t.bi;
         p.bj = p.t.bj;
     } else {
@@ -59,7 +65,7 @@ BwfPlan bwf_plan(int dt, const ConvShape &s, bool v2) {
 // many as the register-staged kernel's plan, whose partials size the workspace.
 BwfPlan bwf_plan_f32(const ConvShape &s) {
     BwfPlan p;
-    p.t = igemm2_tiles_f32(s.K);
+    p.t = Igemm2Tile{igemm2_tiles_f32(s.K, 1 << 24, 1).bi, 64, 4, 3};
     p.bi = p.t.bi;
     p.bj = p.t.bj;
     const int tiles = ((s.K + p.bi - 1) / p.bi) * ((s.KH * s.KW * s.C + p.bj - 1) / p.bj);

@@ -64,7 +64,7 @@ static hipError_t conv_fwd_t(const void *x, int64_t xs, const void *w, void *y, 
     if constexpr (sizeof(T) == 4) {
         if (vi && vj && ys % EPC == 0 && aligned16p(y) &&
             igemm2_fits(a, (int64_t)s.KH * s.KW * s.C * s.K * 4, span_bytes((int64_t)s.N * s.H * s.W, xs, s.C, 4))) {
-            if (!igemm2_launch_f32<DIR_FWD>(a, mj, 1, igemm2_tiles_f32(a.NI), st)) return hipErrorInvalidValue;
+            if (!igemm2_launch_f32<DIR_FWD>(a, mj, 1, igemm2_tiles_f32(a.NI, mj, 1), st)) return hipErrorInvalidValue;
             return hipGetLastError();
         }
     }
@@ -134,7 +134,8 @@ bool conv_fwd_pool_fused(const void *x, int64_t xs, const void *w, void *y, int6
     // fused with 64-channel tiles, 322 and 292 us with 128-channel tiles)
     {
         const int mj_plain = s.N * s.OH * s.OW;
-        const Igemm2Tile pt = igemm2_tiles_narrow(s.K, mj_plain, 1);
+        Igemm2Tile pt = igemm2_tiles_narrow(s.K, mj_plain, 1);
+        if (pt.bj < 96) pt.bj = 128;         // (64 x 64 tiles: counted as the 64 x 128 ones they halve)
         const int64_t blocks = (int64_t)((s.K + pt.bi - 1) / pt.bi) * ((mj_plain + pt.bj - 1) / pt.bj);
         if (blocks > 2 * kFusedPoolCUs) return false;
     }

@@ -10,7 +10,7 @@
 //    given the chunk that belongs at its LDS slot, as a 32-bit byte offset into
 //    its operand; out-of-range chunks get an offset past the operand's end,
 //    which the buffer range check turns into zeros.
-//  * A ring of NS LDS stages (two to four): the copies of K-tiles t+1 .. t+NS-1 are
+//  * A ring of NS LDS stages (two or three): the copies of K-tiles t+1 .. t+NS-1 are
 //    in flight while the MFMAs consume tile t.  Each stage is a separate LDS
 //    object and the loop is unrolled by NS; a step waits only for the copies of
 //    its own tile (s_waitcnt vmcnt(n) with n = the copies of the later tiles).
@@ -32,6 +32,7 @@
 // than 2^31 bytes and the filter has at most 31 rows and 31 columns.
 #pragma once
 #include <type_traits>
+#include <utility>
 
 #include "igemm.h"
 
@@ -125,7 +126,8 @@ __device__ __forceinline__ U4 lds_tr_pair(const unsigned char *p0, const unsigne
 // k-rows start alternately at bank 0 and bank 32: bit 1 of k moves k-rows 2 and 3 of a
 // group by one chunk pair and bit 3 of k the second group by two, which keeps every chunk
 // inside its aligned group of eight.  32-row k-rows are 64 bytes: the 4 k-rows of a group already
-// cover every bank once, and bit 3 of k moves the second group to the other chunk pair.
+// cover every bank once, and bit 3 of k moves the second group to the other chunk pair; so do
+// 160-row k-rows, whose 320 bytes start the 4 k-rows of a group a quarter of the banks apart.
 //
 // fp32: a fragment read touches 16 consecutive rows (64 bytes, four chunks) of the k-rows
 // 4g + e, g = 0..3 the lane group; (k >> 2) & 3 moves each group to its own 64 bytes of the
@@ -136,8 +138,8 @@ __device__ __forceinline__ int kmajor_swz(int k) {
         static_assert(R == 32 || R % 64 == 0, "k-major tile rows");
         return R == 32 ? ((k >> 2) & 1) << 2 : ((k >> 2) & 3) << 2;
     } else {
-        static_assert(R == 32 || R == 64 || R == 128 || R == 192 || R == 256, "k-major tile rows");
-        if constexpr (R == 32) return ((k >> 3) & 1) << 1;
+        static_assert(R == 32 || R == 64 || R == 128 || R == 160 || R == 192 || R == 256, "k-major tile rows");
+        if constexpr (R == 32 || R == 160) return ((k >> 3) & 1) << 1;
         else if constexpr (R == 64) return ((k & 3) ^ ((k >> 3) & 1)) << 1;
         else if constexpr (R != 192) return ((k & 3) << 1) ^ (((k >> 3) & 1) << 3);
         else return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
@@ -159,6 +161,10 @@ __device__ __forceinline__ U4 lds_k4(const unsigned char *tile, int k4, int row)
     U4 r;
     r.x = p[0]; r.y = p[R]; r.z = p[2 * R]; r.w = p[3 * R];
     return r;
+}
+
+__device__ __forceinline__ float u4_f32(const U4 &v, int e) {
+    return __uint_as_float(e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w);
 }
 
 // Workgroups are dealt to the 8 XCDs of the chip round-robin by linear id, and each XCD
@@ -188,14 +194,13 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     constexpr int WI = BI / 2, WJ = BJ / WGJ;
     constexpr int MI = WI / 16, MJ = WJ / 16;
     static_assert(NW == 4 || NW == 8, "waves");
-    static_assert(NS >= 2 && NS <= 4, "stages");
+    static_assert(NS == 2 || NS == 3, "stages");
     static_assert(NLI >= 1 && NLJ >= 1 && MI >= 1 && MJ >= 1, "tile");
     static_assert(NS * SB <= 160 * 1024, "LDS");
 
     __shared__ __attribute__((aligned(1024))) unsigned char lds0[SB];
     __shared__ __attribute__((aligned(1024))) unsigned char lds1[SB];
-    __shared__ __attribute__((aligned(1024))) unsigned char lds2[NS >= 3 ? SB : 16];
-    __shared__ __attribute__((aligned(1024))) unsigned char lds3[NS >= 4 ? SB : 16];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds2[NS == 3 ? SB : 16];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -529,10 +534,23 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
                     fj[y] = *reinterpret_cast<const U4 *>(stJ + lds_off(row, 4 * s + lg));
                 }
             }
+            if constexpr (ES == 4) {
+                // (one k at a time over all of the wave's tiles: an accumulator's next product is
+                // MI * MJ matrix instructions away instead of the next one)
 #pragma unroll
-            for (int x = 0; x < MI; ++x)
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int y = 0; y < MJ; ++y) Mfma<T>::run(acc[x][y], fi[x], fj[y]);
+                    for (int x = 0; x < MI; ++x)
+#pragma unroll
+                        for (int y = 0; y < MJ; ++y)
+                            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(u4_f32(fi[x], e), u4_f32(fj[y], e),
+                                                                             acc[x][y], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int x = 0; x < MI; ++x)
+#pragma unroll
+                    for (int y = 0; y < MJ; ++y) Mfma<T>::run(acc[x][y], fi[x], fj[y]);
+            }
         }
         // Schedule: the fragment reads of the first sub-step, then the MFMAs of the first
         // sub-step alternating with the reads of the second, then its MFMAs -- so the LDS
@@ -554,13 +572,12 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     // (every wave has passed the barrier, so none still reads it) with tile kt + NS - 1.
     auto stage = [&](auto S_) __attribute__((always_inline)) -> unsigned char * {
         constexpr int S = decltype(S_)::value % NS;
-        return S == 0 ? lds0 : (S == 1 ? lds1 : (S == 2 ? lds2 : lds3));
+        return S == 0 ? lds0 : (S == 1 ? lds1 : lds2);
     };
     auto step = [&](auto S_, int kt) __attribute__((always_inline)) {
         constexpr int S = decltype(S_)::value;
-        // (the copies of the min(NS - 2, nk - 1 - kt) tiles after kt that are already issued)
-        if (NS >= 4 && kt + 2 < nk) wait_barrier<(NS - 2) * NL>();
-        else if (NS >= 3 && kt + 1 < nk) wait_barrier<NL>();
+        // (with three stages tile kt + 1's copies are already issued and may stay in flight)
+        if (NS == 3 && kt + 1 < nk) wait_barrier<NL>();
         else wait_barrier<0>();
         if (kt + NS - 1 < nk) issue(kt + NS - 1, stage(std::integral_constant<int, S + NS - 1>{}));
         if constexpr (DIR != DIR_BWD_FILTER) {
@@ -599,18 +616,15 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
 
     if (nk > 0) {
         issue(0, lds0);
-        if (NS >= 3 && nk > 1) issue(1, lds1);
-        if (NS >= 4 && nk > 2) issue(2, lds2);
+        if (NS == 3 && nk > 1) issue(1, lds1);
         int kt = 0;
         for (; kt + NS <= nk; kt += NS) {
             step(std::integral_constant<int, 0>{}, kt);
             step(std::integral_constant<int, 1>{}, kt + 1);
-            if constexpr (NS >= 3) step(std::integral_constant<int, 2>{}, kt + 2);
-            if constexpr (NS >= 4) step(std::integral_constant<int, 3>{}, kt + 3);
+            if constexpr (NS == 3) step(std::integral_constant<int, 2>{}, kt + 2);
         }
         if (kt < nk) step(std::integral_constant<int, 0>{}, kt);
-        if (NS >= 3 && kt + 1 < nk) step(std::integral_constant<int, 1>{}, kt + 1);
-        if (NS >= 4 && kt + 2 < nk) step(std::integral_constant<int, 2>{}, kt + 2);
+        if (NS == 3 && kt + 1 < nk) step(std::integral_constant<int, 1>{}, kt + 1);
     }
 
     // ------------------------------------------------------------ epilogue
@@ -630,9 +644,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     for (int x = 0; x < MI; ++x)
 #pragma unroll
         for (int q = 0; q < 4; ++q) cs[x][q] = 0.f;
-    // Row offsets of this lane's output rows.  (Loading an input gradient's old values and ReLU
-    // outputs for all of a wave's tiles before the first store ran its kernels faster alone but
-    // the two-stream step slower, about 1 %; they stay loaded tile by tile.)
+    // Row offsets of this lane's output rows.
     int64_t roff[MJ];
 #pragma unroll
     for (int y = 0; y < MJ; ++y) {
@@ -659,10 +671,34 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
         }
         roff[y] = rowoff;
     }
+    // The old values (beta) and ReLU outputs of one row group of an input gradient, four
+    // elements per lane and channel group: a row group's loads are issued together, one group
+    // ahead of its stores.  (A load per 16 x 16 tile right before its store, one memory latency
+    // each, cost 28 x 28 x 512, 3 x 3, batch 64, a tenth of its time.)
+    typedef typename std::conditional<ES == 4, f32x4_t, uint2>::type E4;
+    E4 yv[2][MI], ov[2][MI];
+    auto epi_fetch = [&](auto Y_) __attribute__((always_inline)) {
+        constexpr int y = decltype(Y_)::value;
+        if constexpr (DIR == DIR_BWD_DATA && y < MJ) {
+            if (a.k_split == 0 && j0 + wj * WJ + y * 16 + ld < MJ_ext) {
 #pragma unroll
-    for (int y = 0; y < MJ; ++y) {
+                for (int x = 0; x < MI; ++x) {
+                    const int i = i0 + wi * WI + x * 16 + 4 * lg;
+                    if (i >= a.NI) continue;
+                    if (relu)
+                        yv[y & 1][x] = *reinterpret_cast<const E4 *>(reinterpret_cast<const T *>(a.relu_y) + roff[y] + i);
+                    if (a.beta != 0.f)
+                        ov[y & 1][x] = *reinterpret_cast<const E4 *>(reinterpret_cast<const T *>(a.out) + roff[y] + i);
+                }
+            }
+        }
+    };
+    epi_fetch(std::integral_constant<int, 0>{});
+    auto epi_row = [&](auto Y_) __attribute__((always_inline)) {
+        constexpr int y = decltype(Y_)::value;
+        epi_fetch(std::integral_constant<int, y + 1>{});
         const int j = j0 + wj * WJ + y * 16 + ld;
-        if (j >= MJ_ext) continue;
+        if (j >= MJ_ext) return;
         const int64_t rowoff = roff[y];
 #pragma unroll
         for (int x = 0; x < MI; ++x) {
@@ -684,16 +720,13 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
                 f32x4_t r = v;
                 if constexpr (DIR == DIR_BWD_DATA) {
                     if (a.beta != 0.f) {
-                        const f32x4_t old = *reinterpret_cast<const f32x4_t *>(o);
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) r[q] += a.beta * old[q];
+                        for (int q = 0; q < 4; ++q) r[q] += a.beta * ov[y & 1][x][q];
                     }
                     if (relu) {
-                        const f32x4_t yy = *reinterpret_cast<const f32x4_t *>(
-                            reinterpret_cast<const float *>(a.relu_y) + rowoff + i);
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
-                            r[q] = yy[q] > 0.f ? r[q] : 0.f;
+                            r[q] = yv[y & 1][x][q] > 0.f ? r[q] : 0.f;
                             cs[x][q] += r[q];
                         }
                     }
@@ -713,15 +746,14 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
                 float r4[4] = {v[0], v[1], v[2], v[3]};
                 if constexpr (DIR == DIR_BWD_DATA) {
                     if (a.beta != 0.f) {
-                        const uint2 old = *reinterpret_cast<const uint2 *>(o);
+                        const uint2 old = ov[y & 1][x];
                         r4[0] += a.beta * bf16_to_f32(old.x & 0xffffu);
                         r4[1] += a.beta * bf16_to_f32(old.x >> 16);
                         r4[2] += a.beta * bf16_to_f32(old.y & 0xffffu);
                         r4[3] += a.beta * bf16_to_f32(old.y >> 16);
                     }
                     if (relu) {
-                        const uint2 yy = *reinterpret_cast<const uint2 *>(
-                            reinterpret_cast<const bf16_t *>(a.relu_y) + rowoff + i);
+                        const uint2 yy = yv[y & 1][x];
                         const float yq[4] = {bf16_to_f32(yy.x & 0xffffu), bf16_to_f32(yy.x >> 16),
                                              bf16_to_f32(yy.y & 0xffffu), bf16_to_f32(yy.y >> 16)};
 #pragma unroll
@@ -757,7 +789,10 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
                 }
             }
         }
-    }
+    };
+    [&]<int... Y>(std::integer_sequence<int, Y...>) __attribute__((always_inline)) {
+        (epi_row(std::integral_constant<int, Y>{}), ...);
+    }(std::make_integer_sequence<int, MJ>{});
     if constexpr (kPoolFits) {
         if (pooled) {
             // pool rows q0 .. q0 + nq - 1 of this band; each thread takes one channel pair of the

@@ -1,6 +1,8 @@
 // Host-side launch of the implicit-GEMM kernel: tile choice, vector-path
 // selection and grid shape.
 #pragma once
+#include <utility>
+
 #include "igemm.h"
 #include "igemm2.h"
 #include "kernels.h"
@@ -43,12 +45,28 @@ struct Igemm2Tile {
     int bi, bj, nw, ns;
 };
 
-// Chosen from sweeps over the AlexNet/VGG layer shapes on MI355X.  Two 4-wave blocks
-// share each CU (two LDS stages each; the 64-channel kernel fits three).  128-channel tiles
-// pay when the channel count is a multiple of 128 and they give at least one block per CU
-// (AlexNet conv4/conv5 forward: 57 -> 54 and 38 -> 36 us against 64-channel tiles), and
-// 192-channel tiles likewise for multiples of 192 (AlexNet conv2 forward: 76 -> 64 us),
-// otherwise 64-channel tiles.
+// Relative time of `blocks` blocks on 256 CUs that hold two each: a full round of two per CU
+// counts 1; a last round takes 0.6 when it gives no CU a second block (a block that has a CU to
+// itself runs about 1.6 times as fast as one that shares it), more as second blocks come in.
+static inline double round_cost(int64_t blocks) {
+    const double f = (double)(blocks % 512) / 512.0;
+    const double tail = f == 0.0 ? 0.0 : (f <= 0.5 ? 0.6 : std::min(1.0, 0.6 + 1.6 * (f - 0.5)));
+    return (double)(blocks / 512) + tail;
+}
+
+// Chosen from sweeps over convolution layer shapes on MI355X.  Two 4-wave blocks share each CU.
+// The copies into LDS (64 bytes per clock and CU) and the fragment reads out of it bound these
+// kernels, so wide tiles pay as soon as there are blocks to fill the CUs:
+//  * multiples of 128 channels with at least one 128 x 128 block per CU: 128-channel tiles.  Over
+//    more than one round the row side is 128, 160 or 192 by round_cost times the tile's relative
+//    time (1, 1.15, 1.4 for 1, 1.25, 1.5 times the work).  3 x 3, 56 x 56 x 256, batch 64, forward: 128 rows
+//    242 us (6.1 rounds), 160 210 (4.9), 192 223 (4.1); 28 x 28 x 512, batch 64: 238, 210 and 230; input
+//    gradient 256, 224, 248; 35 x 35 x 256 -> 384, batch 37: 94, 78, 85 and (input gradient) 95, 106, 76.
+//  * multiples of 192 likewise (AlexNet conv2 forward: 76 -> 64 us);
+//  * otherwise 64-channel tiles: 64 x 128, or 64 x 64 with three LDS stages up to 320 blocks, where
+//    64 x 128 leaves most CUs with one block whose barriers and copies nothing overlaps (17 x 17,
+//    160 -> 192, 1 x 7, batch 32: forward 12.9 -> 12.0 us, 28 x 28 x 192 -> 96, 1 x 1, batch 8: 6.7 -> 5.7; at
+//    614 blocks, 35 x 35 x 64 -> 96, 3 x 3, batch 32: 12.6 against 14.8, the other way).
 static inline Igemm2Tile igemm2_tiles(int ni, int mj, int zdim) {
     const int64_t blocks_j = (int64_t)((mj + 127) / 128) * zdim;
     if (ni % 128 == 0 && (ni / 128) * blocks_j >= 256) {
@@ -57,7 +75,17 @@ static inline Igemm2Tile igemm2_tiles(int ni, int mj, int zdim) {
         const int64_t b128 = (ni / 128) * blocks_j, b96 = (ni / 128) * (int64_t)((mj + 95) / 96) * zdim;
         // (not for a single row of tiles: 96-row tiles would leave most of the second row empty)
         if (b128 < 448 && b96 <= 512 && mj > 128) return {128, 96, 4, 2};
-        return {128, 128, 4, 2};
+        Igemm2Tile best{128, 128, 4, 2};
+        if (b128 <= 512) return best;
+        double least = round_cost(b128);
+        for (const auto &[bj, rel] : {std::pair{160, 1.15}, std::pair{192, 1.4}}) {
+            const double c = rel * round_cost((ni / 128) * (int64_t)((mj + bj - 1) / bj) * zdim);
+            if (c < least) {
+                least = c;
+                best.bj = bj;
+            }
+        }
+        return best;
     }
     if (ni % 192 == 0 && (ni / 192) * blocks_j >= 256) {
         // 96-row J tiles when they fill the last round of two blocks per CU better: the same
@@ -70,6 +98,7 @@ static inline Igemm2Tile igemm2_tiles(int ni, int mj, int zdim) {
         if (zdim == 1 && fill(b96) > fill(b128) + 0.05) return {192, 96, 4, 2};
         return {192, 128, 4, 2};
     }
+    if ((int64_t)((ni + 63) / 64) * blocks_j <= 320) return {64, 64, 4, 3};
     return {64, 128, 4, 2};
 }
 
@@ -82,14 +111,17 @@ static inline Igemm2Tile igemm2_tiles_narrow(int ni, int mj, int zdim) {
 
 // fp32 tiles.  The fp32 matrix rate is a sixteenth of bf16's, so small tiles already keep the
 // matrix cores busy (a 32 x 32 wave tile takes 1024 matrix cycles per K tile against 64 cycles of
-// its own LDS reads) and give small layers the most blocks: 64 x 64 tiles, or 32 x 64 where 64-row
-// tiles would compute a sixth or more of their rows for nothing (at most 32 channels, 96, 160).
-// 16 x 28 x 28 x 96 -> 128, 3 x 3: forward 36 us with 64 x 64, 64 x 128 or 128 x 64 tiles, 64 with
-// 128 x 128 (register-staged kernel: 80); its input gradient 44 us with 32 x 64, 51 with 64 x 64
-// (register-staged kernel with its separate ReLU backward: 106).
-static inline Igemm2Tile igemm2_tiles_f32(int ni) {
+// its own LDS reads): 64 x 64 tiles; 32 x 64 where 64-row tiles would compute a sixth or more of
+// their rows for nothing (at most 32 channels, 96, 160) or give fewer blocks than CUs; 32 x 32 where
+// 32 x 64 gives fewer.  16 x 28 x 28 x 96 -> 128, 3 x 3: forward 36 us with 64 x 64, 64 x 128 or 128 x 64
+// tiles, 64 with 128 x 128 (register-staged kernel: 80); its input gradient 44 us with 32 x 64, 51 with
+// 64 x 64 (register-staged kernel with its separate ReLU backward: 106).  8 x 14 x 14 x 256, 3 x 3: 55 us
+// with 64 x 64 (100 blocks), 37 with 32 x 64, 35 with 32 x 32; 1 x 28 x 28 x 96 -> 64: 23, 16, 12.
+static inline Igemm2Tile igemm2_tiles_f32(int ni, int mj, int zdim) {
     const int r32 = (ni + 31) / 32 * 32, r64 = (ni + 63) / 64 * 64;
-    return (r64 - r32) * 6 >= r64 ? Igemm2Tile{32, 64, 4, 3} : Igemm2Tile{64, 64, 4, 3};
+    const int64_t bj = (int64_t)((mj + 63) / 64) * zdim;
+    if ((r64 - r32) * 6 < r64 && r64 / 64 * bj >= 256) return {64, 64, 4, 3};
+    return {32, r32 / 32 * bj < 256 ? 32 : 64, 4, 3};
 }
 
 template <typename T, int DIR, int BI, int BJ, int NW, int NS>
@@ -101,59 +133,40 @@ template <int DIR>
 static bool igemm2_launch_f32(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipStream_t st) {
     a.tiles_i = (a.NI + t.bi - 1) / t.bi;
     const dim3 grid((unsigned)(a.tiles_i * ((mj + t.bj - 1) / t.bj)), 1, (unsigned)zdim);
-    if (t.bj != 64 || t.nw != 4 || t.ns != 3) return false;
-    if (t.bi == 32) { igemm2_go<float, DIR, 32, 64, 4, 3>(a, grid, st); return true; }
-    if (t.bi == 64) { igemm2_go<float, DIR, 64, 64, 4, 3>(a, grid, st); return true; }
+    if (t.nw != 4 || t.ns != 3) return false;
+    if (t.bi == 64 && t.bj == 64) { igemm2_go<float, DIR, 64, 64, 4, 3>(a, grid, st); return true; }
+    if (t.bi == 32 && t.bj == 64) { igemm2_go<float, DIR, 32, 64, 4, 3>(a, grid, st); return true; }
+    if (t.bi == 32 && t.bj == 32) { igemm2_go<float, DIR, 32, 32, 4, 3>(a, grid, st); return true; }
     return false;
 }
 
-// Launches one of the compiled configurations; false if t is not one of them.
+// Launches one of the compiled configurations; false if t is not one of them.  (96- and 160-row
+// J tiles, 192-row ones and 192-channel tiles are forward and bwd-input only: the filter gradient
+// keeps both operands k-major, with more address registers per copy, and spills there.)
 template <int DIR>
 static bool igemm2_launch(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipStream_t st) {
     a.tiles_i = (a.NI + t.bi - 1) / t.bi;
     const int tiles_j = (mj + t.bj - 1) / t.bj;
     const dim3 grid((unsigned)(a.tiles_i * tiles_j), 1, (unsigned)zdim);
-    const int key = ((t.bi / 64) << 12) | ((t.bj / 64) << 8) | (t.nw << 4) | t.ns;
-    if (t.bi == 32 && t.bj == 128 && t.nw == 4 && t.ns == 2) {
-        igemm2_go<bf16_t, DIR, 32, 128, 4, 2>(a, grid, st);
-        return true;
+    if (t.nw != 4) return false;
+    const int key = t.bi * 10000 + t.bj * 10 + t.ns;
+    switch (key) {
+    case 321282: igemm2_go<bf16_t, DIR, 32, 128, 4, 2>(a, grid, st); return true;
+    case 640643: igemm2_go<bf16_t, DIR, 64, 64, 4, 3>(a, grid, st); return true;
+    case 641282: igemm2_go<bf16_t, DIR, 64, 128, 4, 2>(a, grid, st); return true;
+    case 1281282: igemm2_go<bf16_t, DIR, 128, 128, 4, 2>(a, grid, st); return true;
     }
-    if (t.bi == 128 && t.bj == 96 && t.nw == 4 && t.ns == 2) {
-        // (96-row k-major tiles are not laid out: forward and bwd-input only)
-        if constexpr (DIR == DIR_BWD_FILTER) return false;
-        else { igemm2_go<bf16_t, DIR, 128, 96, 4, 2>(a, grid, st); return true; }
-    }
-    if (t.bj == 192 && t.nw == 4 && t.ns == 2) {
-        // (192-row J tiles: the forward row bands of a fused max-pool and 64-channel forward
-        // tiles; 192-row k-major tiles are not laid out)
-        if constexpr (DIR == DIR_BWD_FILTER) return false;
-        else {
-            if (t.bi == 64) { igemm2_go<bf16_t, DIR, 64, 192, 4, 2>(a, grid, st); return true; }
-            if (t.bi == 128) { igemm2_go<bf16_t, DIR, 128, 192, 4, 2>(a, grid, st); return true; }
-            if (t.bi == 192) { igemm2_go<bf16_t, DIR, 192, 192, 4, 2>(a, grid, st); return true; }
-            return false;
+    if constexpr (DIR != DIR_BWD_FILTER) {
+        switch (key) {
+        case 641922: igemm2_go<bf16_t, DIR, 64, 192, 4, 2>(a, grid, st); return true;
+        case 1280962: igemm2_go<bf16_t, DIR, 128, 96, 4, 2>(a, grid, st); return true;
+        case 1281602: igemm2_go<bf16_t, DIR, 128, 160, 4, 2>(a, grid, st); return true;
+        case 1281922: igemm2_go<bf16_t, DIR, 128, 192, 4, 2>(a, grid, st); return true;
+        case 1920962: igemm2_go<bf16_t, DIR, 192, 96, 4, 2>(a, grid, st); return true;
+        case 1921282: igemm2_go<bf16_t, DIR, 192, 128, 4, 2>(a, grid, st); return true;
         }
     }
-    if (t.bi == 192 && t.bj == 96 && t.nw == 4 && t.ns == 2) {
-        if constexpr (DIR == DIR_BWD_FILTER) return false;
-        else { igemm2_go<bf16_t, DIR, 192, 96, 4, 2>(a, grid, st); return true; }
-    }
-    if (t.bi == 192 && t.bj == 128 && t.nw == 4 && t.ns == 2) {
-        // (the filter-gradient direction does not fit these tiles in its registers)
-        if constexpr (DIR == DIR_BWD_FILTER) return false;
-        else { igemm2_go<bf16_t, DIR, 192, 128, 4, 2>(a, grid, st); return true; }
-    }
-    switch (key) {
-    case (1 << 12) | (2 << 8) | (8 << 4) | 3: igemm2_go<bf16_t, DIR, 64, 128, 8, 3>(a, grid, st); return true;
-    case (1 << 12) | (4 << 8) | (8 << 4) | 3: igemm2_go<bf16_t, DIR, 64, 256, 8, 3>(a, grid, st); return true;
-    case (2 << 12) | (2 << 8) | (8 << 4) | 3: igemm2_go<bf16_t, DIR, 128, 128, 8, 3>(a, grid, st); return true;
-    case (2 << 12) | (4 << 8) | (8 << 4) | 3: igemm2_go<bf16_t, DIR, 128, 256, 8, 3>(a, grid, st); return true;
-    case (2 << 12) | (2 << 8) | (4 << 4) | 2: igemm2_go<bf16_t, DIR, 128, 128, 4, 2>(a, grid, st); return true;
-    case (1 << 12) | (2 << 8) | (4 << 4) | 3: igemm2_go<bf16_t, DIR, 64, 128, 4, 3>(a, grid, st); return true;
-    case (1 << 12) | (2 << 8) | (4 << 4) | 2: igemm2_go<bf16_t, DIR, 64, 128, 4, 2>(a, grid, st); return true;
-    case (1 << 12) | (4 << 8) | (4 << 4) | 2: igemm2_go<bf16_t, DIR, 64, 256, 4, 2>(a, grid, st); return true;
-    default: return false;
-    }
+    return false;
 }
 
 // Split-K for GEMMs with few output tiles (fully connected layers at small batch): the

@@ -76,28 +76,55 @@ def test_conv_f32_paths(case):
     _check_all(name, torch.float32, N, H, W, C, K, KH, KW, s, pads, wide)
 
 
-def test_conv_f32_relu_bwd_least_workspace():
-    """A workspace that holds the unfused pair's partials but not the fused kernel's is accepted
-    and gives the same gradient (the bias gradient up to the order of its fp32 sums)."""
+BF16_CASES = [
+    # 64 x 64 tiles with three LDS stages: one, two, three and four reduction tiles, remainders
+    ("b64_k1", 1, 9, 9, 64, 72, 1, 1, 1, (0, 0, 0, 0), 0),
+    ("b64_k2", 1, 8, 8, 104, 64, 1, 1, 1, (0, 0, 0, 0), 8),
+    ("b64_k3", 2, 7, 5, 64, 40, 1, 3, 1, (0, 0, 1, 1), 0),
+    ("b64_k4_s2", 2, 11, 9, 24, 96, 3, 3, 2, (1, 1, 1, 1), 0),
+    # more than one round of 128 x 128 blocks: 160- and 192-row tiles, forward and input gradient
+    ("rows160", 7, 100, 100, 16, 128, 1, 1, 1, (0, 0, 0, 0), 0),
+    ("rows160_dx", 7, 100, 100, 128, 16, 1, 1, 1, (0, 0, 0, 0), 0),
+    ("rows192", 9, 100, 100, 24, 128, 1, 1, 1, (0, 0, 0, 0), 0),
+    ("rows192_dx", 9, 100, 100, 128, 24, 1, 1, 1, (0, 0, 0, 0), 0),
+]
+
+
+@pytest.mark.parametrize("case", BF16_CASES, ids=[c[0] for c in BF16_CASES])
+def test_conv_bf16_paths(case):
+    name, N, H, W, C, K, KH, KW, s, pads, wide = case
+    _check_all(name, torch.bfloat16, N, H, W, C, K, KH, KW, s, pads, wide)
+
+
+def _relu_bwd_with_workspace(dy, w, y, nbytes):
     lib = load()
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+    dp, db = torch.empty_like(y), torch.empty(y.shape[3], dtype=torch.float32, device=DEV)
+    rc = lib.tfk_conv2d_bwd_input_relu_bwd(
+        ops._ptr(dy), ops.nhwc(dy), ops._ptr(w), ops.window(3, 3, 1, (1, 1, 1, 1)), ops._dt(y), ops._ptr(y),
+        ops._ptr(dp), ops.nhwc(y), ctypes.c_float(0.0), ops._ptr(db), ops._ptr(ws), nbytes, ops._stream(None))
+    assert rc == 0
+    torch.cuda.synchronize()
+    return dp, db
+
+
+@pytest.mark.parametrize("dtype,least", [
+    (torch.float32, lambda y: ops.bias_relu_bwd_workspace_bytes(y)),
+    # 64 x 128 tiles: two rows of partials per block (more than the unfused pair's here)
+    (torch.bfloat16, lambda y: max(ops.bias_relu_bwd_workspace_bytes(y), 2 * (-(-y[..., 0].numel() // 128)) * y.shape[3] * 4)),
+], ids=["f32", "bf16"])
+def test_conv_relu_bwd_least_workspace(dtype, least):
+    """A workspace that holds the partials of the unfused pair (fp32) or of 64 x 128 tiles (bf16),
+    but not those of the tiles the rule takes, is accepted and gives the same gradient (the bias
+    gradient up to the order of its fp32 sums)."""
     rng = np.random.default_rng(5)
     N, H, W, C, K = 8, 28, 28, 96, 64
-    y = torch.from_numpy(np.maximum(rng.standard_normal((N, H, W, C)), 0.0)).float().to(DEV)
-    w, dy = _mk((3, 3, C, K), torch.float32, rng, 0.05), _mk((N, H, W, K), torch.float32, rng)
+    y = torch.from_numpy(np.maximum(rng.standard_normal((N, H, W, C)), 0.0)).to(dtype).to(DEV)
+    w, dy = _mk((3, 3, C, K), dtype, rng, 0.05), _mk((N, H, W, K), dtype, rng)
     want = ops.conv2d_workspace_bytes(3, y, K, 3, 3, 1, (1, 1, 1, 1))
-    least = ops.bias_relu_bwd_workspace_bytes(y)
-    assert least <= want
-    out = []
-    for nbytes in (want, least):
-        ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
-        dp, db = torch.empty_like(y), torch.empty(C, dtype=torch.float32, device=DEV)
-        rc = lib.tfk_conv2d_bwd_input_relu_bwd(
-            ops._ptr(dy), ops.nhwc(dy), ops._ptr(w), ops.window(3, 3, 1, (1, 1, 1, 1)), 0, ops._ptr(y), ops._ptr(dp),
-            ops.nhwc(y), ctypes.c_float(0.0), ops._ptr(db), ops._ptr(ws), nbytes, ops._stream(None))
-        assert rc == 0
-        torch.cuda.synchronize()
-        out.append((dp, db))
-    assert torch.equal(out[0][0], out[1][0])
+    assert least(y) <= want
+    a, b = _relu_bwd_with_workspace(dy, w, y, want), _relu_bwd_with_workspace(dy, w, y, least(y))
+    assert torch.equal(a[0], b[0])
     # N H W = 6272 terms of one fp32 sum each side: 2 * 6272 * 2^-24 of the sum of magnitudes at most
-    bound = 2 * N * H * W * 2.0 ** -24 * f64(out[0][0].abs()).sum(axis=(0, 1, 2))
-    assert np.all(np.abs(f64(out[0][1]) - f64(out[1][1])) <= bound)
+    bound = 2 * N * H * W * 2.0 ** -24 * f64(a[0].abs()).sum(axis=(0, 1, 2))
+    assert np.all(np.abs(f64(a[1]) - f64(b[1])) <= bound)
