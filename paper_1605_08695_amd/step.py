@@ -433,6 +433,7 @@ class Replica:
         self.lane_streams = {k: self.side if k == 1 else torch.cuda.Stream(device=dev) for k in used}
         self.lane_ws = {k: torch.zeros_like(self.ws) for k in used}
         self.marks = {}                          # node index (or "start") -> ops.Mark, made on first use
+        self.use_side, self.use_lanes = self._stream_rule()
         # ---- bias gradients of an untraced step: each ReLU/bias backward leaves its per-block
         # partials in a workspace of its own, and one launch sums them all before the update
         self.defer_bias = True
@@ -444,6 +445,31 @@ class Replica:
     # 4.56; 3 / 2 2.93 and 5.33, where a three-stream forward lines Inception's branches up badly)
     kFwdLanes = 4
     kBwdLanes = 2
+
+    # A fork to another stream and its join cost 6-13 us of host time (an event recorded and waited
+    # for) and drain the stream they are recorded on, whatever the kernels do.  Recorded steps, by
+    # the mean work of the filter gradients that would run on the side stream (serial / side stream /
+    # side and lanes, us): an inception module 14 x 14 at batch 4 (0.1 GFLOP) 144 / 178 / 229, batch 16
+    # (0.5) 170 / 192 / 244, batch 48 (1.6) 241 / 215 / 242, batch 128 (4.3) 349 / 330 / 332; GoogLeNet
+    # batch 2 (0.1) 943 / 1078 / 1392, batch 16 (0.6) 1271 / 1161 / 1561, batch 128 (4.9) 3387 / 3082 /
+    # 2894; Inception-v3 batch 4 (0.5) 2354 / 2983 / 3045; the AlexNet stack batch 4 (1.3) 201 / 193.
+    kSideFlops = 0.8e9
+    kLaneFlops = 3e9
+
+    def _stream_rule(self):
+        """Whether a concurrent step is worth a side stream for the filter gradients, and lanes for
+        independent branches: (side, lanes).  fp32 counts 8 times (its convolutions take about that
+        much longer); a single filter gradient has only its own input gradient to run beside."""
+        work = []
+        for op in self.ops:
+            if isinstance(op, Conv) and (op.src != "x" or self.net.input_grad):
+                n, oh, ow, _ = self.net.tensors[self.merged[op.name]["members"][0].dst if op.name in self.merged
+                                                else op.dst]
+                work.append(2.0 * n * oh * ow * op.kh * op.kw * self.net.tensors[op.src][3] * op.cout)
+        if len(work) < 2:
+            return False, False
+        mean = sum(work) / len(work) * (8.0 if self.dtype == torch.float32 else 1.0)
+        return mean >= self.kSideFlops, mean >= self.kLaneFlops
 
     def _forward_plan(self, nlanes: int):
         """The forward ops (a pool made inside its convolution left out) placed on ``nlanes``
@@ -847,14 +873,19 @@ class Replica:
                            a["epsilon"], self.t, shadow=self.shadow, stream=stream)
             if trace: trace("apply_adam:end", None, stream=stream, var=self.params)
 
+    def _passes(self, trace, stream, concurrent):
+        lanes = concurrent and self.use_lanes
+        self.forward(trace, stream, lanes=lanes)
+        self.backward(trace, stream, side=self.side if concurrent and self.use_side else None, lanes=lanes)
+
     def step(self, trace=None, stream=None, concurrent=True):
-        """One training step on ``stream``; unless ``concurrent`` is false, the forward pass's
-        independent branches run side by side on the lane streams and the filter gradients
-        overlap the rest of the backward pass on a second stream.  ``trace(event, op,
+        """One training step on ``stream``; unless ``concurrent`` is false, and where the step's work
+        is worth it (``use_side``, ``use_lanes``), the forward pass's independent branches run side
+        by side on the lane streams and the filter gradients overlap the rest of the backward
+        pass on a second stream.  ``trace(event, op,
         stream=s, **tensors)`` is called before and after every op (``event`` ending in
         ``:end``), with the stream the op runs on (None: the current stream)."""
-        self.forward(trace, stream, lanes=concurrent)
-        self.backward(trace, stream, side=self.side if concurrent else None)
+        self._passes(trace, stream, concurrent)
         self.update(trace, stream)
 
     def record_step(self, stream=None, concurrent=True) -> "ops.Program":
@@ -865,8 +896,7 @@ class Replica:
         prog = ops.Program()
         prog.with_update = self.optimizer != "adam"
         with prog.recording():
-            self.forward(None, stream, lanes=concurrent)
-            self.backward(None, stream, side=self.side if concurrent else None)
+            self._passes(None, stream, concurrent)
             if prog.with_update:
                 self.update(None, stream)
         if not prog.with_update:

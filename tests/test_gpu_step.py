@@ -413,3 +413,43 @@ def test_deferred_bias_gradients_match_immediate(make):
         assert bitwise_equal(a.grads, b.grads), r
         assert bitwise_equal(a.params, b.params), r
     say("deferred bias gradients", net.name, "workspaces:", len(a.bias_ws))
+
+
+@pytest.mark.parametrize("make", [lambda: W.googlenet(batch=4), lambda: W.inception_v3(batch=2)],
+                         ids=["googlenet_b4", "inception_v3_b2"])
+def test_streams_at_small_sizes_match_one_stream(make):
+    """The side stream and the lanes at sizes where the step's own rule runs on one stream: the
+    same bits as one stream, eagerly and from a recorded program."""
+    net = make()
+    net.lr = 1e-6
+    inp = W.make_inputs(net, seed=3)
+    one, two = Replica(net, inp), Replica(net, inp)
+    assert not two.use_side and not two.use_lanes
+    two.use_side = two.use_lanes = True
+    prog = None
+    for r in range(3):
+        one.step()
+        if r == 0:
+            two.step()
+        elif r == 1:
+            prog = two.record_step()
+        else:
+            two.run_program(prog)
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(two.params).all()), r
+        assert bitwise_equal(one.grads, two.grads), r
+        assert bitwise_equal(one.params, two.params), r
+        for t in one.act:
+            assert bitwise_equal(one.act[t], two.act[t]), (r, t)
+    prog.close()
+
+
+def test_stream_rule_by_work():
+    """One stream for small steps and for a network with one filter gradient to overlap, a side
+    stream from middling work on, lanes for the benchmarked sizes."""
+    def rule(net):
+        rep = Replica(net, W.make_inputs(net, seed=0))
+        return rep.use_side, rep.use_lanes
+    assert rule(W.single_layer()) == (False, False)
+    assert rule(W.googlenet(batch=1)) == (False, False)
+    assert rule(W.alexnet(batch=4)) == (True, False)
