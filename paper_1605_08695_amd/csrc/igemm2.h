@@ -32,7 +32,6 @@
 // than 2^31 bytes and the filter has at most 31 rows and 31 columns.
 #pragma once
 #include <type_traits>
-#include <utility>
 
 #include "igemm.h"
 
@@ -644,7 +643,11 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     for (int x = 0; x < MI; ++x)
 #pragma unroll
         for (int q = 0; q < 4; ++q) cs[x][q] = 0.f;
-    // Row offsets of this lane's output rows.
+    // Row offsets of this lane's output rows.  (Loading an input gradient's old values and ReLU
+    // outputs for all of a wave's tiles before the first store ran its kernels faster alone but
+    // the two-stream step slower, about 1 %, and loading them one row group ahead of its stores
+    // gained nothing alone (28 x 28 x 512, 3 x 3, batch 64: 280 us either way) and cost a module's
+    // step 2 %; they stay loaded tile by tile.)
     int64_t roff[MJ];
 #pragma unroll
     for (int y = 0; y < MJ; ++y) {
@@ -671,34 +674,10 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
         }
         roff[y] = rowoff;
     }
-    // The old values (beta) and ReLU outputs of one row group of an input gradient, four
-    // elements per lane and channel group: a row group's loads are issued together, one group
-    // ahead of its stores.  (A load per 16 x 16 tile right before its store, one memory latency
-    // each, cost 28 x 28 x 512, 3 x 3, batch 64, a tenth of its time.)
-    typedef typename std::conditional<ES == 4, f32x4_t, uint2>::type E4;
-    E4 yv[2][MI], ov[2][MI];
-    auto epi_fetch = [&](auto Y_) __attribute__((always_inline)) {
-        constexpr int y = decltype(Y_)::value;
-        if constexpr (DIR == DIR_BWD_DATA && y < MJ) {
-            if (a.k_split == 0 && j0 + wj * WJ + y * 16 + ld < MJ_ext) {
 #pragma unroll
-                for (int x = 0; x < MI; ++x) {
-                    const int i = i0 + wi * WI + x * 16 + 4 * lg;
-                    if (i >= a.NI) continue;
-                    if (relu)
-                        yv[y & 1][x] = *reinterpret_cast<const E4 *>(reinterpret_cast<const T *>(a.relu_y) + roff[y] + i);
-                    if (a.beta != 0.f)
-                        ov[y & 1][x] = *reinterpret_cast<const E4 *>(reinterpret_cast<const T *>(a.out) + roff[y] + i);
-                }
-            }
-        }
-    };
-    epi_fetch(std::integral_constant<int, 0>{});
-    auto epi_row = [&](auto Y_) __attribute__((always_inline)) {
-        constexpr int y = decltype(Y_)::value;
-        epi_fetch(std::integral_constant<int, y + 1>{});
+    for (int y = 0; y < MJ; ++y) {
         const int j = j0 + wj * WJ + y * 16 + ld;
-        if (j >= MJ_ext) return;
+        if (j >= MJ_ext) continue;
         const int64_t rowoff = roff[y];
 #pragma unroll
         for (int x = 0; x < MI; ++x) {
@@ -720,13 +699,16 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
                 f32x4_t r = v;
                 if constexpr (DIR == DIR_BWD_DATA) {
                     if (a.beta != 0.f) {
+                        const f32x4_t old = *reinterpret_cast<const f32x4_t *>(o);
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) r[q] += a.beta * ov[y & 1][x][q];
+                        for (int q = 0; q < 4; ++q) r[q] += a.beta * old[q];
                     }
                     if (relu) {
+                        const f32x4_t yy = *reinterpret_cast<const f32x4_t *>(
+                            reinterpret_cast<const float *>(a.relu_y) + rowoff + i);
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
-                            r[q] = yv[y & 1][x][q] > 0.f ? r[q] : 0.f;
+                            r[q] = yy[q] > 0.f ? r[q] : 0.f;
                             cs[x][q] += r[q];
                         }
                     }
@@ -746,14 +728,15 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
                 float r4[4] = {v[0], v[1], v[2], v[3]};
                 if constexpr (DIR == DIR_BWD_DATA) {
                     if (a.beta != 0.f) {
-                        const uint2 old = ov[y & 1][x];
+                        const uint2 old = *reinterpret_cast<const uint2 *>(o);
                         r4[0] += a.beta * bf16_to_f32(old.x & 0xffffu);
                         r4[1] += a.beta * bf16_to_f32(old.x >> 16);
                         r4[2] += a.beta * bf16_to_f32(old.y & 0xffffu);
                         r4[3] += a.beta * bf16_to_f32(old.y >> 16);
                     }
                     if (relu) {
-                        const uint2 yy = yv[y & 1][x];
+                        const uint2 yy = *reinterpret_cast<const uint2 *>(
+                            reinterpret_cast<const bf16_t *>(a.relu_y) + rowoff + i);
                         const float yq[4] = {bf16_to_f32(yy.x & 0xffffu), bf16_to_f32(yy.x >> 16),
                                              bf16_to_f32(yy.y & 0xffffu), bf16_to_f32(yy.y >> 16)};
 #pragma unroll
@@ -789,10 +772,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
                 }
             }
         }
-    };
-    [&]<int... Y>(std::integer_sequence<int, Y...>) __attribute__((always_inline)) {
-        (epi_row(std::integral_constant<int, Y>{}), ...);
-    }(std::make_integer_sequence<int, MJ>{});
+    }
     if constexpr (kPoolFits) {
         if (pooled) {
             // pool rows q0 .. q0 + nq - 1 of this band; each thread takes one channel pair of the
