@@ -498,6 +498,134 @@ __global__ __launch_bounds__(256) void maxpool_fwd_win_kernel(const T *__restric
     }
 }
 
+// 3x3 windows at stride 1 (the inception modules' pooling branches), bf16 with uint8 taps: a thread
+// takes kPoolStrip output rows of one column and channel chunk.  It loads the 3 chunks of each of
+// its kPoolStrip + 2 input rows once (4.5 per output instead of 9), reduces each row's three taps
+// to one key per element (bits << 8 | 3 - kw, ordered as in maxpool_fwd_win_kernel) and takes each
+// output as the largest of three rows' keys plus 6, 3, 0 for kh = 0, 1, 2: the low byte is 9 - tap,
+// so that a tie goes to the first tap.  9 + 3 integer instructions per element and output replace
+// 18.  A sign bit in any tap leaves the thread's outputs, and a NaN maximum its output, to
+// pool_scan_row, the float scan.  128 x 28 x 28 x 256: see launch rule.
+constexpr int kPoolStrip = 4;
+constexpr int64_t kStripThreads = 1 << 16;
+
+// One output row's chunk by the float scan (first maximum in kh, kw order; padded taps skipped).
+__device__ __forceinline__ void pool_scan_row(const bf16_t *__restrict__ x, const PoolGeom &g, int n, int oh, int ow, int c,
+                                           bf16_t *__restrict__ y, uint8_t *__restrict__ taps) {
+    float best[8];
+    int32_t bi[8];
+    bool have = false;
+    for (int kh = 0; kh < 3; ++kh) {
+        const int ih = oh + kh - g.pt;
+        if ((unsigned)ih >= (unsigned)g.H) continue;
+        for (int kw = 0; kw < 3; ++kw) {
+            const int iw = ow + kw - g.pl;
+            if ((unsigned)iw >= (unsigned)g.W) continue;
+            float f[8];
+            chunk_to_f32<bf16_t>(*reinterpret_cast<const U4 *>(x + (((int64_t)n * g.H + ih) * g.W + iw) * g.xs + c), f);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (!have || f[e] > best[e]) {
+                    best[e] = f[e];
+                    bi[e] = kh * 3 + kw;
+                }
+            }
+            have = true;
+        }
+    }
+    const int64_t opix = ((int64_t)n * g.OH + oh) * g.OW + ow;
+    *reinterpret_cast<U4 *>(y + opix * g.ys + c) = f32_to_chunk<bf16_t>(best);
+    arg_store<uint8_t, 8>(taps + opix * g.C + c, bi);
+}
+
+// dec: work item -> (channel chunk, column, strip of rows, image).
+__global__ __launch_bounds__(256) void maxpool_fwd_strip_kernel(const bf16_t *__restrict__ x, PoolGeom g,
+                                                                bf16_t *__restrict__ y, uint8_t *__restrict__ taps,
+                                                                int64_t total, Decode dec) {
+    constexpr int R = kPoolStrip;
+    typedef PoolIx<true> M;
+    typedef M::I I;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= total) return;
+    int cv, ow, strip, n;
+    int64_t q;
+    decode(dec, t, cv, q, ow, strip, n);
+    const int oh0 = strip * R, c = cv * 8;
+    U4 v[R + 2][3];
+    uint32_t code[3];
+#pragma unroll
+    for (int kw = 0; kw < 3; ++kw) code[kw] = (unsigned)(ow + kw - g.pl) < (unsigned)g.W ? 3u - kw : 0u;
+    uint32_t sg = 0;
+#pragma unroll
+    for (int r = 0; r < R + 2; ++r) {
+        const int ih = oh0 + r - g.pt;
+        const I row = M::mul(M::mul((I)n, (I)g.H) + (I)ih, (I)g.W);
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw) {
+            U4 u{0u, 0u, 0u, 0u};
+            if ((unsigned)ih < (unsigned)g.H && code[kw] != 0)
+                u = *reinterpret_cast<const U4 *>(x + (M::mul(row + (I)(ow + kw - g.pl), (I)g.xs) + (I)c));
+            v[r][kw] = u;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R + 2; ++r)
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw) sg |= v[r][kw].x | v[r][kw].y | v[r][kw].z | v[r][kw].w;
+    uint32_t scan = (sg & 0x80008000u) != 0 ? (1u << R) - 1u : 0u;     // rows left to pool_scan_row
+    uint32_t key[3][8];                  // keys of the last three input rows (row r in key[r % 3])
+#pragma unroll
+    for (int r = 0; r < R + 2; ++r) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            uint32_t lo[3], hi[3];
+#pragma unroll
+            for (int kw = 0; kw < 3; ++kw) {
+                const uint32_t d = w == 0 ? v[r][kw].x : w == 1 ? v[r][kw].y : w == 2 ? v[r][kw].z : v[r][kw].w;
+                lo[kw] = __builtin_amdgcn_perm(d, code[kw], 0x0C050400u);
+                hi[kw] = __builtin_amdgcn_perm(d, code[kw], 0x0C070600u);
+            }
+            key[r % 3][2 * w] = max(max(lo[0], lo[1]), lo[2]);
+            key[r % 3][2 * w + 1] = max(max(hi[0], hi[1]), hi[2]);
+        }
+        if (r < 2) continue;
+        const int oh = oh0 + r - 2;
+        if (oh >= g.OH) break;
+        if (scan >> (r - 2) & 1u) continue;
+        // (a row outside the image holds keys below every valid tap's: it adds nothing)
+        const bool in0 = (unsigned)(oh - g.pt) < (unsigned)g.H, in1 = (unsigned)(oh + 1 - g.pt) < (unsigned)g.H,
+                   in2 = (unsigned)(oh + 2 - g.pt) < (unsigned)g.H;
+        uint32_t kb[8], top = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t a = in0 ? key[(r - 2) % 3][e] + 6u : 0u, b = in1 ? key[(r - 1) % 3][e] + 3u : 0u,
+                           d = in2 ? key[r % 3][e] : 0u;
+            kb[e] = max(max(a, b), d);
+            top = max(top, kb[e]);
+        }
+        if ((top >> 8) > 0x7F80u) {      // a NaN maximum (+inf is 0x7F80)
+            scan |= 1u << (r - 2);
+            continue;
+        }
+        const I opix = M::mul(M::mul((I)n, (I)g.OH) + (I)oh, (I)g.OW) + (I)ow;
+        U4 o;
+        o.x = __builtin_amdgcn_perm(kb[1], kb[0], 0x06050201u);
+        o.y = __builtin_amdgcn_perm(kb[3], kb[2], 0x06050201u);
+        o.z = __builtin_amdgcn_perm(kb[5], kb[4], 0x06050201u);
+        o.w = __builtin_amdgcn_perm(kb[7], kb[6], 0x06050201u);
+        *reinterpret_cast<U4 *>(y + (M::mul(opix, (I)g.ys) + (I)c)) = o;
+        uint2 tp;
+        tp.x = 0x09090909u - (__builtin_amdgcn_perm(kb[1], kb[0], 0x0C0C0400u) |
+                              __builtin_amdgcn_perm(kb[3], kb[2], 0x04000C0Cu));
+        tp.y = 0x09090909u - (__builtin_amdgcn_perm(kb[5], kb[4], 0x0C0C0400u) |
+                              __builtin_amdgcn_perm(kb[7], kb[6], 0x04000C0Cu));
+        *reinterpret_cast<uint2 *>(taps + (M::mul(opix, (I)g.C) + (I)c)) = tp;
+    }
+    if (scan != 0)
+        for (int r = 0; r < R && oh0 + r < g.OH; ++r)
+            if (scan >> r & 1u) pool_scan_row(x, g, n, oh0 + r, ow, c, y, taps);
+}
+
 // ------------------------------------------------------------------ max-pool backward
 // Gather form: each input element visits the windows that contain it in
 // ascending output order and adds the gradients routed to it.
@@ -632,6 +760,80 @@ __global__ __launch_bounds__(256) void maxpool_bwd_kernel(const T *__restrict__ 
             if (beta != 0.f) s[0] += beta * Elem<T>::load(out);
             Elem<T>::store(out, s[0]);
         }
+    }
+}
+
+// 3x3 windows at stride 1, bf16 gradients with uint8 taps: a thread takes kPoolStrip input rows of
+// one column and channel chunk and visits each of the kPoolStrip + 2 rows of 3 windows around them
+// once, adding a window's element to the accumulator of the row (of three) that its tap names: 4.5
+// tap and gradient loads and conversions per output instead of 9.  Every element still adds its
+// windows in ascending output order (the bits of the gather form).  The next row of windows is
+// loaded before the current one is added.
+__global__ __launch_bounds__(256) void maxpool_bwd_strip_kernel(const bf16_t *__restrict__ dy,
+                                                                const uint8_t *__restrict__ taps, PoolGeom g, float beta,
+                                                                bf16_t *dx, int64_t total, Decode dec) {
+    constexpr int R = kPoolStrip;
+    typedef PoolIx<true> M;
+    typedef M::I I;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= total) return;
+    int cv, w, strip, n;
+    int64_t q;
+    decode(dec, t, cv, q, w, strip, n);
+    const int h0 = strip * R, c = cv * 8;
+    float acc[R][8];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[r][e] = 0.f;
+    U4 dv[2][3];
+    uint2 tv[2][3];
+    auto fetch = [&](int i) __attribute__((always_inline)) {
+        const int oh = h0 + g.pt - 2 + i;
+        const I row = M::mul(M::mul((I)n, (I)g.OH) + (I)oh, (I)g.OW);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int ow = w + g.pl - 2 + j;
+            dv[i & 1][j] = U4{0u, 0u, 0u, 0u};
+            tv[i & 1][j] = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);        // (no tap)
+            if ((unsigned)oh < (unsigned)g.OH && (unsigned)ow < (unsigned)g.OW) {
+                const I opix = row + (I)ow;
+                dv[i & 1][j] = *reinterpret_cast<const U4 *>(dy + (M::mul(opix, (I)g.ys) + (I)c));
+                tv[i & 1][j] = *reinterpret_cast<const uint2 *>(taps + (M::mul(opix, (I)g.C) + (I)c));
+            }
+        }
+    };
+    fetch(0);
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+        if (i + 1 < R + 2) fetch(i + 1);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            float f[8];
+            chunk_to_f32<bf16_t>(dv[i & 1][j], f);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t tap = ((e < 4 ? tv[i & 1][j].x : tv[i & 1][j].y) >> (8 * (e & 3))) & 0xffu;
+#pragma unroll
+                for (int kh = 0; kh < 3; ++kh) {
+                    const int rr = i - 2 + kh;
+                    if (rr >= 0 && rr < R) acc[rr][e] += tap == (uint32_t)(kh * 3 + 2 - j) ? f[e] : 0.f;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int h = h0 + r;
+        if (h >= g.H) break;
+        bf16_t *out = dx + (M::mul(M::mul(M::mul((I)n, (I)g.H) + (I)h, (I)g.W) + (I)w, (I)g.xs) + (I)c);
+        if (beta != 0.f) {
+            float o[8];
+            chunk_to_f32<bf16_t>(*reinterpret_cast<const U4 *>(out), o);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[r][e] += beta * o[e];
+        }
+        *reinterpret_cast<U4 *>(out) = f32_to_chunk<bf16_t>(acc[r]);
     }
 }
 
@@ -1422,6 +1624,14 @@ hipError_t launch_maxpool_relu_bwd(int dt, const void *dy, const void *am, bool 
                                                 defer);
 }
 
+// Whether a 3x3 stride-1 pool takes the strip kernels over `rows` rows: 16-byte chunks, 32-bit
+// indices, and enough strips to fill the GPU.
+static bool pool_strips(const PoolGeom &g, bool vec, int rows, int cols, int64_t *total) {
+    if (!vec || g.KH != 3 || g.KW != 3 || g.sh != 1 || g.sw != 1 || !pool_o32(g, 0)) return false;
+    *total = (int64_t)g.N * ((rows + kPoolStrip - 1) / kPoolStrip) * cols * (g.C / 8);
+    return *total >= kStripThreads;
+}
+
 template <typename T, typename A>
 static hipError_t maxpool_fwd_t(const void *x, const PoolGeom &g, void *y, A *am, hipStream_t st) {
     constexpr int EPC = Elem<T>::kPerChunk;
@@ -1432,6 +1642,15 @@ static hipError_t maxpool_fwd_t(const void *x, const PoolGeom &g, void *y, A *am
     const int grid = grid_for(work, 256, 16384);
     const Decode dec = make_decode(cv, g.OW, g.OH, work);
     const bool o32 = pool_o32(g, 0);
+    if constexpr (std::is_same<T, bf16_t>::value && std::is_same<A, uint8_t>::value) {
+        int64_t total;
+        if (pool_strips(g, vec, g.OH, g.OW, &total)) {
+            const Decode ds = make_decode(cv, g.OW, (g.OH + kPoolStrip - 1) / kPoolStrip, total);
+            hipLaunchKernelGGL(maxpool_fwd_strip_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
+                               (const T *)x, g, (T *)y, am, total, ds);
+            return hipGetLastError();
+        }
+    }
     if (vec && g.KH == 3 && g.KW == 3 && o32)
         hipLaunchKernelGGL((maxpool_fwd_win_kernel<T, 3, 3, A, true>), dim3(grid), dim3(256), 0, st, (const T *)x, g,
                            (T *)y, am, dec);
@@ -1470,6 +1689,15 @@ static hipError_t maxpool_bwd_t(const void *dy, const A *am, const PoolGeom &g, 
     const int64_t work = (int64_t)g.N * g.H * g.W * cv;
     const int grid = grid_for(work, 256, 16384);
     const Decode dec = make_decode(cv, g.W, g.H, work);
+    if constexpr (std::is_same<T, bf16_t>::value && std::is_same<A, uint8_t>::value) {
+        int64_t total;
+        if (pool_strips(g, vec, g.H, g.W, &total)) {
+            const Decode ds = make_decode(cv, g.W, (g.H + kPoolStrip - 1) / kPoolStrip, total);
+            hipLaunchKernelGGL(maxpool_bwd_strip_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
+                               (const T *)dy, am, g, beta, (T *)dx, total, ds);
+            return hipGetLastError();
+        }
+    }
     if (vec && pool_o32(g, 0))
         hipLaunchKernelGGL((maxpool_bwd_kernel<T, true, A, true>), dim3(grid), dim3(256), 0, st, (const T *)dy, am, g,
                            beta, (T *)dx, dec);
