@@ -83,7 +83,7 @@ static hipError_t conv_bwd_data_t(const void *dy, int64_t dys, const void *w, vo
                 a.k_split = ks;
                 a.split_stride = (int64_t)mj * a.NI;
                 a.out = ws;
-                if (!igemm2_launch<DIR_BWD_DATA>(a, mj, sp, bwd_data_tiles(1, a.NI, mj, sp), st))
+                if (!igemm2_launch<DIR_BWD_DATA>(a, mj, sp, igemm2_tiles_split(a.NI, mj, sp), st))
                     return hipErrorInvalidValue;
                 const hipError_t e = hipGetLastError();
                 if (e != hipSuccess) return e;

@@ -31,11 +31,13 @@ BwfPlan bwf_plan(int dt, const ConvShape &s, bool v2) {
     // output channels a multiple of 64 but not of 128 (AlexNet conv2's 192): 64-channel tiles leave
     // none empty (128-channel ones would compute a quarter of the rows for nothing), and three of
     // their 48 KiB blocks fit a CU, so the splits fill one round of three (conv2: 95 -> 90 us)
-    // Small products (up to 10 GFLOP): 64 x 64 tiles with three LDS stages; their splits reduce to
+    // Small products (up to 10 GFLOP in at most 256 128 x 128 tiles): 64 x 64 tiles with three LDS stages; their splits reduce to
     // fewer, shorter partials and their blocks overlap better (14 x 14 x 512 -> 128, 1 x 1, batch 128:
     // 17.0 -> 14.3 us; 28 x 28 x 192 -> 176, batch 128: 28.2 -> 21.5; 8 x 28 x 28 x 192 -> 96: 13.2 -> 9.4; at
     // 11.3 GFLOP, 14 x 14 x 112 -> 224, 3 x 3, batch 128: 28.7 against 31.0)
-    const bool small = v2 && s.K > 32 && 2.0 * m * s.K * ((double)s.N * s.OH * s.OW) <= 1e10;
+    // (with more tiles there is no split and the output's bytes bound it: 9216 -> 4096 over 128
+    // rows 54 us with 64 x 64 tiles, 43 with 128 x 128)
+    const bool small = v2 && s.K > 32 && (int64_t)((s.K + 127) / 128) * ((m + 127) / 128) <= 256 && 2.0 * m * s.K * ((double)s.N * s.OH * s.OW) <= 1e10;
     const bool by64 = v2 && !small && s.K > 64 && s.K % 128 != 0 && s.K % 64 == 0;
     if (v2) {
         p.t = small ? Igemm2Tile{64, 64, 4, 3}
