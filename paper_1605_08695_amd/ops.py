@@ -9,6 +9,7 @@ current stream) and raises TfkError on a non-OK status.  There is no CPU path.
 from __future__ import annotations
 
 import ctypes
+import functools
 from typing import NamedTuple, Optional, Sequence, Tuple
 
 import torch
@@ -30,35 +31,80 @@ def _dt(t: torch.Tensor) -> int:
     raise TypeError("tfk supports float32 and bfloat16 tensors, got %s" % t.dtype)
 
 
-def _stream(stream) -> ctypes.c_void_p:
+# A small layer's kernels take a few microseconds, as long as marshalling one call did (10-12 us for a
+# convolution): what follows from shapes and strides alone -- view and window descriptors, workspace
+# sizes -- is computed once per distinct value and kept (bounded), and addresses and streams are
+# passed as plain integers (5 us).  Nothing is kept by the identity or address of a tensor.
+_KEPT = 4096
+
+
+def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
-def _ptr(t: Optional[torch.Tensor]) -> ctypes.c_void_p:
-    return ctypes.c_void_p(t.data_ptr() if t is not None else 0)
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return t.data_ptr() if t is not None else None
+
+
+def _describe(shape, strides) -> Nhwc:
+    n, h, w, c = shape
+    s0, s1, s2, s3 = strides
+    if n * h * w > 0:
+        ps = s2 if w > 1 else (s1 if h > 1 else (s0 if n > 1 else c))
+        if s3 != 1 or (w > 1 and s2 != ps) or (h > 1 and s1 != w * ps) or (n > 1 and s0 != h * w * ps):
+            raise ValueError("tensor is not an NHWC view with unit channel stride: strides %s" % (tuple(strides),))
+    else:
+        ps = c
+    return Nhwc(n, h, w, c, ps)
 
 
 def nhwc(t: torch.Tensor) -> Nhwc:
     """Describes a 4-D NHWC tensor (or a channel slice of one) for the library."""
     if t.dim() != 4:
         raise ValueError("expected a 4-D NHWC tensor, got shape %s" % (tuple(t.shape),))
-    n, h, w, c = t.shape
-    s0, s1, s2, s3 = t.stride()
-    if n * h * w > 0:
-        ps = s2 if w > 1 else (s1 if h > 1 else (s0 if n > 1 else c))
-        if s3 != 1 or (w > 1 and s2 != ps) or (h > 1 and s1 != w * ps) or (n > 1 and s0 != h * w * ps):
-            raise ValueError("tensor is not an NHWC view with unit channel stride: strides %s" % (t.stride(),))
-    else:
-        ps = c
-    return Nhwc(n, h, w, c, ps)
+    return _describe(t.shape, t.stride())
+
+
+_described = functools.lru_cache(_KEPT)(_describe)
+
+
+def _view(t: torch.Tensor) -> Nhwc:
+    """nhwc(t), shared between calls with tensors of one shape and strides (read only)."""
+    if t.dim() != 4:
+        raise ValueError("expected a 4-D NHWC tensor, got shape %s" % (tuple(t.shape),))
+    return _described(t.shape, t.stride())
 
 
 def window(kh, kw, stride, pads) -> Window:
     sh, sw = (stride, stride) if isinstance(stride, int) else stride
     pt, pb, pl, pr = pads
     return Window(kh, kw, sh, sw, pt, pb, pl, pr)
+
+
+_windowed = functools.lru_cache(_KEPT)(window)
+
+
+def _win(kh, kw, stride, pads) -> Window:
+    """window(...), shared between calls with the same values (read only)."""
+    return _windowed(kh, kw, stride if isinstance(stride, int) else tuple(stride), tuple(pads))
+
+
+@functools.lru_cache(_KEPT)
+def _conv_need(op, shape, strides, cout, kh, kw, stride, pads, dt) -> int:
+    return load().tfk_conv2d_workspace_bytes(op, _describe(shape, strides), cout, window(kh, kw, stride, pads), dt)
+
+
+def _conv_ws_need(op, x, cout, kh, kw, stride, pads, dt) -> int:
+    """The workspace query of a convolution over x (a forward input's view), by its values."""
+    return _conv_need(op, x.shape, x.stride(), cout, kh, kw, stride if isinstance(stride, int) else tuple(stride),
+                      tuple(pads), dt)
+
+
+@functools.lru_cache(_KEPT)
+def _bias_need(shape, strides, dt) -> int:
+    return load().tfk_bias_relu_bwd_workspace_bytes(_describe(shape, strides), dt)
 
 
 def out_len(n, k, s, p0, p1) -> int:
@@ -91,14 +137,14 @@ def _ws(nbytes: int, device, stream=None) -> Optional[torch.Tensor]:
 
 # ----------------------------------------------------------------------------- convolution
 def conv2d_workspace_bytes(op: int, x: torch.Tensor, cout: int, kh, kw, stride, pads) -> int:
-    return load().tfk_conv2d_workspace_bytes(op, nhwc(x), cout, window(kh, kw, stride, pads), _dt(x))
+    return _conv_ws_need(op, x, cout, kh, kw, stride, pads, _dt(x))
 
 
 def _conv_fwd(x, w, bias, stride, pads, y, ws, stream):
     lib = load()
     kh, kw, cin, cout = w.shape
-    win = window(kh, kw, stride, pads)
-    need = lib.tfk_conv2d_workspace_bytes(0, nhwc(x), cout, win, _dt(x))
+    win = _win(kh, kw, stride, pads)
+    need = _conv_ws_need(0, x, cout, kh, kw, stride, pads, _dt(x))
     if need and (ws is None or ws.numel() < need):
         ws = _ws(need, x.device, stream)
     if y is None:
@@ -109,13 +155,13 @@ def _conv_fwd(x, w, bias, stride, pads, y, ws, stream):
         raise TypeError("x, w and y must share one dtype")
     wsp = _ptr(ws) if need else None
     if bias is None:
-        check(lib.tfk_conv2d_fwd(_ptr(x), nhwc(x), _ptr(w), cout, win, _dt(x), _ptr(y), nhwc(y), wsp, need,
+        check(lib.tfk_conv2d_fwd(_ptr(x), _view(x), _ptr(w), cout, win, _dt(x), _ptr(y), _view(y), wsp, need,
                                  _stream(stream)))
     else:
         if bias.dtype != torch.float32 or bias.numel() != cout or not bias.is_contiguous():
             raise ValueError("bias must be a contiguous float32 vector of cout values")
-        check(lib.tfk_conv2d_fwd_bias_relu(_ptr(x), nhwc(x), _ptr(w), cout, _ptr(bias), win, _dt(x), _ptr(y),
-                                           nhwc(y), wsp, need, _stream(stream)))
+        check(lib.tfk_conv2d_fwd_bias_relu(_ptr(x), _view(x), _ptr(w), cout, _ptr(bias), win, _dt(x), _ptr(y),
+                                           _view(y), wsp, need, _stream(stream)))
     return y
 
 
@@ -135,8 +181,8 @@ def conv2d_fwd_bias_relu_maxpool(x, w, bias, stride, pads, pool_hw, pool_stride,
     where the convolution's row bands hold whole pool windows.  Returns (y, py, taps)."""
     lib = load()
     kh, kw, cin, cout = w.shape
-    win = window(kh, kw, stride, pads)
-    need = lib.tfk_conv2d_workspace_bytes(0, nhwc(x), cout, win, _dt(x))
+    win = _win(kh, kw, stride, pads)
+    need = _conv_ws_need(0, x, cout, kh, kw, stride, pads, _dt(x))
     if need and (ws is None or ws.numel() < need):
         ws = _ws(need, x.device, stream)
     n, h, ww, _ = x.shape
@@ -145,7 +191,7 @@ def conv2d_fwd_bias_relu_maxpool(x, w, bias, stride, pads, pool_hw, pool_stride,
     if y is None:
         y = _empty(stream, (n, oh, ow, cout), dtype=x.dtype, device=x.device)
     pkh, pkw = pool_hw
-    pwin = window(pkh, pkw, pool_stride, pool_pads)
+    pwin = _win(pkh, pkw, pool_stride, pool_pads)
     poh = out_len(oh, pkh, pwin.stride_h, pool_pads[0], pool_pads[1])
     pow_ = out_len(ow, pkw, pwin.stride_w, pool_pads[2], pool_pads[3])
     if py is None:
@@ -158,8 +204,8 @@ def conv2d_fwd_bias_relu_maxpool(x, w, bias, stride, pads, pool_hw, pool_stride,
         raise ValueError("taps must be a dense uint8 tensor")
     if bias.dtype != torch.float32 or bias.numel() != cout or not bias.is_contiguous():
         raise ValueError("bias must be a contiguous float32 vector of cout values")
-    check(lib.tfk_conv2d_fwd_bias_relu_maxpool(_ptr(x), nhwc(x), _ptr(w), cout, _ptr(bias), win, _dt(x), _ptr(y),
-                                               nhwc(y), pwin, _ptr(py), nhwc(py), _ptr(taps),
+    check(lib.tfk_conv2d_fwd_bias_relu_maxpool(_ptr(x), _view(x), _ptr(w), cout, _ptr(bias), win, _dt(x), _ptr(y),
+                                               _view(y), pwin, _ptr(py), _view(py), _ptr(taps),
                                                _ptr(ws) if need else None, need, _stream(stream)))
     return y, py, taps
 
@@ -170,11 +216,11 @@ def conv2d_bwd_input(dy, w, dx, stride, pads, beta=0.0, ws=None, stream=None):
     kh, kw, cin, cout = w.shape
     if not (w.dtype == dy.dtype == dx.dtype):
         raise TypeError("dy, w and dx must share one dtype")
-    win = window(kh, kw, stride, pads)
-    need = lib.tfk_conv2d_workspace_bytes(1, nhwc(dx), cout, win, _dt(dx))
+    win = _win(kh, kw, stride, pads)
+    need = _conv_ws_need(1, dx, cout, kh, kw, stride, pads, _dt(dx))
     if need and (ws is None or ws.numel() < need):
         ws = _ws(need, dx.device, stream)
-    check(lib.tfk_conv2d_bwd_input(_ptr(dy), nhwc(dy), _ptr(w), win, _dt(dy), _ptr(dx), nhwc(dx), float(beta),
+    check(lib.tfk_conv2d_bwd_input(_ptr(dy), _view(dy), _ptr(w), win, _dt(dy), _ptr(dx), _view(dx), float(beta),
                                    _ptr(ws) if need else None, need, _stream(stream)))
     return dx
 
@@ -189,11 +235,12 @@ def conv2d_bwd_input_relu_bwd(dy, w, y, dpre, stride, pads, dbias=None, ws=None,
     kh, kw, cin, cout = w.shape
     if not (w.dtype == dy.dtype == y.dtype == dpre.dtype):
         raise TypeError("dy, w, y and dpre must share one dtype")
-    d_y, d_p = nhwc(y), nhwc(dpre)
-    if (d_y.n, d_y.h, d_y.w, d_y.c, d_y.pixel_stride) != (d_p.n, d_p.h, d_p.w, d_p.c, d_p.pixel_stride):
+    d_y, d_p = _view(y), _view(dpre)
+    if d_y is not d_p and ((d_y.n, d_y.h, d_y.w, d_y.c, d_y.pixel_stride) !=
+                           (d_p.n, d_p.h, d_p.w, d_p.c, d_p.pixel_stride)):
         raise ValueError("y and dpre must share one view (extents and pixel stride)")
-    win = window(kh, kw, stride, pads)
-    need = lib.tfk_conv2d_workspace_bytes(3, d_p, cout, win, _dt(y))
+    win = _win(kh, kw, stride, pads)
+    need = _conv_ws_need(3, dpre, cout, kh, kw, stride, pads, _dt(y))
     if defer:
         _need_ws(ws, need)
         dbias = None
@@ -201,7 +248,7 @@ def conv2d_bwd_input_relu_bwd(dy, w, y, dpre, stride, pads, dbias=None, ws=None,
         dbias = _empty(stream, cin, dtype=torch.float32, device=y.device)
     if need and (ws is None or ws.numel() < need):
         ws = _ws(need, y.device, stream)
-    check(lib.tfk_conv2d_bwd_input_relu_bwd(_ptr(dy), nhwc(dy), _ptr(w), win, _dt(dy), _ptr(y), _ptr(dpre), d_p,
+    check(lib.tfk_conv2d_bwd_input_relu_bwd(_ptr(dy), _view(dy), _ptr(w), win, _dt(dy), _ptr(y), _ptr(dpre), d_p,
                                             float(beta), _ptr(dbias), _ptr(ws) if need else None, need,
                                             _stream(stream)))
     return dpre, (_deferred(lib, cin) if defer else dbias)
@@ -216,11 +263,11 @@ def conv2d_bwd_filter(x, dy, kernel_hw, stride, pads, dw=None, ws=None, stream=N
         dw = _empty(stream, (kh, kw, x.shape[3], cout), dtype=torch.float32, device=x.device)
     if dy.dtype != x.dtype or dw.dtype != torch.float32:
         raise TypeError("x and dy share one dtype; dw is float32")
-    win = window(kh, kw, stride, pads)
-    need = lib.tfk_conv2d_workspace_bytes(2, nhwc(x), cout, win, _dt(x))
+    win = _win(kh, kw, stride, pads)
+    need = _conv_ws_need(2, x, cout, kh, kw, stride, pads, _dt(x))
     if ws is None or ws.numel() < need:
         ws = _ws(need, x.device, stream)
-    check(lib.tfk_conv2d_bwd_filter(_ptr(x), nhwc(x), _ptr(dy), nhwc(dy), win, _dt(x), _ptr(dw), _ptr(ws),
+    check(lib.tfk_conv2d_bwd_filter(_ptr(x), _view(x), _ptr(dy), _view(dy), win, _dt(x), _ptr(dw), _ptr(ws),
                                     need, _stream(stream)))
     return dw
 
@@ -234,7 +281,7 @@ def conv2d_bwd_filter_noalloc(x, dy, kernel_hw, stride, pads, dw, stream=None):
         raise TypeError("x and dy share one dtype; dw is float32")
     if tuple(dw.shape) != (kh, kw, x.shape[3], cout) or not dw.is_contiguous():
         raise ValueError("dw must be a contiguous float32 HWIO tensor")
-    check(load().tfk_conv2d_bwd_filter_noalloc(_ptr(x), nhwc(x), _ptr(dy), nhwc(dy), window(kh, kw, stride, pads),
+    check(load().tfk_conv2d_bwd_filter_noalloc(_ptr(x), _view(x), _ptr(dy), _view(dy), _win(kh, kw, stride, pads),
                                                _dt(x), _ptr(dw), _stream(stream)))
     return dw
 
@@ -242,12 +289,12 @@ def conv2d_bwd_filter_noalloc(x, dy, kernel_hw, stride, pads, dw, stream=None):
 # ----------------------------------------------------------------------------- bias + relu
 def bias_relu_fwd(y, bias, stream=None):
     """In place: y <- max(y + bias, 0)."""
-    check(load().tfk_bias_relu_fwd(_ptr(y), nhwc(y), _ptr(bias), _dt(y), _stream(stream)))
+    check(load().tfk_bias_relu_fwd(_ptr(y), _view(y), _ptr(bias), _dt(y), _stream(stream)))
     return y
 
 
 def bias_relu_bwd_workspace_bytes(y) -> int:
-    return load().tfk_bias_relu_bwd_workspace_bytes(nhwc(y), _dt(y))
+    return _bias_need(y.shape, y.stride(), _dt(y))
 
 
 def bias_relu_bwd(y, dy, dpre=None, dbias=None, ws=None, stream=None, defer=False):
@@ -258,7 +305,7 @@ def bias_relu_bwd(y, dy, dpre=None, dbias=None, ws=None, stream=None, defer=Fals
     if dpre is None:
         dpre = _empty_like(stream, dy)
     view = y if y is not None else dy
-    need = lib.tfk_bias_relu_bwd_workspace_bytes(nhwc(view), _dt(view))
+    need = _bias_need(view.shape, view.stride(), _dt(view))
     if defer:
         _need_ws(ws, need)
         dbias = None
@@ -266,7 +313,7 @@ def bias_relu_bwd(y, dy, dpre=None, dbias=None, ws=None, stream=None, defer=Fals
         dbias = _empty(stream, dy.shape[3], dtype=torch.float32, device=dy.device)
     if ws is None or ws.numel() < need:
         ws = _ws(need, dy.device, stream)
-    d_y, d_dy, d_dp = nhwc(view), nhwc(dy), nhwc(dpre)
+    d_y, d_dy, d_dp = _view(view), _view(dy), _view(dpre)
     if (d_y.pixel_stride, d_y.c) != (d_dy.pixel_stride, d_dy.c) or (d_y.pixel_stride, d_y.c) != (d_dp.pixel_stride, d_dp.c):
         raise ValueError("y, dy and dpre must share one view (extents and pixel stride)")
     check(lib.tfk_bias_relu_bwd(_ptr(y), _ptr(dy), d_y, _ptr(dpre), _ptr(dbias), _dt(dy), _ptr(ws), need,
@@ -302,7 +349,7 @@ def maxpool_fwd(x, kernel_hw, stride, pads, y=None, argmax=None, stream=None, ta
     window taps kh * KW + kw (a quarter of the bytes); the backward ops accept either."""
     lib = load()
     kh, kw = kernel_hw
-    win = window(kh, kw, stride, pads)
+    win = _win(kh, kw, stride, pads)
     n, h, w, c = x.shape
     oh = out_len(h, kh, win.stride_h, pads[0], pads[1])
     ow = out_len(w, kw, win.stride_w, pads[2], pads[3])
@@ -311,7 +358,7 @@ def maxpool_fwd(x, kernel_hw, stride, pads, y=None, argmax=None, stream=None, ta
     if argmax is None:
         argmax = _empty(stream, (n, oh, ow, c), dtype=torch.uint8 if taps else torch.int32, device=x.device)
     fn = _argmax_fn(lib, "tfk_maxpool_fwd", argmax)
-    check(fn(_ptr(x), nhwc(x), win, _dt(x), _ptr(y), nhwc(y), _ptr(argmax), _stream(stream)))
+    check(fn(_ptr(x), _view(x), win, _dt(x), _ptr(y), _view(y), _ptr(argmax), _stream(stream)))
     return y, argmax
 
 
@@ -325,7 +372,7 @@ def _argmax_fn(lib, name, argmax):
 def maxpool_bwd(dy, argmax, dx, kernel_hw, stride, pads, beta=0.0, stream=None):
     kh, kw = kernel_hw
     fn = _argmax_fn(load(), "tfk_maxpool_bwd", argmax)
-    check(fn(_ptr(dy), _ptr(argmax), nhwc(dy), window(kh, kw, stride, pads), _dt(dy), _ptr(dx), nhwc(dx),
+    check(fn(_ptr(dy), _ptr(argmax), _view(dy), _win(kh, kw, stride, pads), _dt(dy), _ptr(dx), _view(dx),
              float(beta), _stream(stream)))
     return dx
 
@@ -342,17 +389,18 @@ def maxpool_bwd_relu_bwd(dy, argmax, y, dpre, kernel_hw, stride, pads, beta=0.0,
     lib = load()
     kh, kw = kernel_hw
     fn = _argmax_fn(lib, "tfk_maxpool_bwd_relu_bwd", argmax)
-    d_p = nhwc(dpre)
+    d_p = _view(dpre)
     if y is not None:
-        d_y = nhwc(y)
-        if (d_y.n, d_y.h, d_y.w, d_y.c, d_y.pixel_stride) != (d_p.n, d_p.h, d_p.w, d_p.c, d_p.pixel_stride):
+        d_y = _view(y)
+        if d_y is not d_p and ((d_y.n, d_y.h, d_y.w, d_y.c, d_y.pixel_stride) !=
+                           (d_p.n, d_p.h, d_p.w, d_p.c, d_p.pixel_stride)):
             raise ValueError("y and dpre must share one view (extents and pixel stride)")
     pys = 0
     if py is not None:
         if tuple(py.shape) != tuple(dy.shape) or py.dtype != dy.dtype:
             raise ValueError("py must have dy's shape and element type")
-        pys = nhwc(py).pixel_stride
-    need = lib.tfk_bias_relu_bwd_workspace_bytes(d_p, _dt(dpre))
+        pys = _view(py).pixel_stride
+    need = _bias_need(dpre.shape, dpre.stride(), _dt(dpre))
     if defer:
         _need_ws(ws, need)
         dbias = None
@@ -360,7 +408,7 @@ def maxpool_bwd_relu_bwd(dy, argmax, y, dpre, kernel_hw, stride, pads, beta=0.0,
         dbias = _empty(stream, dpre.shape[3], dtype=torch.float32, device=dpre.device)
     if ws is None or ws.numel() < need:
         ws = _ws(need, dpre.device, stream)
-    check(fn(_ptr(dy), _ptr(argmax), nhwc(dy), window(kh, kw, stride, pads), _dt(dy),
+    check(fn(_ptr(dy), _ptr(argmax), _view(dy), _win(kh, kw, stride, pads), _dt(dy),
              _ptr(y), _ptr(py), pys, _ptr(dpre), d_p,
              float(beta), _ptr(dbias), _ptr(ws), need, _stream(stream)))
     return dpre, (_deferred(lib, dpre.shape[3]) if defer else dbias)
