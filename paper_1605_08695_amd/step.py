@@ -433,7 +433,7 @@ class Replica:
         self.lane_streams = {k: self.side if k == 1 else torch.cuda.Stream(device=dev) for k in used}
         self.lane_ws = {k: torch.zeros_like(self.ws) for k in used}
         self.marks = {}                          # node index (or "start") -> ops.Mark, made on first use
-        self.use_side, self.use_lanes = self._stream_rule()
+        self.use_streams = self._stream_rule()
         # ---- bias gradients of an untraced step: each ReLU/bias backward leaves its per-block
         # partials in a workspace of its own, and one launch sums them all before the update
         self.defer_bias = True
@@ -447,19 +447,20 @@ class Replica:
     kBwdLanes = 2
 
     # A fork to another stream and its join cost 6-13 us of host time (an event recorded and waited
-    # for) and drain the stream they are recorded on, whatever the kernels do.  Recorded steps, by
-    # the mean work of the filter gradients that would run on the side stream (serial / side stream /
-    # side and lanes, us): an inception module 14 x 14 at batch 4 (0.1 GFLOP) 144 / 178 / 229, batch 16
-    # (0.5) 170 / 192 / 244, batch 48 (1.6) 241 / 215 / 242, batch 128 (4.3) 349 / 330 / 332; GoogLeNet
-    # batch 2 (0.1) 943 / 1078 / 1392, batch 16 (0.6) 1271 / 1161 / 1561, batch 128 (4.9) 3387 / 3082 /
-    # 2894; Inception-v3 batch 4 (0.5) 2354 / 2983 / 3045; the AlexNet stack batch 4 (1.3) 201 / 193.
-    kSideFlops = 0.8e9
-    kLaneFlops = 3e9
+    # for) and drain the stream they are recorded on, whatever the kernels do.  Recorded steps by the
+    # mean work of the filter gradients that would run on the side stream, one stream / side stream /
+    # side stream and lanes (us): inception modules 28 x 28 at batch 8 (0.8 GFLOP) 189 / 205 / 250, batch
+    # 16 (1.6) 244 / 250 / 257, batch 32 (3.2) 320 / 297 / 288, batch 128 (13) 796 / 732 / 736; 14 x 14 at
+    # batch 32 (1.1) 220 / 213 / 263, batch 63 (2.1) 277 / 279 / 266, batch 128 (4.3) 375 / 348 / 348; 7 x 7 at
+    # batch 64 (1.5) 237 / 245 / 273; the AlexNet stack at batch 8 (2.4) 250 / 232, batch 32 (9.7) 400 / 385;
+    # GoogLeNet batch 2 (0.1) 943 / 1078 / 1392, batch 128 (4.9) 3387 / 3082 / 2894; Inception-v3 batch 4
+    # (0.5) 2354 / 2983 / 3045.
+    kStreamFlops = 1.8e9
 
-    def _stream_rule(self):
-        """Whether a concurrent step is worth a side stream for the filter gradients, and lanes for
-        independent branches: (side, lanes).  fp32 counts 8 times (its convolutions take about that
-        much longer); a single filter gradient has only its own input gradient to run beside."""
+    def _stream_rule(self) -> bool:
+        """Whether a concurrent step is worth its streams (the side stream and the lanes).  fp32
+        counts 8 times (its convolutions take about that much longer); a single filter gradient has
+        only its own input gradient to run beside."""
         work = []
         for op in self.ops:
             if isinstance(op, Conv) and (op.src != "x" or self.net.input_grad):
@@ -467,9 +468,8 @@ class Replica:
                                                 else op.dst]
                 work.append(2.0 * n * oh * ow * op.kh * op.kw * self.net.tensors[op.src][3] * op.cout)
         if len(work) < 2:
-            return False, False
-        mean = sum(work) / len(work) * (8.0 if self.dtype == torch.float32 else 1.0)
-        return mean >= self.kSideFlops, mean >= self.kLaneFlops
+            return False
+        return sum(work) / len(work) * (8.0 if self.dtype == torch.float32 else 1.0) >= self.kStreamFlops
 
     def _forward_plan(self, nlanes: int):
         """The forward ops (a pool made inside its convolution left out) placed on ``nlanes``
@@ -874,13 +874,13 @@ class Replica:
             if trace: trace("apply_adam:end", None, stream=stream, var=self.params)
 
     def _passes(self, trace, stream, concurrent):
-        lanes = concurrent and self.use_lanes
-        self.forward(trace, stream, lanes=lanes)
-        self.backward(trace, stream, side=self.side if concurrent and self.use_side else None, lanes=lanes)
+        streams = concurrent and self.use_streams
+        self.forward(trace, stream, lanes=streams)
+        self.backward(trace, stream, side=self.side if streams else None, lanes=streams)
 
     def step(self, trace=None, stream=None, concurrent=True):
         """One training step on ``stream``; unless ``concurrent`` is false, and where the step's work
-        is worth it (``use_side``, ``use_lanes``), the forward pass's independent branches run side
+        is worth it (``use_streams``), the forward pass's independent branches run side
         by side on the lane streams and the filter gradients overlap the rest of the backward
         pass on a second stream.  ``trace(event, op,
         stream=s, **tensors)`` is called before and after every op (``event`` ending in

@@ -424,8 +424,8 @@ def test_streams_at_small_sizes_match_one_stream(make):
     net.lr = 1e-6
     inp = W.make_inputs(net, seed=3)
     one, two = Replica(net, inp), Replica(net, inp)
-    assert not two.use_side and not two.use_lanes
-    two.use_side = two.use_lanes = True
+    assert not two.use_streams
+    two.use_streams = True
     prog = None
     for r in range(3):
         one.step()
@@ -445,11 +445,11 @@ def test_streams_at_small_sizes_match_one_stream(make):
 
 
 def test_stream_rule_by_work():
-    """One stream for small steps and for a network with one filter gradient to overlap, a side
-    stream from middling work on, lanes for the benchmarked sizes."""
+    """One stream for small steps and for a network with one filter gradient to overlap, the side
+    stream and the lanes from middling work on."""
     def rule(net):
-        rep = Replica(net, W.make_inputs(net, seed=0))
-        return rep.use_side, rep.use_lanes
-    assert rule(W.single_layer()) == (False, False)
-    assert rule(W.googlenet(batch=1)) == (False, False)
-    assert rule(W.alexnet(batch=4)) == (True, False)
+        return Replica(net, W.make_inputs(net, seed=0)).use_streams
+    assert not rule(W.single_layer())
+    assert not rule(W.single_layer(batch=64, hw=48, cin=64, cout=96))
+    assert not rule(W.googlenet(batch=1))
+    assert rule(W.alexnet(batch=8))
