@@ -209,7 +209,9 @@ TFK_API tfk_status tfk_conv2d_bwd_input_relu_bwd(const void *dy, tfk_nhwc dyd, c
  * above): op 0 = forward, 1 = backprop-input,
  * 2 = backprop-filter, 3 = backprop-input fused with the ReLU backward;
  * xd is the forward input, cout the filter's output channels.  Returns 0
- * for invalid arguments (the operation itself then reports the error). */
+ * for invalid arguments (the operation itself then reports the error).  Part of it may be room
+ * for a faster form (padded copies of operands whose channel counts are not whole 16-byte
+ * chunks, more partial sums): a call given less, but what its plain form needs, runs that. */
 TFK_API size_t tfk_conv2d_workspace_bytes(int32_t op, tfk_nhwc xd, int32_t cout, tfk_window p,
                                   tfk_dtype dt);
 

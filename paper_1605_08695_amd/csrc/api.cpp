@@ -231,6 +231,20 @@ struct OwnedEvent {
 // write-back for the host's sake, cost the recording stream about 6 us per join).
 constexpr unsigned kJoinEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
 
+// Workspace that a call must be given (op 0 forward, 1 input gradient, 2 filter gradient; the query may
+// ask for more, see use_ws).
+size_t conv_need(int op, int dti, const ConvShape &s) {
+    if (op == 0) return std::max(conv_fold_applies(dti, s) ? conv_fold_ws_bytes(0, s) : 0, conv_fwd_split_ws_bytes(dti, s));
+    return op == 1 ? conv_bwd_data_ws_bytes(dti, s) : conv_bwd_filter_ws_bytes(dti, s);
+}
+
+// Bytes of the caller's workspace that a call may use: all that the query asks for (want) when it holds
+// them and `hits` finds no operand in them, else what it must hold (need).
+template <typename F>
+size_t use_ws(const void *ws, size_t ws_bytes, size_t need, size_t want, F hits) {
+    return want > need && ws != nullptr && ws_bytes >= want && aligned(ws, 16) && !hits(want) ? want : need;
+}
+
 tfk_status join(hipEvent_t e, hipStream_t waiter, hipStream_t producer) {
     hipError_t r = hipEventRecord(e, producer);
     if (r == hipSuccess) r = hipStreamWaitEvent(waiter, e, 0);
@@ -274,10 +288,7 @@ size_t tfk_conv2d_workspace_bytes(int32_t op, tfk_nhwc xd, int32_t cout, tfk_win
     if (op == 3) return conv_bwd_data_relu_ws_want(dti, s, xd.pixel_stride);
     int64_t xs = xd.pixel_stride;
     fold_full_window(s, xs);
-    if (op == 0) return std::max(conv_fold_applies(dti, s) ? conv_fold_ws_bytes(0, s) : 0,
-                                 conv_fwd_split_ws_bytes(dti, s));
-    if (op == 1) return conv_bwd_data_ws_bytes(dti, s);
-    return conv_bwd_filter_ws_bytes(dti, s);
+    return std::max(conv_need(op, dti, s), conv_pad_applies(dti, s) ? conv_pad_ws_bytes(op, dti, s) : 0);
 }
 
 // Validation of the forward convolution (shared by tfk_conv2d_fwd, tfk_conv2d_fwd_bias_relu and the
@@ -303,11 +314,14 @@ static tfk_status conv_fwd_check(const void *x, tfk_nhwc &xd, const void *w, int
     const int64_t xbytes = view_bytes(xd, es), wbytes = filter_bytes(s, es);
     fold_full_window(s, xs);
     const int dti = dt == TFK_F32 ? 0 : 1;
-    need = std::max(conv_fold_applies(dti, s) ? conv_fold_ws_bytes(0, s) : 0, conv_fwd_split_ws_bytes(dti, s));
+    need = conv_need(0, dti, s);
     TRY(check_ws(ws, ws_bytes, need));
-    if (need && (overlap(ws, (int64_t)need, x, xbytes) || overlap(ws, (int64_t)need, w, wbytes) ||
-                 overlap(ws, (int64_t)need, y, yb)))
-        return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
+    const auto hits = [&](size_t b) {
+        return overlap(ws, (int64_t)b, x, xbytes) || overlap(ws, (int64_t)b, w, wbytes) || overlap(ws, (int64_t)b, y, yb) ||
+               (bias != nullptr && b > need && overlap(ws, (int64_t)b, bias, (int64_t)cout * 4));
+    };
+    if (need && hits(need)) return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
+    need = use_ws(ws, ws_bytes, need, conv_pad_applies(dti, s) ? conv_pad_ws_bytes(0, dti, s) : 0, hits);
     return TFK_OK;
 }
 
@@ -321,7 +335,7 @@ static tfk_status conv_fwd_impl(const void *x, tfk_nhwc xd, const void *w, int32
     TRY(conv_fwd_check(x, xd, w, cout, bias, p, dt, y, yd, ws, ws_bytes, s, xs, need));
     if (xd.n == 0) return ok();
     return hip_status(launch_conv_fwd(dt == TFK_F32 ? 0 : 1, x, xs, w, y, yd.pixel_stride, s, bias,
-                                      need ? ws : nullptr, (hipStream_t)stream),
+                                      need ? ws : nullptr, need, (hipStream_t)stream),
                       what);
 }
 
@@ -363,13 +377,16 @@ tfk_status tfk_conv2d_bwd_input(const void *dy, tfk_nhwc dyd, const void *w, tfk
     int64_t xs = dxd.pixel_stride;
     fold_full_window(s, xs);
     const int dti = dt == TFK_F32 ? 0 : 1;
-    const size_t need = conv_bwd_data_ws_bytes(dti, s);
+    size_t need = conv_need(1, dti, s);
     TRY(check_ws(ws, ws_bytes, need));
-    if (need && (overlap(ws, (int64_t)need, dy, view_bytes(dyd, es)) || overlap(ws, (int64_t)need, w, wbytes) ||
-                 overlap(ws, (int64_t)need, dx, xb)))
-        return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
+    const auto hits = [&](size_t b) {
+        return overlap(ws, (int64_t)b, dy, view_bytes(dyd, es)) || overlap(ws, (int64_t)b, w, wbytes) ||
+               overlap(ws, (int64_t)b, dx, xb);
+    };
+    if (need && hits(need)) return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
+    need = use_ws(ws, ws_bytes, need, conv_pad_applies(dti, s) ? conv_pad_ws_bytes(1, dti, s) : 0, hits);
     return hip_status(launch_conv_bwd_data(dti, dy, dyd.pixel_stride, w, dx, xs, beta, s,
-                                           need ? (float *)ws : nullptr, (hipStream_t)stream),
+                                           need ? (float *)ws : nullptr, need, (hipStream_t)stream),
                       "conv2d_bwd_input");
 }
 
@@ -417,7 +434,7 @@ tfk_status tfk_conv2d_bwd_input_relu_bwd(const void *dy, tfk_nhwc dyd, const voi
     if (hits(need)) return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
     // (beyond the required bytes the workspace is used only where it holds all that is wanted)
     const size_t want = conv_bwd_data_relu_ws_want(dti, s, xs);
-    const size_t use = ws_bytes >= want && !hits(want) ? want : need;
+    const size_t use = use_ws(ws, ws_bytes, need, want, hits);
     BiasPartials bp{nullptr, 0};
     TRY(hip_status(launch_conv_bwd_data_relu(dti, dy, dyd.pixel_stride ? dyd.pixel_stride : dyd.c, w, dpre, xs, y,
                                              beta, dbias, (float *)ws, use, s, st, dbias ? nullptr : &bp),
@@ -445,14 +462,16 @@ tfk_status tfk_conv2d_bwd_filter(const void *x, tfk_nhwc xd, const void *dy, tfk
     const int64_t xb = view_bytes(xd, es), yb = view_bytes(dyd, es);
     int64_t xs = xd.pixel_stride;
     fold_full_window(s, xs);
-    const size_t need = conv_bwd_filter_ws_bytes(dti, s);
+    size_t need = conv_need(2, dti, s);
     TRY(check_ws(ws, ws_bytes, need));
     if (overlap(dw, wb, x, xb) || overlap(dw, wb, dy, yb))
         return fail(TFK_ERR_ALIAS, "dw overlaps x or dy");
-    if (need && (overlap(ws, (int64_t)need, x, xb) || overlap(ws, (int64_t)need, dy, yb) ||
-                 overlap(ws, (int64_t)need, dw, wb)))
-        return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
-    return hip_status(launch_conv_bwd_filter(dti, x, xs, dy, dyd.pixel_stride, dw, s, ws, st),
+    const auto hits = [&](size_t b) {
+        return overlap(ws, (int64_t)b, x, xb) || overlap(ws, (int64_t)b, dy, yb) || overlap(ws, (int64_t)b, dw, wb);
+    };
+    if (need && hits(need)) return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
+    need = use_ws(ws, ws_bytes, need, conv_pad_applies(dti, s) ? conv_pad_ws_bytes(2, dti, s) : 0, hits);
+    return hip_status(launch_conv_bwd_filter(dti, x, xs, dy, dyd.pixel_stride, dw, s, ws, need, st),
                       "conv2d_bwd_filter");
 }
 
@@ -630,7 +649,9 @@ tfk_status tfk_conv2d_fwd_bias_relu_maxpool(const void *x, tfk_nhwc xd, const vo
     if (overlap(taps, tb, x, xb) || overlap(taps, tb, w, wb) || overlap(taps, tb, y, yb) || overlap(taps, tb, py, pb) ||
         overlap(taps, tb, bias, bb))
         return fail(TFK_ERR_ALIAS, "taps overlap a tensor");
-    if (need && (overlap(ws, (int64_t)need, py, pb) || overlap(ws, (int64_t)need, taps, tb)))
+    const auto hits = [&](size_t b) { return overlap(ws, (int64_t)b, py, pb) || overlap(ws, (int64_t)b, taps, tb); };
+    if (need && hits(need)) need = conv_need(0, dt == TFK_F32 ? 0 : 1, s);
+    if (need && hits(need))
         return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
     hipStream_t st = (hipStream_t)stream;
     const char *what = "conv2d_fwd_bias_relu_maxpool";
@@ -641,7 +662,7 @@ tfk_status tfk_conv2d_fwd_bias_relu_maxpool(const void *x, tfk_nhwc xd, const vo
     }
     // not one kernel for this shape: the convolution, then the max-pool of y
     const hipError_t e = launch_conv_fwd(dt == TFK_F32 ? 0 : 1, x, xs, w, y, yd.pixel_stride, s, bias,
-                                         need ? ws : nullptr, st);
+                                         need ? ws : nullptr, need, st);
     if (e != hipSuccess) return hip_status(e, what);
     return hip_status(launch_maxpool_fwd(dt == TFK_F32 ? 0 : 1, y, g, py, taps, true, st), what);
 }

@@ -148,12 +148,25 @@ size_t conv_bwd_data_relu_ws_bytes(int dt, const ConvShape &s, int64_t dxs) {
 // The rule's tiles (and fp32's fused kernel) may leave more partials than the workspace must hold:
 // the query asks for room for them, and a call given less takes other tiles (fp32: the unfused pair).
 size_t conv_bwd_data_relu_ws_want(int dt, const ConvShape &s, int64_t dxs) {
-    return std::max(conv_bwd_data_relu_ws_bytes(dt, s, dxs), (size_t)relu_partial_rows(dt, s, true) * s.C * sizeof(float));
+    return std::max({conv_bwd_data_relu_ws_bytes(dt, s, dxs), (size_t)relu_partial_rows(dt, s, true) * s.C * sizeof(float),
+                     conv_pad_applies(dt, s) ? conv_pad_ws_bytes(3, dt, s) : 0});
 }
 
 hipError_t launch_conv_bwd_data_relu(int dt, const void *dy, int64_t dys, const void *w, void *dpre, int64_t dxs,
                                      const void *y, float beta, float *db, float *ws, size_t ws_bytes,
                                      const ConvShape &s, hipStream_t st, BiasPartials *defer) {
+    if (conv_pad_applies(dt, s) && ws_bytes >= conv_pad_ws_bytes(3, dt, s)) {
+        hipError_t e;
+        BiasPartials bp{nullptr, 0};
+        if (conv_bwd_data_padded(dt, dy, dys, w, dpre, dxs, beta, s, y, ws, st, &e, &bp)) {
+            if (e != hipSuccess) return e;
+            if (defer != nullptr) {
+                *defer = bp;
+                return hipSuccess;
+            }
+            return launch_sum_partials(bp.part, bp.rows, s.C, db, st);
+        }
+    }
     int parts = 0;
     float *db_at = nullptr;
     const bool all = ws_bytes >= conv_bwd_data_relu_ws_want(dt, s, dxs);
@@ -172,13 +185,17 @@ hipError_t launch_conv_bwd_data_relu(int dt, const void *dy, int64_t dys, const 
         }
     }
     // otherwise the two ops in sequence: the input gradient, then the ReLU backward in place
-    const hipError_t e = launch_conv_bwd_data(dt, dy, dys, w, dpre, dxs, beta, s, nullptr, st);
+    const hipError_t e = launch_conv_bwd_data(dt, dy, dys, w, dpre, dxs, beta, s, nullptr, 0, st);
     if (e != hipSuccess) return e;
     return launch_bias_relu_bwd(dt, y, dpre, dpre, (int64_t)s.N * s.H * s.W, s.C, dxs, db, ws, st, defer);
 }
 
 hipError_t launch_conv_bwd_data(int dt, const void *dy, int64_t dys, const void *w, void *dx, int64_t dxs,
-                                float beta, const ConvShape &s, float *ws, hipStream_t st) {
+                                float beta, const ConvShape &s, float *ws, size_t ws_bytes, hipStream_t st) {
+    if (conv_pad_applies(dt, s) && ws_bytes >= conv_pad_ws_bytes(1, dt, s)) {
+        hipError_t e;
+        if (conv_bwd_data_padded(dt, dy, dys, w, dx, dxs, beta, s, nullptr, ws, st, &e, nullptr)) return e;
+    }
     return dt == 0 ? conv_bwd_data_t<float>(dy, dys, w, dx, dxs, beta, s, st, ws)
                    : conv_bwd_data_t<bf16_t>(dy, dys, w, dx, dxs, beta, s, st, ws);
 }

@@ -148,7 +148,7 @@ static hipError_t conv_bwd_filter_t(const void *x, int64_t xs, const void *dy, i
 }
 
 hipError_t launch_conv_bwd_filter(int dt, const void *x, int64_t xs, const void *dy, int64_t dys, float *dw,
-                                  const ConvShape &s, void *ws, hipStream_t st) {
+                                  const ConvShape &s, void *ws, size_t ws_bytes, hipStream_t st) {
     if (dt == 1 && conv_band_bwf_applies(s) && dys % 8 == 0 && aligned16p(dy) && aligned16p(ws)) {
         const int64_t npix = (int64_t)s.N * s.H * s.W;
         unsigned char *base = reinterpret_cast<unsigned char *>(ws);
@@ -160,6 +160,10 @@ hipError_t launch_conv_bwd_filter(int dt, const void *x, int64_t xs, const void 
     }
     if (conv_fold_applies(dt, s) && dys % 8 == 0 && ((uintptr_t)dy & 15) == 0 && ((uintptr_t)ws & 15) == 0)
         return launch_conv_bwd_filter_folded(x, xs, dy, dys, dw, s, ws, st);
+    if (conv_pad_applies(dt, s) && !conv_fold_applies(dt, s) && ws_bytes >= conv_pad_ws_bytes(2, dt, s)) {
+        hipError_t e;
+        if (conv_bwd_filter_padded(dt, x, xs, dy, dys, dw, s, ws, st, &e)) return e;
+    }
     return dt == 0 ? conv_bwd_filter_t<float>(x, xs, dy, dys, dw, s, ws, st)
                    : conv_bwd_filter_t<bf16_t>(x, xs, dy, dys, dw, s, ws, st);
 }

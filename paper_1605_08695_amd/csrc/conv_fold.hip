@@ -213,7 +213,7 @@ hipError_t launch_conv_fwd_folded(const void *x, int64_t xs, const void *w, void
                        reinterpret_cast<const bf16_t *>(w), s.KH, s.KW, s.C, s.K, f.F, f.Cp, f.v.KW, wv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_conv_fwd(1, xin, 8, wv, y, ys, f.v, bias, nullptr, st);
+    return launch_conv_fwd(1, xin, 8, wv, y, ys, f.v, bias, nullptr, 0, st);
 }
 
 hipError_t launch_conv_bwd_filter_folded(const void *x, int64_t xs, const void *dy, int64_t dys, float *dw,
@@ -230,7 +230,7 @@ hipError_t launch_conv_bwd_filter_folded(const void *x, int64_t xs, const void *
     const bf16_t *xin = padded_input(x, npix, s.C, xs, f.Cp, xp, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_conv_bwd_filter(1, xin, 8, dy, dys, dwv, f.v, ws2, st);
+    e = launch_conv_bwd_filter(1, xin, 8, dy, dys, dwv, f.v, ws2, 0, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(unfold_filter_grad_kernel, dim3(grid_of((int64_t)s.KH * s.KW * s.C * s.K)), dim3(256), 0, st,
                        dwv, s.KH, s.KW, s.C, s.K, f.F, f.Cp, f.v.KW, dw);

@@ -171,7 +171,7 @@ bool conv_fwd_pool_fused(const void *x, int64_t xs, const void *w, void *y, int6
 }
 
 hipError_t launch_conv_fwd(int dt, const void *x, int64_t xs, const void *w, void *y, int64_t ys,
-                           const ConvShape &s, const float *bias, void *ws, hipStream_t st) {
+                           const ConvShape &s, const float *bias, void *ws, size_t ws_bytes, hipStream_t st) {
     if (dt == 1 && ws != nullptr && conv_band_fwd_applies(s) && aligned16p(w) && ((uintptr_t)y & 7) == 0 &&
         ys % 4 == 0) {
         const bf16_t *x4 = rgbx_input(x, (int64_t)s.N * s.H * s.W, s.C, xs, reinterpret_cast<bf16_t *>(ws), st);
@@ -181,6 +181,10 @@ hipError_t launch_conv_fwd(int dt, const void *x, int64_t xs, const void *w, voi
     }
     if (ws != nullptr && conv_fold_applies(dt, s) && ((uintptr_t)y & 15) == 0 && ys % 8 == 0)
         return launch_conv_fwd_folded(x, xs, w, y, ys, s, bias, ws, st);
+    if (conv_pad_applies(dt, s) && !conv_fold_applies(dt, s) && ws_bytes >= conv_pad_ws_bytes(0, dt, s)) {
+        hipError_t e;
+        if (conv_fwd_padded(dt, x, xs, w, y, ys, s, bias, ws, st, &e)) return e;
+    }
     return dt == 0 ? conv_fwd_t<float>(x, xs, w, y, ys, s, bias, ws, st)
                    : conv_fwd_t<bf16_t>(x, xs, w, y, ys, s, bias, ws, st);
 }

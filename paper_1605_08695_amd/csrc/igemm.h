@@ -58,6 +58,7 @@ struct IgArgs {
     int64_t ys;          // pixel stride of y (FWD) or dy (BWD_DATA, BWD_FILTER)
     // GEMM view
     int NI;              // I extent (output channels of this direction)
+    int ni_store;        // pipelined kernel, element-wise epilogue: channels that exist in the output
     int tiles_i;         // number of I tiles (blockIdx.x = tj * tiles_i + ti)
     int k_split;         // BWD_FILTER: reduction elements per split (multiple of the K tile)
     int64_t split_stride;// BWD_FILTER: floats between consecutive partial outputs

@@ -181,7 +181,9 @@ __device__ __forceinline__ int xcd_order(int linear, int total) {
 // SIMD runs two waves: one 8-wave block per CU, or two 4-wave blocks per CU when NS
 // stages fit twice in the 160 KiB of LDS.  Two independent blocks keep a CU's MFMAs busy
 // while the other block waits at its barrier for a slow copy.
-template <typename T, int DIR, int BI, int BJ, int NW, int NS>
+// RAG: the output's channel count (a.ni_store <= a.NI) or addresses do not allow vector stores:
+// the epilogue reads and writes single elements.
+template <typename T, int DIR, int BI, int BJ, int NW, int NS, bool RAG = false>
 __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     constexpr int ES = sizeof(T), EPC = 16 / ES;      // element bytes, elements per 16-byte chunk
     constexpr int BK = 8 * EPC;
@@ -263,7 +265,8 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
             for (int x = 0; x < MI; ++x) {
                 const int i = i0 + (wave & 1) * WI + x * 16 + 4 * (lane >> 4);
                 if (i < a.NI)
-                    for (int q = 0; q < 4; ++q) a.db_part[(int64_t)(i + q) * a.db_rows + row] = 0.f;
+                    for (int q = 0; q < 4; ++q)
+                        if (!RAG || i + q < a.ni_store) a.db_part[(int64_t)(i + q) * a.db_rows + row] = 0.f;
             }
         }
         return;
@@ -608,7 +611,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
                 const int i = i0 + wi * WI + x * 16 + 4 * lg;
                 if (i < a.NI)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) bq[x][q] = a.bias[i + q];
+                    for (int q = 0; q < 4; ++q) bq[x][q] = !RAG || i + q < a.ni_store ? a.bias[i + q] : 0.f;
             }
         }
     }
@@ -634,7 +637,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     // forward with a fused max-pool: the band's bf16 outputs are staged in LDS (channels of the
     // first half of the tile in lds0, of the second in lds1, [row][channel]) once every wave has
     // finished reading the operand stages
-    constexpr bool kPoolFits = ES == 2 && DIR == DIR_FWD && BJ * BI <= 128 * (BI + BJ) && BI % 4 == 0;
+    constexpr bool kPoolFits = ES == 2 && !RAG && DIR == DIR_FWD && BJ * BI <= 128 * (BI + BJ) && BI % 4 == 0;
     const bool pooled = kPoolFits && banded && a.pool_y != nullptr;
     constexpr int HC = BI / 2;                        // channels per staging half
     if (pooled) __syncthreads();
@@ -694,6 +697,22 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
             if constexpr (DIR == DIR_BWD_FILTER) {
                 float *o = reinterpret_cast<float *>(a.out) + rowoff + i;
                 *reinterpret_cast<f32x4_t *>(o) = v;          // NI % 4 == 0 and rows 16-byte aligned
+            } else if constexpr (RAG) {
+                T *o = reinterpret_cast<T *>(a.out) + rowoff + i;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (i + q >= a.ni_store) break;
+                    float r = v[q];
+                    if constexpr (DIR == DIR_BWD_DATA) {
+                        if (a.beta != 0.f) r += a.beta * Elem<T>::load(o + q);
+                        if (relu && !(Elem<T>::load(reinterpret_cast<const T *>(a.relu_y) + rowoff + i + q) > 0.f)) r = 0.f;
+                    } else if (a.bias != nullptr) {
+                        const float b = r + bq[x][q];
+                        r = b > 0.f ? b : 0.f;
+                    }
+                    Elem<T>::store(o + q, r);
+                    if (relu) cs[x][q] += ES == 4 ? r : bf16_to_f32(f32_to_bf16(r));
+                }
             } else if constexpr (ES == 4) {
                 float *o = reinterpret_cast<float *>(a.out) + rowoff + i;
                 f32x4_t r = v;
@@ -829,7 +848,8 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
             const int i = i0 + wi * WI + x * 16 + 4 * lg;
             if (ld == 0 && i < a.NI) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) a.db_part[(int64_t)(i + q) * a.db_rows + row] = cs[x][q];
+                for (int q = 0; q < 4; ++q)
+                    if (!RAG || i + q < a.ni_store) a.db_part[(int64_t)(i + q) * a.db_rows + row] = cs[x][q];
             }
         }
     }

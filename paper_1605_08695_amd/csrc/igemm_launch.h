@@ -170,6 +170,32 @@ static bool igemm2_launch(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipS
     return false;
 }
 
+// The kernel with the element-wise epilogue (RAG): the rule's tiles, of those compiled for it.
+template <typename T>
+static inline Igemm2Tile rag_tiles(int ni, int mj, int zdim) {
+    if constexpr (sizeof(T) == 4) {
+        return Igemm2Tile{64, 64, 4, 3};
+    } else {
+        const Igemm2Tile t = igemm2_tiles(ni, mj, zdim);
+        return t.bi == 64 ? t : Igemm2Tile{128, 128, 4, 2};
+    }
+}
+
+template <typename T, int DIR>
+static hipError_t igemm2_launch_rag(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipStream_t st) {
+    a.tiles_i = (a.NI + t.bi - 1) / t.bi;
+    const dim3 grid((unsigned)(a.tiles_i * ((mj + t.bj - 1) / t.bj)), 1, (unsigned)zdim), block(256);
+    if (t.bi == 64 && t.bj == 64)
+        hipLaunchKernelGGL((igemm2_kernel<T, DIR, 64, 64, 4, 3, true>), grid, block, 0, st, a);
+    else if constexpr (sizeof(T) == 2) {
+        if (t.bi == 64)
+            hipLaunchKernelGGL((igemm2_kernel<T, DIR, 64, 128, 4, 2, true>), grid, block, 0, st, a);
+        else
+            hipLaunchKernelGGL((igemm2_kernel<T, DIR, 128, 128, 4, 2, true>), grid, block, 0, st, a);
+    }
+    return hipGetLastError();
+}
+
 // Split-K for GEMMs with few output tiles (fully connected layers at small batch): the
 // reduction is cut into ranges of whole 64-wide K tiles, one per blockIdx.z, so that about 256
 // blocks run, each range keeping at least 8 K tiles.  Returns the number of ranges (1: no split)
@@ -228,6 +254,7 @@ static inline void fill_geom(IgArgs &a, const ConvShape &s) {
     a.beta = 0.f;
     a.bias = nullptr;
     a.xcd_order = 1;
+    a.ni_store = 0;
     a.k_split = 0;
     a.split_stride = 0;
     a.bytes_i = a.bytes_j = 0;

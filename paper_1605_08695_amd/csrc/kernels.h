@@ -40,8 +40,10 @@ struct SgdBatch {
 
 // dt: 0 = fp32, 1 = bf16
 // bias (may be null): fused y = max(conv + bias, +0).
+// ws_bytes: what the caller knows ws to hold; from conv_pad_ws_bytes on, shapes that conv_pad_applies to
+// run on padded copies (here and in the other directions).
 hipError_t launch_conv_fwd(int dt, const void *x, int64_t xs, const void *w, void *y, int64_t ys,
-                           const ConvShape &s, const float *bias, void *ws, hipStream_t st);
+                           const ConvShape &s, const float *bias, void *ws, size_t ws_bytes, hipStream_t st);
 // The forward convolution with bias + ReLU and a VALID max-pool of its output (g: the pool over
 // y) fused in one kernel, when its row bands cover whole pool windows (bf16, the implicit-GEMM
 // path): writes y, the pooled py (pixel stride pys) and the uint8 window taps.  Returns false,
@@ -50,7 +52,7 @@ bool conv_fwd_pool_fused(const void *x, int64_t xs, const void *w, void *y, int6
                          const float *bias, const PoolGeom &g, void *py, int64_t pys, uint8_t *taps,
                          hipStream_t st, hipError_t *err);
 hipError_t launch_conv_bwd_data(int dt, const void *dy, int64_t dys, const void *w, void *dx, int64_t dxs,
-                                float beta, const ConvShape &s, float *ws, hipStream_t st);
+                                float beta, const ConvShape &s, float *ws, size_t ws_bytes, hipStream_t st);
 // Workspace of the split-K forward / input gradient (0: no split for this shape).
 size_t conv_fwd_split_ws_bytes(int dt, const ConvShape &s);
 size_t conv_bwd_data_ws_bytes(int dt, const ConvShape &s);
@@ -84,7 +86,7 @@ struct PartialsBatch {
 hipError_t launch_sum_partials_multi(int count, const float *const *part, const int *rows, const int *channels,
                                      float *const *out, hipStream_t st);
 hipError_t launch_conv_bwd_filter(int dt, const void *x, int64_t xs, const void *dy, int64_t dys, float *dw,
-                                  const ConvShape &s, void *ws, hipStream_t st);
+                                  const ConvShape &s, void *ws, size_t ws_bytes, hipStream_t st);
 // Split-K plan of bwd-filter: number of splits and reduction elements per split.
 void conv_bwd_filter_plan(int dt, const ConvShape &s, int *splits, int *k_split);
 size_t conv_bwd_filter_ws_bytes(int dt, const ConvShape &s);
@@ -92,6 +94,18 @@ size_t conv_bwd_filter_ws_bytes(int dt, const ConvShape &s);
 // device, which must be the device of `stream`.
 size_t noalloc_scratch_bytes();
 hipError_t noalloc_scratch(void **ptr, hipStream_t stream);
+// Channel counts that are not multiples of a 16-byte chunk, on padded copies in the workspace
+// (conv_pad.hip).  The launchers return false, launching nothing, when an operand that is not copied is
+// misaligned.  op: 0 forward, 1 input gradient, 2 filter gradient, 3 input gradient with the ReLU backward.
+bool conv_pad_applies(int dt, const ConvShape &s);
+size_t conv_pad_ws_bytes(int op, int dt, const ConvShape &s);
+bool conv_fwd_padded(int dt, const void *x, int64_t xs, const void *w, void *y, int64_t ys, const ConvShape &s,
+                     const float *bias, void *ws, hipStream_t st, hipError_t *err);
+bool conv_bwd_data_padded(int dt, const void *dy, int64_t dys, const void *w, void *dx, int64_t dxs, float beta,
+                          const ConvShape &s, const void *relu_y, void *ws, hipStream_t st, hipError_t *err,
+                          BiasPartials *parts);
+bool conv_bwd_filter_padded(int dt, const void *x, int64_t xs, const void *dy, int64_t dys, float *dw, const ConvShape &s,
+                            void *ws, hipStream_t st, hipError_t *err);
 // bf16 convolutions with C % 8 != 0 run as an equivalent 8-channel convolution (conv_fold.hip).
 bool conv_fold_applies(int dt, const ConvShape &s);
 size_t conv_fold_ws_bytes(int op, const ConvShape &s);

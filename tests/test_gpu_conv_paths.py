@@ -96,6 +96,44 @@ def test_conv_bf16_paths(case):
     _check_all(name, torch.bfloat16, N, H, W, C, K, KH, KW, s, pads, wide)
 
 
+# channel counts that are not multiples of a 16-byte chunk: padded copies in the workspace and the
+# element-wise epilogue (one or both counts odd, strided phases, channel slices at odd offsets, 64-
+# and 128-channel tiles)
+PAD_CASES = [
+    ("pad_c21_k64", torch.bfloat16, 12, 33, 31, 21, 64, 3, 3, 1, (1, 1, 1, 1), 0),
+    ("pad_c64_k37", torch.bfloat16, 5, 41, 25, 64, 37, 3, 3, 1, (1, 1, 1, 1), 0),
+    ("pad_c45_k131_s2", torch.bfloat16, 16, 29, 30, 45, 131, 3, 3, 2, (1, 0, 1, 0), 0),
+    ("pad_c99_k203_slices", torch.bfloat16, 6, 23, 21, 99, 203, 1, 3, 1, (0, 0, 1, 1), 5),
+    ("pad_c250_k250_wide", torch.bfloat16, 9, 64, 64, 250, 250, 1, 1, 1, (0, 0, 0, 0), 0),
+    ("pad_small", torch.bfloat16, 1, 9, 11, 9, 70, 3, 3, 1, (1, 1, 1, 1), 0),
+    ("pad_f32_c30_k65", torch.float32, 6, 33, 31, 30, 65, 3, 3, 1, (1, 1, 1, 1), 0),
+    ("pad_f32_c64_k7_s2", torch.float32, 36, 35, 33, 64, 7, 5, 5, 2, (2, 2, 2, 2), 3),
+]
+
+
+@pytest.mark.parametrize("case", PAD_CASES, ids=[c[0] for c in PAD_CASES])
+def test_conv_padded_channels(case):
+    name, dtype, N, H, W, C, K, KH, KW, s, pads, wide = case
+    x = torch.empty((N, H, W, C), dtype=dtype, device=DEV)
+    # (the query asks for the padded copies; their filter alone is more than nothing)
+    assert ops.conv2d_workspace_bytes(0, x, K, KH, KW, s, pads) >= KH * KW * C * K * x.element_size()
+    _check_all(name, dtype, N, H, W, C, K, KH, KW, s, pads, wide)
+
+
+def test_conv_padded_channels_least_workspace():
+    """Without the workspace that the padded copies need (none is required here) the same shapes run
+    on the register-staged kernel."""
+    lib = load()
+    rng = np.random.default_rng(8)
+    x, w = _mk((12, 33, 31, 21), torch.bfloat16, rng), _mk((3, 3, 21, 64), torch.bfloat16, rng, 0.1)
+    y = torch.empty((12, 33, 31, 64), dtype=torch.bfloat16, device=DEV)
+    rc = lib.tfk_conv2d_fwd(ops._ptr(x), ops.nhwc(x), ops._ptr(w), 64, ops.window(3, 3, 1, (1, 1, 1, 1)), 1, ops._ptr(y),
+                            ops.nhwc(y), None, 0, ops._stream(None))
+    assert rc == 0
+    torch.cuda.synchronize()
+    assert_close(f64(y), oracle.conv2d_fwd(f64(x), f64(w), 1, (1, 1, 1, 1)), torch.bfloat16, label="no workspace")
+
+
 def _relu_bwd_with_workspace(dy, w, y, nbytes):
     lib = load()
     ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
