@@ -238,6 +238,12 @@ size_t conv_need(int op, int dti, const ConvShape &s) {
     return op == 1 ? conv_bwd_data_ws_bytes(dti, s) : conv_bwd_filter_ws_bytes(dti, s);
 }
 
+// Workspace that the query asks for beyond that: room for padded copies or a first layer's partials.
+size_t conv_want(int op, int dti, const ConvShape &s) {
+    return std::max(conv_pad_applies(dti, s) ? conv_pad_ws_bytes(op, dti, s) : 0,
+                    op == 2 ? conv_band_bwf_want_bytes(dti, s) : 0);
+}
+
 // Bytes of the caller's workspace that a call may use: all that the query asks for (want) when it holds
 // them and `hits` finds no operand in them, else what it must hold (need).
 template <typename F>
@@ -288,7 +294,7 @@ size_t tfk_conv2d_workspace_bytes(int32_t op, tfk_nhwc xd, int32_t cout, tfk_win
     if (op == 3) return conv_bwd_data_relu_ws_want(dti, s, xd.pixel_stride);
     int64_t xs = xd.pixel_stride;
     fold_full_window(s, xs);
-    return std::max(conv_need(op, dti, s), conv_pad_applies(dti, s) ? conv_pad_ws_bytes(op, dti, s) : 0);
+    return std::max(conv_need(op, dti, s), conv_want(op, dti, s));
 }
 
 // Validation of the forward convolution (shared by tfk_conv2d_fwd, tfk_conv2d_fwd_bias_relu and the
@@ -321,7 +327,7 @@ static tfk_status conv_fwd_check(const void *x, tfk_nhwc &xd, const void *w, int
                (bias != nullptr && b > need && overlap(ws, (int64_t)b, bias, (int64_t)cout * 4));
     };
     if (need && hits(need)) return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
-    need = use_ws(ws, ws_bytes, need, conv_pad_applies(dti, s) ? conv_pad_ws_bytes(0, dti, s) : 0, hits);
+    need = use_ws(ws, ws_bytes, need, conv_want(0, dti, s), hits);
     return TFK_OK;
 }
 
@@ -384,7 +390,7 @@ tfk_status tfk_conv2d_bwd_input(const void *dy, tfk_nhwc dyd, const void *w, tfk
                overlap(ws, (int64_t)b, dx, xb);
     };
     if (need && hits(need)) return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
-    need = use_ws(ws, ws_bytes, need, conv_pad_applies(dti, s) ? conv_pad_ws_bytes(1, dti, s) : 0, hits);
+    need = use_ws(ws, ws_bytes, need, conv_want(1, dti, s), hits);
     return hip_status(launch_conv_bwd_data(dti, dy, dyd.pixel_stride, w, dx, xs, beta, s,
                                            need ? (float *)ws : nullptr, need, (hipStream_t)stream),
                       "conv2d_bwd_input");
@@ -470,7 +476,7 @@ tfk_status tfk_conv2d_bwd_filter(const void *x, tfk_nhwc xd, const void *dy, tfk
         return overlap(ws, (int64_t)b, x, xb) || overlap(ws, (int64_t)b, dy, yb) || overlap(ws, (int64_t)b, dw, wb);
     };
     if (need && hits(need)) return fail(TFK_ERR_ALIAS, "workspace overlaps an operand");
-    need = use_ws(ws, ws_bytes, need, conv_pad_applies(dti, s) ? conv_pad_ws_bytes(2, dti, s) : 0, hits);
+    need = use_ws(ws, ws_bytes, need, conv_want(2, dti, s), hits);
     return hip_status(launch_conv_bwd_filter(dti, x, xs, dy, dyd.pixel_stride, dw, s, ws, need, st),
                       "conv2d_bwd_filter");
 }
@@ -482,19 +488,21 @@ tfk_status tfk_conv2d_bwd_filter_noalloc(const void *x, tfk_nhwc xd, const void 
     TRY(check_conv(xd, dyd.c, p, dt, dyd, "x", "dy", s));
     int64_t xs = xd.pixel_stride;
     fold_full_window(s, xs);
-    const size_t need = conv_bwd_filter_ws_bytes(dt == TFK_F32 ? 0 : 1, s);
-    const size_t have = noalloc_scratch_bytes();
+    const int dti = dt == TFK_F32 ? 0 : 1;
+    const size_t need = conv_need(2, dti, s), have = noalloc_scratch_bytes();
     if (need > have)
         return fail(TFK_ERR_WORKSPACE,
                     "conv2d_bwd_filter_noalloc: this shape needs %zu bytes of scratch, more than the library's "
                     "fixed %zu bytes; use tfk_conv2d_bwd_filter with a workspace",
                     need, have);
+    // (all that the query asks for where the scratch holds it: the same kernels, the same bits)
+    const size_t want = std::max(need, conv_want(2, dti, s)), use = want <= have ? want : need;
     void *scratch = nullptr;
-    if (need) {
+    if (use) {
         const hipError_t e = noalloc_scratch(&scratch, (hipStream_t)stream);
         if (e != hipSuccess) return hip_status(e, "conv2d_bwd_filter_noalloc: device scratch of the stream's GPU");
     }
-    return tfk_conv2d_bwd_filter(x, xd, dy, dyd, p, dt, dw, scratch, need, stream);
+    return tfk_conv2d_bwd_filter(x, xd, dy, dyd, p, dt, dw, scratch, use, stream);
 }
 
 // ------------------------------------------------------------------ bias + ReLU

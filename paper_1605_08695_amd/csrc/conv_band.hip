@@ -31,9 +31,10 @@ namespace {
 
 constexpr int kCUs = 256;                 // MI355X compute units: one persistent workgroup each
 constexpr int kXBand = 45056;             // bytes of one staged input band (5632 pixels)
-constexpr int kBandPix = kXBand / 8;
 constexpr int kMaxKSteps = 18;            // forward: reduction rows <= 18 * 32 (an even number of steps)
-constexpr int kFiltBytes = kMaxKSteps * 32 * 128;
+// Forward of small filters (3 x 3, 7 x 7): half the LDS, so that two workgroups share a CU.
+constexpr int kXBandSmall = 24576;
+constexpr int kMaxKStepsSmall = 8;
 constexpr int kDyBandPix = 256;           // bwd-filter: pixels per band (dy rows of 64 channels)
 constexpr int kBwfGroups = 40;            // bwd-filter: at most 40 16-row tap groups (5 per wave)
 
@@ -50,6 +51,9 @@ struct BandArgs {
     int run;                // bands per workgroup: workgroup g takes bands g * run .. g * run + run - 1
     int rows_in;            // staged input rows per band: (R - 1) * sh + KH
     int wst;                // staged pixels per row (even)
+    int pl0;                // image column of staged column 0 is -pl0 (pl, or pl + 1 so that 16-byte copies
+                            // start on an even pixel)
+    int xoff;               // bytes from a window's staged origin for that: 8 (pl0 - pl)
     int kwp;                // taps per filter row in the reduction order (forward: KW rounded to 2; bwd-filter: to 4)
     int nks;                // forward: 32-wide reduction steps (even)
     FastDiv dWst, dOW, dKwp;
@@ -104,7 +108,7 @@ struct BandCopier {
         const int e = X16 ? 2 * u : (u >> 1);            // first pixel of the unit
         uint32_t r, c;
         a.dWst.divmod((uint32_t)e, r, c);
-        const int ih = ih0 + (int)r, iw = (int)c - a.pl;
+        const int ih = ih0 + (int)r, iw = (int)c - a.pl0;
         const bool ok = e < npix && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
         const bf16_t *src = img + ((int64_t)ih * a.W + iw) * 4 + (X16 ? 0 : 2 * (u & 1));
         const void *zero = (const void *)g_zero_chunk;
@@ -128,11 +132,13 @@ __device__ __forceinline__ void band_dma(const BandArgs &a, int b, unsigned char
 // reduction step kk + 1 are read from LDS while the MFMAs of step kk run, and the outputs of a
 // band are stored during the next band (after its loads are issued), so neither the LDS latency
 // nor the drain of the stores stalls the single wave of a SIMD.
-template <bool A16, bool X16>
-__global__ __launch_bounds__(256, 1) void band_fwd_kernel(const BandArgs a) {
-    __shared__ __attribute__((aligned(1024))) unsigned char filt[kFiltBytes];
-    __shared__ __attribute__((aligned(1024))) unsigned char xb0[kXBand];
-    __shared__ __attribute__((aligned(1024))) unsigned char xb1[kXBand];
+// KST: reduction steps that the LDS filter holds, XB: bytes of a staged band, WGS: workgroups per CU,
+// GY: pixel groups per wave and pass.
+template <bool A16, bool X16, int KST, int XB, int WGS, int GY>
+__global__ __launch_bounds__(256, WGS) void band_fwd_kernel(const BandArgs a) {
+    __shared__ __attribute__((aligned(1024))) unsigned char filt[KST * 32 * 128];
+    __shared__ __attribute__((aligned(1024))) unsigned char xb0[XB];
+    __shared__ __attribute__((aligned(1024))) unsigned char xb1[XB];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lg = lane >> 4, ld = lane & 15;
@@ -170,21 +176,21 @@ __global__ __launch_bounds__(256, 1) void band_fwd_kernel(const BandArgs a) {
     }
     // Outputs of the previous pass, stored while the next pass multiplies: packed bf16 of acc[x][y]
     // and the output offset (elements) of each of the lane's pixels (-1: no pixel).
-    uint2 held[4][4];
-    int64_t hoff[4];
+    uint2 held[4][GY];
+    int64_t hoff[GY];
 #pragma unroll
-    for (int y = 0; y < 4; ++y) hoff[y] = -1;
+    for (int y = 0; y < GY; ++y) hoff[y] = -1;
     bf16_t *const out = reinterpret_cast<bf16_t *>(a.out);
     auto store_row = [&](int x) __attribute__((always_inline)) {
         const int co = co0 + 16 * x + 4 * lg;
         if (co >= a.K) return;
 #pragma unroll
-        for (int y = 0; y < 4; ++y)
+        for (int y = 0; y < GY; ++y)
             if (hoff[y] >= 0) *reinterpret_cast<uint2 *>(out + hoff[y] + co) = held[x][y];
     };
 
     const int groups = (a.R * a.OW + 15) >> 4;
-    const int passes = (groups + 15) >> 4;
+    const int passes = (groups + 4 * GY - 1) / (4 * GY);
     for (int it = 0; b < b_end; ++b, ++it) {
         const unsigned char *cur = (it & 1) ? xb1 : xb0;
         unsigned char *nxt = (it & 1) ? xb0 : xb1;
@@ -197,25 +203,25 @@ __global__ __launch_bounds__(256, 1) void band_fwd_kernel(const BandArgs a) {
         const int pb = min(a.R, a.OH - oh0) * a.OW;         // valid pixels of this band
         for (int pass = 0; pass < passes; ++pass) {
             const int nc = pass == 0 ? ncw : 0;
-            int boff[4];
-            int64_t coff[4];
+            int boff[GY];
+            int64_t coff[GY];
 #pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                const int q = (pass * 16 + wave + 4 * y) * 16 + ld;
+            for (int y = 0; y < GY; ++y) {
+                const int q = (pass * 4 * GY + wave + 4 * y) * 16 + ld;
                 uint32_t r, ow;
                 a.dOW.divmod((uint32_t)(q < pb ? q : 0), r, ow);
-                boff[y] = ((int)r * a.sh * a.wst + (int)ow * a.sw) * 8;
+                boff[y] = ((int)r * a.sh * a.wst + (int)ow * a.sw) * 8 + a.xoff;
                 coff[y] = q < pb ? (((int64_t)n * a.OH + oh0 + (int)r) * a.OW + (int)ow) * a.ys : -1;
             }
-            f32x4_t acc[4][4];
+            f32x4_t acc[4][GY];
 #pragma unroll
             for (int x = 0; x < 4; ++x)
 #pragma unroll
-                for (int y = 0; y < 4; ++y) acc[x][y] = fresh_zero4();
+                for (int y = 0; y < GY; ++y) acc[x][y] = fresh_zero4();
 
             // tap pair (kh, kw) = (t / kwp, t % kwp) of t = 8 kk + 2 lg, advanced by 8 taps per step
             int tkh = (2 * lg) / a.kwp, tkw = (2 * lg) % a.kwp;
-            auto load = [&](int kk, U4 (&fi)[4], U4 (&fj)[4]) __attribute__((always_inline)) {
+            auto load = [&](int kk, U4 (&fi)[4], U4 (&fj)[GY]) __attribute__((always_inline)) {
                 const int to = 8 * kk + 2 * lg < ntaps ? (tkh * a.wst + tkw) * 8 : 0;
                 tkw += 8;
 #pragma unroll
@@ -226,7 +232,7 @@ __global__ __launch_bounds__(256, 1) void band_fwd_kernel(const BandArgs a) {
                     }
                 }
 #pragma unroll
-                for (int y = 0; y < 4; ++y) {
+                for (int y = 0; y < GY; ++y) {
                     const unsigned char *p = cur + boff[y] + to;
                     if constexpr (A16) {
                         fj[y] = *reinterpret_cast<const U4 *>(p);
@@ -243,17 +249,17 @@ __global__ __launch_bounds__(256, 1) void band_fwd_kernel(const BandArgs a) {
                     fi[x] = lds_tr_pair(filt + kmajor_off<bf16_t, 64>(k, row), filt + kmajor_off<bf16_t, 64>(k + 4, row));
                 }
             };
-            auto mma = [&](const U4 (&fi)[4], const U4 (&fj)[4]) __attribute__((always_inline)) {
+            auto mma = [&](const U4 (&fi)[4], const U4 (&fj)[GY]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int x = 0; x < 4; ++x)
 #pragma unroll
-                    for (int y = 0; y < 4; ++y) Mfma<bf16_t>::run(acc[x][y], fi[x], fj[y]);
+                    for (int y = 0; y < GY; ++y) Mfma<bf16_t>::run(acc[x][y], fi[x], fj[y]);
             };
             // Two fragment sets: the reads of step kk + 1 are issued before the MFMAs of step kk.
             // Each double step also issues two of this wave's copies of the next band and one
             // channel row of the previous pass's outputs, so that the memory instructions are
             // spread under the MFMAs instead of stalling the wave before or after them.
-            U4 fiA[4], fjA[4], fiB[4], fjB[4];
+            U4 fiA[4], fjA[GY], fiB[4], fjB[GY];
             load(0, fiA, fjA);
             int j = 0;
             for (int kk = 0; kk < a.nks; kk += 2, ++j) {     // nks is even
@@ -276,7 +282,7 @@ __global__ __launch_bounds__(256, 1) void band_fwd_kernel(const BandArgs a) {
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
 #pragma unroll
-                for (int y = 0; y < 4; ++y) {
+                for (int y = 0; y < GY; ++y) {
                     float v4[4] = {acc[x][y][0], acc[x][y][1], acc[x][y][2], acc[x][y][3]};
                     if (a.bias != nullptr) {
 #pragma unroll
@@ -290,7 +296,7 @@ __global__ __launch_bounds__(256, 1) void band_fwd_kernel(const BandArgs a) {
                 }
             }
 #pragma unroll
-            for (int y = 0; y < 4; ++y) hoff[y] = coff[y];
+            for (int y = 0; y < GY; ++y) hoff[y] = coff[y];
         }
 
         wait_barrier<0>();
@@ -543,7 +549,7 @@ __global__ __launch_bounds__(NW * 64, 1) void band_bwf_kernel(const BandArgs a) 
         const int t = 4 * (g < ngroups ? g : 0) + (ld & 3);
         uint32_t kh, kw;
         a.dKwp.divmod((uint32_t)t, kh, kw);
-        tapb[y] = ((int)kh * a.wst + (int)kw) * 8;
+        tapb[y] = ((int)kh * a.wst + (int)kw) * 8 + a.xoff;
     }
 
     // dy of band b: pixel p of the band at k-row p of a k-major [256][64] tile (zero past the
@@ -687,11 +693,11 @@ void fill_band_args(BandArgs &a, const ConvShape &s) {
 
 // Band height: the most output rows whose input rows fit one staged band (and, for bwd-filter,
 // whose pixels fit the dy tile).
-int band_rows(const ConvShape &s, int wst, int max_pix) {
+int band_rows(const ConvShape &s, int wst, int max_pix, int xbytes) {
     int R = 0;
     for (int r = 1; r <= s.OH; ++r) {
         const int rows_in = (r - 1) * s.sh + s.KH;
-        if ((int64_t)rows_in * wst > kBandPix || (max_pix > 0 && r * s.OW > max_pix)) break;
+        if ((int64_t)rows_in * wst > xbytes / 8 || (max_pix > 0 && r * s.OW > max_pix)) break;
         R = r;
     }
     return R;
@@ -699,34 +705,56 @@ int band_rows(const ConvShape &s, int wst, int max_pix) {
 
 // Consecutive bands of an image share KH - sh input rows; a workgroup takes a run of consecutive
 // bands, so those rows are read again from its L2 instead of from memory.  Runs are as long as
-// one band per CU at most would need: ceil(bands / CUs).
-void set_runs(BandArgs &a) { a.run = (a.bands + kCUs - 1) / kCUs; }
+// one band per workgroup slot at most would need: ceil(bands / slots).
+void set_runs(BandArgs &a, int slots) { a.run = (a.bands + slots - 1) / slots; }
 int band_grid(const BandArgs &a) { return (a.bands + a.run - 1) / a.run; }
 
-bool plan(const ConvShape &s, bool bwf, BandArgs &a) {
+void set_bands(BandArgs &a, const ConvShape &s, int R, int slots) {
+    a.R = R;
+    a.rows_in = (R - 1) * s.sh + s.KH;
+    a.bands_per_img = (s.OH + R - 1) / R;
+    a.bands = s.N * a.bands_per_img;
+    set_runs(a, slots);
+}
+
+// Fewer rows per band where the highest bands would leave workgroup slots without one.
+int spread_rows(const ConvShape &s, int R, int slots) {
+    return (int)std::min<int64_t>(R, std::max<int64_t>(1, ((int64_t)s.N * s.OH + slots - 1) / slots));
+}
+
+// The small-filter forward form (half the LDS, two workgroups per CU).
+bool fwd_small(const ConvShape &s, const BandArgs &a) {
+    return a.nks <= kMaxKStepsSmall && band_rows(s, a.wst, 0, kXBandSmall) >= 1;
+}
+
+// base: the plan of the filter gradient's required workspace (at least four tap groups, bands as high as
+// the LDS allows, staged columns from -pl).
+bool plan(const ConvShape &s, bool bwf, BandArgs &a, bool base = false) {
     if (s.C > 4 || s.K % 16 != 0) return false;
     const int kwp = bwf ? (s.KW + 3) / 4 * 4 : (s.KW + 1) / 2 * 2;
-    int wst = (s.OW - 1) * s.sw + kwp;
+    // An even pl0 lets 16-byte copies fill the staged rows (the image's pixel pairs start on even
+    // columns); the forward's 16-byte operand reads of even strides need an unshifted row.
+    a.pl0 = s.pl + (!base && s.pl % 2 != 0 && s.W % 2 == 0 && (bwf || s.sw % 2 != 0) ? 1 : 0);
+    a.xoff = 8 * (a.pl0 - s.pl);
+    int wst = (s.OW - 1) * s.sw + kwp + (a.pl0 - s.pl);
     wst += wst & 1;
     if (bwf) {
-        if (s.KH * (kwp / 4) > kBwfGroups || s.KH * (kwp / 4) < 4) return false;
+        if (s.KH * (kwp / 4) > kBwfGroups || s.KH * (kwp / 4) < (base ? 4 : 2)) return false;
     } else {
         const int nks = ((s.KH * kwp * 4 + 63) / 64) * 2;     // even: the loop runs two steps at a time
         if (nks > kMaxKSteps) return false;
         a.nks = nks;
     }
-    const int R = band_rows(s, wst, bwf ? kDyBandPix : 0);
-    if (R < 1) return false;
     fill_band_args(a, s);
     a.kwp = kwp;
     a.wst = wst;
-    a.R = R;
-    a.rows_in = (R - 1) * s.sh + s.KH;
-    a.bands_per_img = (s.OH + R - 1) / R;
-    const int64_t bands = (int64_t)s.N * a.bands_per_img;
-    if (bands > (1 << 30)) return false;
-    a.bands = (int)bands;
-    set_runs(a);
+    const bool small = !bwf && fwd_small(s, a);
+    const int slots = small ? 2 * kCUs : kCUs;
+    int R = band_rows(s, wst, bwf ? kDyBandPix : 0, small ? kXBandSmall : kXBand);
+    if (R < 1) return false;
+    if (!base) R = spread_rows(s, R, slots);
+    if ((int64_t)s.N * ((s.OH + R - 1) / R) > (1 << 30)) return false;
+    set_bands(a, s, R, slots);
     a.dWst.init((uint32_t)wst);
     a.dOW.init((uint32_t)s.OW);
     a.dKwp.init((uint32_t)kwp);
@@ -736,7 +764,7 @@ bool plan(const ConvShape &s, bool bwf, BandArgs &a) {
 int bwf_splits(const BandArgs &a) { return band_grid(a); }
 
 // 16-byte band copies need pixel pairs that never straddle the image edge.
-bool pairs_aligned(const ConvShape &s) { return s.pl % 2 == 0 && s.W % 2 == 0; }
+bool pairs_aligned(const BandArgs &a) { return a.pl0 % 2 == 0 && a.W % 2 == 0; }
 
 constexpr int kBwfWaves = 8;
 
@@ -760,14 +788,15 @@ bool conv_band_fwd_applies(const ConvShape &s) {
     return plan(s, false, a);
 }
 
-bool conv_band_bwf_applies(const ConvShape &s) {
+// base: within the workspace that a call must be given (see plan).
+bool conv_band_bwf_applies(const ConvShape &s, bool base) {
     BandArgs a;
-    return plan(s, true, a);
+    return plan(s, true, a, base);
 }
 
-size_t conv_band_bwf_partial_bytes(const ConvShape &s) {
+size_t conv_band_bwf_partial_bytes(const ConvShape &s, bool base) {
     BandArgs a;
-    if (!plan(s, true, a)) return 0;
+    if (!plan(s, true, a, base)) return 0;
     return (size_t)bwf_splits(a) * s.KH * s.KW * s.C * s.K * sizeof(float);
 }
 
@@ -783,39 +812,38 @@ hipError_t launch_conv_fwd_band(const bf16_t *x4, const void *w, void *y, int64_
     a.bias = bias;
     a.ys = ys;
     const dim3 grid((unsigned)band_grid(a), (unsigned)((s.K + 63) / 64));
-    const bool x16 = pairs_aligned(s);
+    const bool x16 = pairs_aligned(a);
     constexpr int kRegKS = 17, kRegUPW = 14;    // AlexNet conv1: 11 x 12 taps x 4 channels, 4 rows of 55
     const int ks = (s.KH * a.kwp * 4 + 31) / 32;
     if (ks == kRegKS && s.sw % 2 == 0 && x16 && (int64_t)s.N * s.OH * s.OW * ys < (int64_t)1 << 31) {
-        const int R = band_rows(s, a.wst, 16 * kRegUPW);
+        const int R = band_rows(s, a.wst, 16 * kRegUPW, kXBand);
         if (R >= 1 && (R * s.OW + 15) / 16 == kRegUPW && (R - 1) * s.sh + s.KH <= kRegMaxRows &&
             a.wst <= kRegRowBytes / 8 && a.kwp >= 8) {
-            a.R = R;
-            a.rows_in = (R - 1) * s.sh + s.KH;
-            a.bands_per_img = (s.OH + R - 1) / R;
-            a.bands = s.N * a.bands_per_img;
-            set_runs(a);
+            set_bands(a, s, R, kCUs);
             const dim3 g2((unsigned)band_grid(a), (unsigned)((s.K + 63) / 64));
             hipLaunchKernelGGL((band_fwd_reg_kernel<kRegKS, kRegUPW>), g2, dim3(256), 0, st, a);
             return hipGetLastError();
         }
     }
-    if (s.sw % 2 == 0 && x16)
-        hipLaunchKernelGGL((band_fwd_kernel<true, true>), grid, dim3(256), 0, st, a);
-    else if (s.sw % 2 == 0)
-        hipLaunchKernelGGL((band_fwd_kernel<true, false>), grid, dim3(256), 0, st, a);
-    else if (x16)
-        hipLaunchKernelGGL((band_fwd_kernel<false, true>), grid, dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL((band_fwd_kernel<false, false>), grid, dim3(256), 0, st, a);
+    auto go = [&](auto A16_, auto X16_) {
+        constexpr bool A16 = decltype(A16_)::value, X16 = decltype(X16_)::value;
+        if (fwd_small(s, a))
+            hipLaunchKernelGGL((band_fwd_kernel<A16, X16, kMaxKStepsSmall, kXBandSmall, 2, 2>), grid, dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL((band_fwd_kernel<A16, X16, kMaxKSteps, kXBand, 1, 4>), grid, dim3(256), 0, st, a);
+    };
+    using BT = std::true_type;
+    using BF = std::false_type;
+    if (s.sw % 2 == 0) x16 ? go(BT{}, BT{}) : go(BT{}, BF{});
+    else x16 ? go(BF{}, BT{}) : go(BF{}, BF{});
     return hipGetLastError();
 }
 
-// part: conv_band_bwf_partial_bytes(s) of workspace, 16-byte aligned; dy 16-byte aligned with dys % 8 == 0.
+// part: conv_band_bwf_partial_bytes(s, base) of workspace, 16-byte aligned; dy 16-byte aligned with dys % 8 == 0.
 hipError_t launch_conv_bwd_filter_band(const bf16_t *x4, const void *dy, int64_t dys, float *dw, const ConvShape &s,
-                                       float *part, hipStream_t st) {
+                                       float *part, bool base, hipStream_t st) {
     BandArgs a;
-    if (!plan(s, true, a)) return hipErrorInvalidValue;
+    if (!plan(s, true, a, base)) return hipErrorInvalidValue;
     a.x = x4;
     a.w = nullptr;
     a.dy = reinterpret_cast<const bf16_t *>(dy);
@@ -826,7 +854,7 @@ hipError_t launch_conv_bwd_filter_band(const bf16_t *x4, const void *dy, int64_t
     const int splits = bwf_splits(a);
     const dim3 grid((unsigned)splits, (unsigned)((s.K + 63) / 64));
     const int ng = (s.KH * (a.kwp / 4) + kBwfWaves - 1) / kBwfWaves;     // 16-row tap groups per wave
-    if (pairs_aligned(s))
+    if (pairs_aligned(a))
         launch_bwf<true>(ng, grid, a, st);
     else
         launch_bwf<false>(ng, grid, a, st);

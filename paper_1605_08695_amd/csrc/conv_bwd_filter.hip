@@ -99,8 +99,13 @@ size_t conv_bwd_filter_ws_bytes(int dt, const ConvShape &s) {
     size_t need = plan_ws(s, bwf_plan(dt, s, false));
     if (dt == 1) need = std::max(need, plan_ws(s, bwf_plan(dt, s, true)));
     if (conv_fold_applies(dt, s)) need = std::max(need, conv_fold_ws_bytes(2, s));
-    if (dt == 1 && conv_band_bwf_applies(s)) need = std::max(need, band_x_bytes(s) + conv_band_bwf_partial_bytes(s));
+    if (dt == 1 && conv_band_bwf_applies(s, true))
+        need = std::max(need, band_x_bytes(s) + conv_band_bwf_partial_bytes(s, true));
     return need;
+}
+
+size_t conv_band_bwf_want_bytes(int dt, const ConvShape &s) {
+    return dt == 1 && conv_band_bwf_applies(s, false) ? band_x_bytes(s) + conv_band_bwf_partial_bytes(s, false) : 0;
 }
 
 template <typename T>
@@ -149,14 +154,16 @@ static hipError_t conv_bwd_filter_t(const void *x, int64_t xs, const void *dy, i
 
 hipError_t launch_conv_bwd_filter(int dt, const void *x, int64_t xs, const void *dy, int64_t dys, float *dw,
                                   const ConvShape &s, void *ws, size_t ws_bytes, hipStream_t st) {
-    if (dt == 1 && conv_band_bwf_applies(s) && dys % 8 == 0 && aligned16p(dy) && aligned16p(ws)) {
+    const size_t band = conv_band_bwf_want_bytes(dt, s);
+    const bool base = band == 0 || ws_bytes < band;
+    if (dt == 1 && conv_band_bwf_applies(s, base) && dys % 8 == 0 && aligned16p(dy) && aligned16p(ws)) {
         const int64_t npix = (int64_t)s.N * s.H * s.W;
-        unsigned char *base = reinterpret_cast<unsigned char *>(ws);
-        const bf16_t *x4 = rgbx_input(x, npix, s.C, xs, reinterpret_cast<bf16_t *>(base), st);
+        unsigned char *at = reinterpret_cast<unsigned char *>(ws);
+        const bf16_t *x4 = rgbx_input(x, npix, s.C, xs, reinterpret_cast<bf16_t *>(at), st);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        float *part = reinterpret_cast<float *>(base + band_x_bytes(s));
-        return launch_conv_bwd_filter_band(x4, dy, dys, dw, s, part, st);
+        float *part = reinterpret_cast<float *>(at + band_x_bytes(s));
+        return launch_conv_bwd_filter_band(x4, dy, dys, dw, s, part, base, st);
     }
     if (conv_fold_applies(dt, s) && dys % 8 == 0 && ((uintptr_t)dy & 15) == 0 && ((uintptr_t)ws & 15) == 0)
         return launch_conv_bwd_filter_folded(x, xs, dy, dys, dw, s, ws, st);

@@ -117,6 +117,9 @@ __global__ __launch_bounds__(256) void relu_bwd_partial_kernel(const T *__restri
     const int64_t p0 = (int64_t)blockIdx.x * ppb;
     const int64_t p1 = min(P, p0 + ppb);
     const bool active = row < R;
+    // (without a ReLU, in place: the gradient passes through as it is and is only summed;
+    // 2560 x 1664 bf16 logits' gradient: 11.2 -> 7 us)
+    const bool store = y != nullptr || dpre != dy;
     for (int cv = lane_cv; cv < CV; cv += CVB) {
         float s[EPC];
 #pragma unroll
@@ -156,7 +159,7 @@ __global__ __launch_bounds__(256) void relu_bwd_partial_kernel(const T *__restri
                             fd[e] = fy[e] > 0.f ? fd[e] : 0.f;
                             s[e] += fd[e];
                         }
-                        *reinterpret_cast<U4 *>(dpre + off) = f32_to_chunk<T>(fd);
+                        if (store) *reinterpret_cast<U4 *>(dpre + off) = f32_to_chunk<T>(fd);
                     }
                 }
             }
@@ -167,7 +170,7 @@ __global__ __launch_bounds__(256) void relu_bwd_partial_kernel(const T *__restri
                     const float fy = y != nullptr ? Elem<T>::load(y + off) : 1.f;
                     const float fd = fy > 0.f ? Elem<T>::load(dy + off) : 0.f;
                     s[0] += fd;
-                    Elem<T>::store(dpre + off, fd);
+                    if (store) Elem<T>::store(dpre + off, fd);
                 }
             }
             // The stored dpre equals the value summed here: with bf16 storage the

@@ -166,3 +166,41 @@ def test_conv_relu_bwd_least_workspace(dtype, least):
     # N H W = 6272 terms of one fp32 sum each side: 2 * 6272 * 2^-24 of the sum of magnitudes at most
     bound = 2 * N * H * W * 2.0 ** -24 * f64(a[0].abs()).sum(axis=(0, 1, 2))
     assert np.all(np.abs(f64(a[1]) - f64(b[1])) <= bound)
+
+
+# first layers (at most 4 channels) on the band kernels: few bands (spread over the workgroups), staged
+# columns shifted by one for 16-byte copies (odd left pad, even width), odd widths, one output row, two
+# channel blocks, and filter gradients of two and three tap groups
+FIRST_CASES = [
+    ("first_3x3s1_evenw", 3, 44, 46, 3, 64, 3, 1, (1, 1, 1, 1)),
+    ("first_3x3s1_oddw", 2, 21, 33, 3, 128, 3, 1, (1, 1, 1, 1)),
+    ("first_3x3s2_valid", 5, 35, 41, 3, 32, 3, 2, (0, 0, 0, 0)),
+    ("first_7x7s2_p3", 2, 60, 64, 3, 64, 7, 2, (3, 3, 3, 3)),
+    ("first_7x7s2_p3_oddw", 1, 31, 45, 3, 48, 7, 2, (3, 3, 3, 3)),
+    ("first_one_row", 1, 3, 250, 4, 64, 3, 1, (0, 0, 1, 1)),
+    ("first_wide", 1, 6, 520, 3, 16, 3, 1, (1, 1, 1, 1)),
+    ("first_many_bands", 90, 24, 24, 1, 16, 3, 1, (1, 1, 1, 1)),
+]
+
+
+@pytest.mark.parametrize("rgbx", [False, True], ids=["copied", "in_place"])
+@pytest.mark.parametrize("case", FIRST_CASES, ids=[c[0] for c in FIRST_CASES])
+def test_first_layer_paths(case, rgbx):
+    name, N, H, W, C, K, k, s, pads = case
+    say("first layer", name, rgbx)
+    rng = np.random.default_rng(zlib.crc32(name.encode()))
+    x = _mk((N, H, W, 4), torch.bfloat16, rng)[..., :C] if rgbx else _mk((N, H, W, C), torch.bfloat16, rng)
+    w = _mk((k, k, C, K), torch.bfloat16, rng, np.sqrt(2.0 / (k * k * C)))
+    bias = torch.from_numpy(rng.standard_normal(K) * 0.5).to(torch.float32).to(DEV)
+    y = ops.conv2d_fwd_bias_relu(x, w, bias, s, pads)
+    plain = ops.conv2d_fwd(x, w, s, pads)
+    torch.cuda.synchronize()
+    pre = oracle.conv2d_fwd(f64(x), f64(w), (s, s), pads)
+    assert_close(f64(plain), pre, torch.bfloat16, label="fwd")
+    assert_close(f64(y), oracle.bias_relu_fwd(pre, f64(bias)), torch.bfloat16, label="fwd + bias + relu")
+    dy = _mk(pre.shape, torch.bfloat16, rng)
+    dw = torch.full((k, k, C, K), 3.0, device=DEV)
+    ops.conv2d_bwd_filter(x, dy, (k, k), s, pads, dw=dw)
+    torch.cuda.synchronize()
+    assert_close(f64(dw), oracle.conv2d_bwd_filter(f64(x), f64(dy), (k, k), (s, s), pads), torch.float32, torch.bfloat16,
+                 label="filter gradient")
