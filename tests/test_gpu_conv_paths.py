@@ -168,6 +168,25 @@ def test_conv_relu_bwd_least_workspace(dtype, least):
     assert np.all(np.abs(f64(a[1]) - f64(b[1])) <= bound)
 
 
+# standalone ReLU backward: partial grids of two blocks per CU (with blocks that get no pixel), of 16
+# pixels a block, of one block, and a channel slice
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("P,C,wide", [(8200, 64, 64), (8193, 24, 72), (2304, 768, 768), (2560, 1664, 1664), (37, 72, 72),
+                                      (1, 1000, 1000), (9001, 13, 13)])
+def test_relu_bwd_partial_grid(P, C, wide, dtype):
+    rng = np.random.default_rng(P + C)
+    y = torch.from_numpy(np.maximum(rng.standard_normal((1, 1, P, wide)), 0.0)).to(dtype).to(DEV)[..., :C]
+    full = _mk((1, 1, P, wide), dtype, rng)
+    dy = full[..., :C]
+    for yy in (y, None):
+        dp, db = ops.bias_relu_bwd(yy, dy, dpre=torch.empty_like(full)[..., :C])
+        torch.cuda.synchronize()
+        ref_dp, ref_db = oracle.bias_relu_bwd(f64(y) if yy is not None else np.ones(y.shape), f64(dy))
+        assert np.array_equal(f64(dp), ref_dp)
+        # a sum of P fp32 terms in any order: at most P 2^-24 of the sum of magnitudes
+        assert np.all(np.abs(f64(db) - ref_db) <= P * 2.0 ** -24 * np.abs(ref_dp).sum(axis=(0, 1, 2)) + 1e-30)
+
+
 # first layers (at most 4 channels) on the band kernels: few bands (spread over the workgroups), staged
 # columns shifted by one for 16-byte copies (odd left pad, even width), odd widths, one output row, two
 # channel blocks, and filter gradients of two and three tap groups
