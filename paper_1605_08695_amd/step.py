@@ -356,8 +356,9 @@ class Replica:
             by_dst.setdefault(c.dst, []).append(c)
         self.relu_groups = {}                    # conv name -> (first channel, width, [convs])
         for dst, cs in by_dst.items():
-            cand = sorted((c for c in cs if c.relu and c.name not in self.relu_fused and dst != net.output),
-                          key=lambda c: c.dst_c0)
+            cand = sorted((c for c in cs if c.relu and c.name not in self.relu_fused), key=lambda c: c.dst_c0)
+            if dst == net.output and (dst in readers or any(c.name in member_of for c in cand)):
+                continue
             runs, cur = [], []
             for c in cand:
                 if cur and c.dst_c0 == cur[-1].dst_c0 + cur[-1].cout:
@@ -512,9 +513,14 @@ class Replica:
                     if not m.relu or (m.name not in self.relu_fused and m.name not in self.relu_groups):
                         # (the output's pre-activation gradient: a buffer slice of this op's own)
                         w.add(m.dst if m.dst != net.output else "dpre_out:" + m.name)
-                    elif m.name in self.relu_groups and id(self.relu_groups[m.name][2]) not in grouped:
-                        grouped.add(id(self.relu_groups[m.name][2]))
-                        w.add(m.dst)
+                    elif m.name in self.relu_groups:
+                        # (the output's: a slice of dpre_out that the group's other nodes read)
+                        run = self.relu_groups[m.name][2]
+                        at = m.dst if m.dst != net.output else "dpre_out:" + run[0].name
+                        r.add(at)
+                        if id(run) not in grouped:
+                            grouped.add(id(run))
+                            w.add(at)
                 if src_grad:
                     w.add(op.src)
                     if op.name in self.relu_last:
@@ -656,20 +662,23 @@ class Replica:
         elif op.name in self.relu_fused:
             dpre = dy                        # written by the fused pool / input-gradient backward
         elif op.name in self.relu_groups:
-            dpre = dy
+            # (in place, but for the output tensor: the seed gradient stays as it is)
+            dst = self.dpre_out if op.dst == net.output else self.grad[op.dst]
+            dpre = self._slice({op.dst: dst}, op)
             c0, width, run = self.relu_groups[op.name]
             if id(run) not in grouped:       # the group's last convolution in forward order
                 grouped.add(id(run))
                 yg, dyg = self.act[op.dst][..., c0:c0 + width], self.grad[op.dst][..., c0:c0 + width]
+                dpg = dst[..., c0:c0 + width]
                 dbg = self.grads[self._layout[run[0].name][2]:self._layout[run[0].name][2] + width]
                 if trace: trace("bias_relu_bwd", op, stream=stream, y=yg, dy=dyg)
                 if defer:
                     ws = self._bias_ws(("group", op.dst, c0), ops.bias_relu_bwd_workspace_bytes(yg))
-                    jobs.append((ops.bias_relu_bwd(yg, dyg, dpre=dyg, ws=ws, stream=stream, defer=True)[1],
+                    jobs.append((ops.bias_relu_bwd(yg, dyg, dpre=dpg, ws=ws, stream=stream, defer=True)[1],
                                  dbg))
                 else:
-                    ops.bias_relu_bwd(yg, dyg, dpre=dyg, dbias=dbg, ws=lws, stream=stream)
-                if trace: trace("bias_relu_bwd:end", op, stream=stream, dpre=dyg, db=dbg)
+                    ops.bias_relu_bwd(yg, dyg, dpre=dpg, dbias=dbg, ws=lws, stream=stream)
+                if trace: trace("bias_relu_bwd:end", op, stream=stream, dpre=dpg, db=dbg)
         else:
             y = self._slice(self.act, op)
             dpre = self._slice({op.dst: self.dpre_out}, op) if op.dst == net.output else dy

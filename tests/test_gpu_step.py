@@ -453,3 +453,28 @@ def test_stream_rule_by_work():
     assert not rule(W.single_layer(batch=64, hw=48, cin=64, cout=96))
     assert not rule(W.googlenet(batch=1))
     assert rule(W.alexnet(batch=8))
+
+
+@pytest.mark.parametrize("lanes", [False, True], ids=["one_stream", "lanes"])
+def test_output_concat_relu_backward_is_one_pass(lanes):
+    """The branches that write an output concat have their ReLU backward in one call, into a buffer
+    beside the seed gradient, which the step leaves as it is."""
+    net = W.googlenet(batch=2)
+    net.lr = 1e-6
+    rep = Replica(net, W.make_inputs(net, seed=11))
+    rep.use_streams = lanes
+    last = {c.name: c for c in net.convs if c.dst == net.output}
+    assert len(last) > 1 and all(k in rep.relu_groups for k in last)
+    seed = rep.grad[net.output].clone()
+    for _ in range(2):
+        rep.step()
+        torch.cuda.synchronize()
+        assert bitwise_equal(rep.grad[net.output], seed)
+        for c in last.values():
+            sl = slice(c.dst_c0, c.dst_c0 + c.cout)
+            want = torch.where(rep.act[net.output][..., sl] > 0, seed[..., sl], torch.zeros_like(seed[..., sl]))
+            assert bitwise_equal(rep.dpre_out[..., sl], want), c.name
+            s = want.double().sum(dim=(0, 1, 2))
+            # fp32 sums of P terms in any order: |error| <= P eps sum |term|
+            bound = want[..., 0].numel() * 2.0 ** -24 * want.double().abs().sum(dim=(0, 1, 2)) + 1e-30
+            assert bool(((rep.db[c.name].double() - s).abs() <= bound).all()), c.name
