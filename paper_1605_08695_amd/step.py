@@ -30,6 +30,7 @@ fused activation gradients); that convolution then skips its own ReLU backward.
 """
 from __future__ import annotations
 
+import threading
 from typing import Dict, List, Optional
 
 import numpy as np
@@ -156,6 +157,28 @@ def lane_plan(nodes, deps, nlanes: int):
             for kk, v in node_clock[tail[k]].items():
                 clock[0][kk] = max(clock[0].get(kk, -2), v)
     return plan, joins
+
+
+# The streams beside a step's own, one set per device for all its replicas.  A process gets four
+# hardware queues by default, and a stream takes the least used one at its first work: with streams of
+# its own, a network made after three others had a lane on its main stream's queue (GoogLeNet b128 2.86
+# -> 3.60 ms, Inception-v3 b32 4.13 -> 5.10, slower than one stream).  Steps that share them from several
+# threads stay correct: every wait is for work enqueued before it.
+_device_stream_sets: Dict[int, List["torch.cuda.Stream"]] = {}
+_device_stream_lock = threading.Lock()
+
+
+def _device_streams(dev, n: int) -> List["torch.cuda.Stream"]:
+    """The side stream and further lane streams of ``dev``, at least ``n``; each waits once for the
+    current stream when made, which is its first work."""
+    index = dev.index if dev.index is not None else torch.cuda.current_device()
+    with _device_stream_lock:
+        made = _device_stream_sets.setdefault(index, [])
+        while len(made) < n:
+            s = torch.cuda.Stream(device=index)
+            s.wait_stream(torch.cuda.current_stream(index))
+            made.append(s)
+        return list(made)
 
 
 class Replica:
@@ -420,7 +443,9 @@ class Replica:
             need = max(need, ops.conv2d_workspace_bytes(2, self.act[c.src], c.cout, c.kh, c.kw, (c.sh, c.sw),
                                                         c.pads))
         self.ws_side = torch.zeros(max(16, (need + 15) // 16 * 16), dtype=torch.uint8, device=dev)
-        self.side = torch.cuda.Stream(device=dev)
+        streams = _device_streams(dev, max(self.kFwdLanes - 1, self.kBwdLanes))
+        self.side = streams[0]
+        self.capture_side = torch.cuda.Stream(device=dev)    # (a captured step joins no shared stream)
         # ---- the forward pass's independent branches run on up to kFwdLanes streams (lane 0 is
         # the step's stream, lane 1 the side stream, idle in the forward pass: with the step's
         # stream, four streams, as many as the hardware queues a process gets by default), each
@@ -431,7 +456,7 @@ class Replica:
         self.bwd_plan = self._backward_plan(self.kBwdLanes)
         used = sorted(({lane for _, lane, _ in self.fwd_plan[0]} | {lane + 1 for _, lane, _ in self.bwd_plan[0]
                                                                     if lane > 0}) - {0})
-        self.lane_streams = {k: self.side if k == 1 else torch.cuda.Stream(device=dev) for k in used}
+        self.lane_streams = {k: streams[k - 1] for k in used}
         self.lane_ws = {k: torch.zeros_like(self.ws) for k in used}
         self.marks = {}                          # node index (or "start") -> ops.Mark, made on first use
         self.use_streams = self._stream_rule()
@@ -885,7 +910,8 @@ class Replica:
     def _passes(self, trace, stream, concurrent):
         streams = concurrent and self.use_streams
         self.forward(trace, stream, lanes=streams)
-        self.backward(trace, stream, side=self.side if streams else None, lanes=streams)
+        side = self.capture_side if torch.cuda.is_current_stream_capturing() else self.side
+        self.backward(trace, stream, side=side if streams else None, lanes=streams)
 
     def step(self, trace=None, stream=None, concurrent=True):
         """One training step on ``stream``; unless ``concurrent`` is false, and where the step's work

@@ -478,3 +478,47 @@ def test_output_concat_relu_backward_is_one_pass(lanes):
             # fp32 sums of P terms in any order: |error| <= P eps sum |term|
             bound = want[..., 0].numel() * 2.0 ** -24 * want.double().abs().sum(dim=(0, 1, 2)) + 1e-30
             assert bool(((rep.db[c.name].double() - s).abs() <= bound).all()), c.name
+
+
+def test_replicas_share_lane_streams():
+    """The replicas of a device run their lanes on one set of streams: steps of two of them, enqueued
+    from two threads on streams of their own, give the bits of steps alone, while a captured step of a
+    third keeps to a side stream of its own."""
+    import threading
+    nets = [W.googlenet(batch=2), W.alexnet(batch=8), W.alexnet(batch=8)]
+    for net in nets:
+        net.lr = 1e-6
+    inp = [W.make_inputs(net, seed=4 + k) for k, net in enumerate(nets)]
+    alone, both = [[Replica(n, i) for n, i in zip(nets, inp)] for _ in range(2)]
+    for rep in alone + both:
+        rep.use_streams = True
+    assert len({s.cuda_stream for rep in both for s in [rep.side, *rep.lane_streams.values()]}) == 3
+    assert both[2].capture_side.cuda_stream not in {s.cuda_stream for s in [both[0].side, *both[0].lane_streams.values()]}
+    for rep in alone:
+        for _ in range(3):
+            rep.step()
+        torch.cuda.synchronize()
+    both[2].step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        both[2].step()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+
+    def run(k):
+        with torch.cuda.stream(streams[k]):
+            for _ in range(3):
+                both[k].step()
+
+    threads = [threading.Thread(target=run, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for _ in range(2):
+        graph.replay()
+    torch.cuda.synchronize()
+    for a, b in zip(alone, both):
+        assert bool(torch.isfinite(b.params).all())
+        assert bitwise_equal(a.grads, b.grads), a.net.name
+        assert bitwise_equal(a.params, b.params), a.net.name
