@@ -423,19 +423,18 @@ class Replica:
                     and self.argmax[nxt.name].dtype == torch.uint8):
                 self.conv_pool[op.name] = nxt
         self.pool_in_conv = {p.name for p in self.conv_pool.values()}
-        # ---- one workspace big enough for every op
+        # ---- one workspace big enough for every call of a step, its filter gradients too: a step on
+        # one stream runs them in it (and a recorded program names it for as long as it is run)
         need = 0
+        for c in list(net.convs) + [g["op"] for g in self.merges]:
+            fused = c.name in self.bwi_relu or c.name in self.relu_last
+            for op_kind in (0, 1, 2, 3) if fused else (0, 1, 2):
+                need = max(need, ops.conv2d_workspace_bytes(op_kind, self.act[c.src], c.cout, c.kh, c.kw,
+                                                            (c.sh, c.sw), c.pads))
         for c in net.convs:
-            x = self.act[c.src]
-            for op_kind in (0, 1, 2, 3) if c.name in self.bwi_relu else (0, 1, 2):
-                need = max(need, ops.conv2d_workspace_bytes(op_kind, x, c.cout, c.kh, c.kw, (c.sh, c.sw), c.pads))
             need = max(need, ops.bias_relu_bwd_workspace_bytes(self._slice(self.act, c)))
         for c0, width, run in {id(g[2]): g for g in self.relu_groups.values()}.values():
             need = max(need, ops.bias_relu_bwd_workspace_bytes(self.act[run[0].dst][..., c0:c0 + width]))
-        for g in self.merges:
-            m = g["op"]
-            for op_kind in (0, 1):
-                need = max(need, ops.conv2d_workspace_bytes(op_kind, self.act[m.src], m.cout, 1, 1, (1, 1), m.pads))
         self.ws = torch.zeros(max(16, (need + 15) // 16 * 16), dtype=torch.uint8, device=dev)
         # ---- filter gradients run on a second stream, with a workspace of their own
         need = 0

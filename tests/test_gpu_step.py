@@ -24,6 +24,7 @@ from oracle import net as onet
 from paper_1605_08695_amd import workloads as W
 from paper_1605_08695_amd.step import Replica
 from tests.gpu_parity import ParityTracer, SampledParityTracer, err, f64, say, ulp_diff_f32
+from tests.test_step_workspace import two_branches
 
 pytestmark = pytest.mark.gpu
 
@@ -390,6 +391,29 @@ def test_program_replays_match_eager(make, opt):
         for a, b in zip(eager.slots, prog_rep.slots):
             assert bitwise_equal(a, b), r
         _ = torch.ones(1024, device="cuda").sum().item()      # unrelated eager work between replays
+    prog.close()
+
+
+@pytest.mark.parametrize("k", [1, 3])
+def test_program_writes_only_the_steps_own_memory(k):
+    """A one-stream step whose merged filter gradient has the largest workspace, recorded and issued
+    again with the memory that was free after the recording filled: the fills stay as they are and every
+    replay equals the eager step."""
+    net = two_branches(k)
+    inp = W.make_inputs(net, seed=5)
+    eager, rep = Replica(net, inp), Replica(net, inp)
+    assert not rep.use_streams
+    eager.step()
+    prog = rep.record_step()
+    torch.cuda.synchronize()
+    fills = [torch.full((rep.ws.numel() >> k,), 7, dtype=torch.uint8, device="cuda") for k in range(8) for _ in range(4)]
+    for r in range(3):
+        eager.step()
+        rep.run_program(prog)
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(rep.params).all()), r
+        assert bitwise_equal(eager.grads, rep.grads) and bitwise_equal(eager.params, rep.params), r
+        assert all(bool((f == 7).all()) for f in fills), r
     prog.close()
 
 
