@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import threading
 from typing import NamedTuple, Optional, Sequence, Tuple
 
 import torch
@@ -115,14 +116,23 @@ def abi_version() -> int:
     return load().tfk_abi_version()
 
 
+_recording = threading.local()     # .program: the Program recording on this thread
+
+
 def _empty(stream, *args, **kw) -> torch.Tensor:
     """torch.empty on the stream the op is enqueued on: the caching allocator then hands the
     memory, once freed, only to later work on that same stream (a temporary freed on return
-    cannot be reused by another stream while the kernel still runs)."""
+    cannot be reused by another stream while the kernel still runs).  A program that is recording
+    keeps it: its runs use the same memory."""
     if stream is None:
-        return torch.empty(*args, **kw)
-    with torch.cuda.stream(stream):
-        return torch.empty(*args, **kw)
+        t = torch.empty(*args, **kw)
+    else:
+        with torch.cuda.stream(stream):
+            t = torch.empty(*args, **kw)
+    prog = getattr(_recording, "program", None)
+    if prog is not None:
+        prog.kept.append(t)
+    return t
 
 
 def _empty_like(stream, t: torch.Tensor) -> torch.Tensor:
@@ -590,13 +600,15 @@ class Program:
 
     ``with prog.recording(): ...`` runs the calls made inside the block as usual and records
     each one that succeeds (same pointers, shapes, scalars and streams); ``run()`` enqueues them
-    again in order.  Buffers the calls name must stay allocated while the program is used."""
+    again in order.  Buffers the caller gave them must stay allocated while the program is used;
+    results and workspaces that the calls made themselves are kept with it."""
 
     def __init__(self):
         self._lib = load()
         h = ctypes.c_void_p()
         check(self._lib.tfk_program_create(ctypes.byref(h)))
         self._h = h
+        self.kept = []
 
     def recording(self):
         prog = self
@@ -604,9 +616,12 @@ class Program:
         class _Rec:
             def __enter__(self):
                 check(prog._lib.tfk_program_begin(prog._h))
+                prog.kept = []
+                _recording.program = prog
                 return prog
 
             def __exit__(self, *exc):
+                _recording.program = None
                 check(prog._lib.tfk_program_end(prog._h))
                 return False
 
@@ -622,6 +637,7 @@ class Program:
         if self._h is not None and self._h.value:
             self._lib.tfk_program_destroy(self._h)
         self._h = None
+        self.kept = []
 
     def __del__(self):
         try:

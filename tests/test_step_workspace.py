@@ -5,6 +5,9 @@ own; from a recorded program that memory would be written again after it was fre
 The replica is built on the CPU over the library's own workspace queries; every other library call is
 replaced by one that does nothing.
 """
+import gc
+import weakref
+
 import pytest
 import torch
 
@@ -74,3 +77,42 @@ def test_no_call_of_a_step_needs_a_temporary(cpu_replica, name, make):
                 rep.step()
         rep.step(trace=lambda event, op, stream=None, **kw: None)
         rep.step(concurrent=False)
+
+
+def test_recorded_program_keeps_what_its_calls_allocate(monkeypatch):
+    """Workspaces and results that recorded calls made themselves live as long as their program, whose
+    runs write them again; unrecorded ones are freed on return."""
+    made, empty = [], torch.empty
+
+    def tracked(*args, **kw):
+        t = empty(*args, **kw)
+        made.append(weakref.ref(t))
+        return t
+    monkeypatch.setattr(ops, "load", _Lib)
+    monkeypatch.setattr(ops, "_stream", lambda stream: 0)
+    x, dy, w = torch.zeros(32, 28, 28, 64), torch.zeros(32, 28, 28, 64), torch.zeros(1, 1, 64, 64)
+    monkeypatch.setattr(torch, "empty", tracked)
+
+    def calls():
+        ops.conv2d_bwd_filter(x, dy, (1, 1), 1, (0, 0, 0, 0))
+        ops.conv2d_bwd_input_relu_bwd(dy, w, x, torch.zeros_like(x), 1, (0, 0, 0, 0))
+        gc.collect()
+        return [r() is not None for r in made]
+    assert len(calls()) == 4 and not any(calls())
+    made.clear()
+    prog = ops.Program()
+    with prog.recording():
+        alive = calls()
+    assert len(alive) == 4 and all(alive)
+    with pytest.raises(ZeroDivisionError), ops.Program().recording():
+        1 / 0
+    assert all(r() is not None for r in made)
+    first = list(made)
+    with prog.recording():                  # recorded anew: the earlier calls are gone, and their memory
+        calls()
+    assert not any(r() is not None for r in first)
+    prog.close()
+    gc.collect()
+    assert not any(r() is not None for r in made)
+    made.clear()
+    assert not any(calls())
