@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import operator
 import threading
 from typing import NamedTuple, Optional, Sequence, Tuple
 
@@ -84,23 +85,32 @@ def window(kh, kw, stride, pads) -> Window:
     return Window(kh, kw, sh, sw, pt, pb, pl, pr)
 
 
-_windowed = functools.lru_cache(_KEPT)(window)
+def _win_key(kh, kw, stride, pads) -> Tuple[int, ...]:
+    """The values of window(...) as plain integers, so that equal keys are equal windows: 1.0 and True
+    equal 1, and an integer tensor or array has no hash of its value."""
+    sh, sw = (stride, stride) if isinstance(stride, int) else stride
+    pt, pb, pl, pr = pads
+    return tuple(map(operator.index, (kh, kw, sh, sw, pt, pb, pl, pr)))
+
+
+@functools.lru_cache(_KEPT)
+def _win_of(key) -> Window:
+    return Window(*key)
 
 
 def _win(kh, kw, stride, pads) -> Window:
     """window(...), shared between calls with the same values (read only)."""
-    return _windowed(kh, kw, stride if isinstance(stride, int) else tuple(stride), tuple(pads))
+    return _win_of(_win_key(kh, kw, stride, pads))
 
 
 @functools.lru_cache(_KEPT)
-def _conv_need(op, shape, strides, cout, kh, kw, stride, pads, dt) -> int:
-    return load().tfk_conv2d_workspace_bytes(op, _describe(shape, strides), cout, window(kh, kw, stride, pads), dt)
+def _conv_need(op, shape, strides, cout, key, dt) -> int:
+    return load().tfk_conv2d_workspace_bytes(op, _describe(shape, strides), cout, Window(*key), dt)
 
 
-def _conv_ws_need(op, x, cout, kh, kw, stride, pads, dt) -> int:
+def _conv_ws_need(op, x, cout, key, dt) -> int:
     """The workspace query of a convolution over x (a forward input's view), by its values."""
-    return _conv_need(op, x.shape, x.stride(), cout, kh, kw, stride if isinstance(stride, int) else tuple(stride),
-                      tuple(pads), dt)
+    return _conv_need(op, x.shape, x.stride(), cout, key, dt)
 
 
 @functools.lru_cache(_KEPT)
@@ -147,14 +157,15 @@ def _ws(nbytes: int, device, stream=None) -> Optional[torch.Tensor]:
 
 # ----------------------------------------------------------------------------- convolution
 def conv2d_workspace_bytes(op: int, x: torch.Tensor, cout: int, kh, kw, stride, pads) -> int:
-    return _conv_ws_need(op, x, cout, kh, kw, stride, pads, _dt(x))
+    return _conv_ws_need(operator.index(op), x, operator.index(cout), _win_key(kh, kw, stride, pads), _dt(x))
 
 
 def _conv_fwd(x, w, bias, stride, pads, y, ws, stream):
     lib = load()
     kh, kw, cin, cout = w.shape
-    win = _win(kh, kw, stride, pads)
-    need = _conv_ws_need(0, x, cout, kh, kw, stride, pads, _dt(x))
+    key = _win_key(kh, kw, stride, pads)
+    win = _win_of(key)
+    need = _conv_ws_need(0, x, cout, key, _dt(x))
     if need and (ws is None or ws.numel() < need):
         ws = _ws(need, x.device, stream)
     if y is None:
@@ -191,8 +202,9 @@ def conv2d_fwd_bias_relu_maxpool(x, w, bias, stride, pads, pool_hw, pool_stride,
     where the convolution's row bands hold whole pool windows.  Returns (y, py, taps)."""
     lib = load()
     kh, kw, cin, cout = w.shape
-    win = _win(kh, kw, stride, pads)
-    need = _conv_ws_need(0, x, cout, kh, kw, stride, pads, _dt(x))
+    key = _win_key(kh, kw, stride, pads)
+    win = _win_of(key)
+    need = _conv_ws_need(0, x, cout, key, _dt(x))
     if need and (ws is None or ws.numel() < need):
         ws = _ws(need, x.device, stream)
     n, h, ww, _ = x.shape
@@ -226,8 +238,9 @@ def conv2d_bwd_input(dy, w, dx, stride, pads, beta=0.0, ws=None, stream=None):
     kh, kw, cin, cout = w.shape
     if not (w.dtype == dy.dtype == dx.dtype):
         raise TypeError("dy, w and dx must share one dtype")
-    win = _win(kh, kw, stride, pads)
-    need = _conv_ws_need(1, dx, cout, kh, kw, stride, pads, _dt(dx))
+    key = _win_key(kh, kw, stride, pads)
+    win = _win_of(key)
+    need = _conv_ws_need(1, dx, cout, key, _dt(dx))
     if need and (ws is None or ws.numel() < need):
         ws = _ws(need, dx.device, stream)
     check(lib.tfk_conv2d_bwd_input(_ptr(dy), _view(dy), _ptr(w), win, _dt(dy), _ptr(dx), _view(dx), float(beta),
@@ -249,8 +262,9 @@ def conv2d_bwd_input_relu_bwd(dy, w, y, dpre, stride, pads, dbias=None, ws=None,
     if d_y is not d_p and ((d_y.n, d_y.h, d_y.w, d_y.c, d_y.pixel_stride) !=
                            (d_p.n, d_p.h, d_p.w, d_p.c, d_p.pixel_stride)):
         raise ValueError("y and dpre must share one view (extents and pixel stride)")
-    win = _win(kh, kw, stride, pads)
-    need = _conv_ws_need(3, dpre, cout, kh, kw, stride, pads, _dt(y))
+    key = _win_key(kh, kw, stride, pads)
+    win = _win_of(key)
+    need = _conv_ws_need(3, dpre, cout, key, _dt(y))
     if defer:
         _need_ws(ws, need)
         dbias = None
@@ -273,8 +287,9 @@ def conv2d_bwd_filter(x, dy, kernel_hw, stride, pads, dw=None, ws=None, stream=N
         dw = _empty(stream, (kh, kw, x.shape[3], cout), dtype=torch.float32, device=x.device)
     if dy.dtype != x.dtype or dw.dtype != torch.float32:
         raise TypeError("x and dy share one dtype; dw is float32")
-    win = _win(kh, kw, stride, pads)
-    need = _conv_ws_need(2, x, cout, kh, kw, stride, pads, _dt(x))
+    key = _win_key(kh, kw, stride, pads)
+    win = _win_of(key)
+    need = _conv_ws_need(2, x, cout, key, _dt(x))
     if ws is None or ws.numel() < need:
         ws = _ws(need, x.device, stream)
     check(lib.tfk_conv2d_bwd_filter(_ptr(x), _view(x), _ptr(dy), _view(dy), win, _dt(x), _ptr(dw), _ptr(ws),

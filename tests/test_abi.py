@@ -479,3 +479,28 @@ def test_channel_slices_alias(lib):
     st = lib.tfk_conv2d_bwd_input(vp(P + 24), yd, vp(P + 0x100000), W, BF16, vp(P), xd, ctypes.c_float(0.0),
                                   None, 0, None)
     assert st == ALIAS
+
+
+def test_window_arguments_are_taken_by_value(lib):
+    """Calls that share descriptors between equal arguments take and refuse what ``window`` does: floats
+    are refused although 1.0 == 1, and integers of any kind and one-shot iterables are read once."""
+    import numpy as np
+    fields = lambda w: tuple(getattr(w, k) for k, _ in w._fields_)
+    x = torch.zeros(2, 8, 8, 16)
+    for stride, pads in [(1, (1, 1, 1, 1)), ((2, 1), [1, 0, 1, 0]), (torch.tensor([1, 1]), torch.tensor([1, 1, 1, 1])),
+                         ((np.int64(1), 1), np.array([1, 1, 1, 1])), (1, (np.array(1), 1, 1, torch.tensor(1)))]:
+        want = fields(ops.window(3, 3, stride, pads))
+        for _ in range(2):
+            assert fields(ops._win(3, 3, stride, pads)) == want
+            assert (ops.conv2d_workspace_bytes(2, x, 32, 3, 3, stride, pads) ==
+                    lib.tfk_conv2d_workspace_bytes(2, Nhwc(2, 8, 8, 16, 16), 32, Window(*want), 0))
+    assert ops.conv2d_workspace_bytes(2, x, 32, 3, 3, iter((1, 1)), iter((1, 1, 1, 1))) == \
+        ops.conv2d_workspace_bytes(2, x, 32, 3, 3, 1, (1, 1, 1, 1))
+    for bad in [(3.0, 3, 1, (1, 1, 1, 1)), (3, 3, (1.0, 1), (1, 1, 1, 1)), (3, 3, 1, (np.float64(1), 1, 1, 1))]:
+        for f in (ops.window, ops._win, lambda *a: ops.conv2d_workspace_bytes(2, x, 32, *a)):
+            with pytest.raises(TypeError):
+                f(*bad)
+    t = torch.tensor([1, 1, 1, 1])
+    assert fields(ops._win(3, 3, 1, t))[4:] == (1, 1, 1, 1)
+    t[0] = 0
+    assert fields(ops._win(3, 3, 1, t))[4:] == (0, 1, 1, 1)
