@@ -783,6 +783,8 @@ void launch_bwf(int ng, dim3 grid, const BandArgs &a, hipStream_t st) {
 
 }  // namespace
 
+size_t conv_band_x_bytes(const ConvShape &s) { return ((size_t)s.N * s.H * s.W * 8 + 255) & ~(size_t)255; }
+
 bool conv_band_fwd_applies(const ConvShape &s) {
     BandArgs a;
     return plan(s, false, a);

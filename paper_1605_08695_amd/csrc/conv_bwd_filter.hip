@@ -84,9 +84,6 @@ size_t plan_ws(const ConvShape &s, const BwfPlan &p) {
     return (size_t)p.splits * (size_t)s.KH * s.KW * s.C * s.K * sizeof(float);
 }
 
-// Workspace bytes ahead of the band kernel's partials: room for a 4-channel copy of x.
-size_t band_x_bytes(const ConvShape &s) { return ((size_t)s.N * s.H * s.W * 8 + 255) & ~(size_t)255; }
-
 }  // namespace
 
 void conv_bwd_filter_plan(int dt, const ConvShape &s, int *splits, int *k_split) {
@@ -100,12 +97,12 @@ size_t conv_bwd_filter_ws_bytes(int dt, const ConvShape &s) {
     if (dt == 1) need = std::max(need, plan_ws(s, bwf_plan(dt, s, true)));
     if (conv_fold_applies(dt, s)) need = std::max(need, conv_fold_ws_bytes(2, s));
     if (dt == 1 && conv_band_bwf_applies(s, true))
-        need = std::max(need, band_x_bytes(s) + conv_band_bwf_partial_bytes(s, true));
+        need = std::max(need, conv_band_x_bytes(s) + conv_band_bwf_partial_bytes(s, true));
     return need;
 }
 
 size_t conv_band_bwf_want_bytes(int dt, const ConvShape &s) {
-    return dt == 1 && conv_band_bwf_applies(s, false) ? band_x_bytes(s) + conv_band_bwf_partial_bytes(s, false) : 0;
+    return dt == 1 && conv_band_bwf_applies(s, false) ? conv_band_x_bytes(s) + conv_band_bwf_partial_bytes(s, false) : 0;
 }
 
 template <typename T>
@@ -162,7 +159,7 @@ hipError_t launch_conv_bwd_filter(int dt, const void *x, int64_t xs, const void 
         const bf16_t *x4 = rgbx_input(x, npix, s.C, xs, reinterpret_cast<bf16_t *>(at), st);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        float *part = reinterpret_cast<float *>(at + band_x_bytes(s));
+        float *part = reinterpret_cast<float *>(at + conv_band_x_bytes(s));
         return launch_conv_bwd_filter_band(x4, dy, dys, dw, s, part, base, st);
     }
     if (conv_fold_applies(dt, s) && dys % 8 == 0 && ((uintptr_t)dy & 15) == 0 && ((uintptr_t)ws & 15) == 0)

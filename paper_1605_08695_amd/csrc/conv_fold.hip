@@ -179,8 +179,10 @@ const bf16_t *padded_input(const void *x, int64_t npix, int C, int64_t xs, int C
 
 }  // namespace
 
+bool rgbx_in_place(const void *x, int64_t xs) { return xs == 4 && ((uintptr_t)x & 7) == 0; }
+
 const bf16_t *rgbx_input(const void *x, int64_t npix, int C, int64_t xs, bf16_t *xp, hipStream_t st) {
-    if (xs == 4 && ((uintptr_t)x & 7) == 0) return reinterpret_cast<const bf16_t *>(x);
+    if (rgbx_in_place(x, xs)) return reinterpret_cast<const bf16_t *>(x);
     pad_channels(x, npix, C, xs, 4, xp, st);
     return xp;
 }

@@ -172,8 +172,10 @@ bool conv_fwd_pool_fused(const void *x, int64_t xs, const void *w, void *y, int6
 
 hipError_t launch_conv_fwd(int dt, const void *x, int64_t xs, const void *w, void *y, int64_t ys,
                            const ConvShape &s, const float *bias, void *ws, size_t ws_bytes, hipStream_t st) {
-    if (dt == 1 && ws != nullptr && conv_band_fwd_applies(s) && aligned16p(w) && ((uintptr_t)y & 7) == 0 &&
-        ys % 4 == 0) {
+    // (with one or two channels the fold's copy of x, which a call must be given room for, can be narrower than
+    // the band kernel's: a call given no more runs the fold)
+    if (dt == 1 && ws != nullptr && conv_band_fwd_applies(s) && (rgbx_in_place(x, xs) || ws_bytes >= conv_band_x_bytes(s)) &&
+        aligned16p(w) && ((uintptr_t)y & 7) == 0 && ys % 4 == 0) {
         const bf16_t *x4 = rgbx_input(x, (int64_t)s.N * s.H * s.W, s.C, xs, reinterpret_cast<bf16_t *>(ws), st);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -117,6 +117,9 @@ hipError_t launch_conv_bwd_filter_folded(const void *x, int64_t xs, const void *
 // First layers with at most 4 input channels as band kernels (conv_band.hip): the input is read
 // as 4-channel pixels (an RGBx view in place, or a padded copy made by rgbx_input in xp).
 const uint16_t *rgbx_input(const void *x, int64_t npix, int C, int64_t xs, uint16_t *xp, hipStream_t st);
+bool rgbx_in_place(const void *x, int64_t xs);
+// Bytes of that copy (the filter gradient's partials follow it).
+size_t conv_band_x_bytes(const ConvShape &s);
 bool conv_band_fwd_applies(const ConvShape &s);
 bool conv_band_bwf_applies(const ConvShape &s, bool base);
 size_t conv_band_bwf_partial_bytes(const ConvShape &s, bool base);

@@ -504,3 +504,14 @@ def test_window_arguments_are_taken_by_value(lib):
     assert fields(ops._win(3, 3, 1, t))[4:] == (1, 1, 1, 1)
     t[0] = 0
     assert fields(ops._win(3, 3, 1, t))[4:] == (0, 1, 1, 1)
+
+
+def test_first_layer_workspace_holds_the_padded_input(lib):
+    """The forward query of first layers that the band kernels take covers their 4-channel copy of x, also
+    where one or two channels fold into fewer than 4 per pixel (strides, pads and widths in multiples of
+    4 or 8)."""
+    for n, h, w, c, k, kk, s, pad in [(19, 108, 20, 2, 64, 5, 4, 0), (2, 64, 64, 1, 16, 8, 8, 0), (3, 32, 40, 1, 32, 5, 4, 0),
+                                      (3, 32, 40, 2, 32, 3, 2, 0), (3, 32, 40, 3, 32, 3, 2, 0), (3, 31, 31, 1, 32, 7, 4, 0),
+                                      (4, 48, 48, 1, 16, 5, 4, 4)]:
+        got = lib.tfk_conv2d_workspace_bytes(0, Nhwc(n, h, w, c, 0), k, Window(kk, kk, s, s, pad, pad, pad, pad), BF16)
+        assert got >= n * h * w * 8, (n, h, w, c)

@@ -223,3 +223,30 @@ def test_first_layer_paths(case, rgbx):
     torch.cuda.synchronize()
     assert_close(f64(dw), oracle.conv2d_bwd_filter(f64(x), f64(dy), (k, k), (s, s), pads), torch.float32, torch.bfloat16,
                  label="filter gradient")
+
+
+# one or two channels whose fold (strides, pads and width divisible by 4 or 8) is narrower than 4 channels
+@pytest.mark.parametrize("N,H,W,C,K,k,s,pads", [(19, 108, 20, 2, 64, 5, 4, (0, 0, 0, 0)), (2, 64, 64, 1, 16, 8, 8, (0, 0, 0, 0)),
+                                                (3, 33, 40, 1, 32, 5, 4, (4, 1, 4, 0))])
+def test_first_layer_narrow_fold(N, H, W, C, K, k, s, pads):
+    """The queried workspace (the band kernel) and the least that is accepted (the fold: its copy of x and
+    its filter): both give the oracle's outputs and leave what follows the workspace alone."""
+    say("first layer, narrow fold", N, H, W, C, K, k, s)
+    lib = load()
+    rng = np.random.default_rng(C)
+    x, w = _mk((N, H, W, C), torch.bfloat16, rng), _mk((k, k, C, K), torch.bfloat16, rng, 0.2)
+    ref = oracle.conv2d_fwd(f64(x), f64(w), (s, s), pads)
+    F = max(f for f in (1, 2, 4, 8) if 8 // f >= C and s % f == 0 and pads[2] % f == 0 and W % f == 0)
+    up = lambda b: -(-b // 256) * 256
+    least = up(N * H * W * (8 // F) * 2) + up(k * -(-k // F) * 8 * K * 2)
+    queried = ops.conv2d_workspace_bytes(0, x, K, k, k, s, pads)
+    assert 8 // F < 4 and queried > least
+    for nbytes in (queried, least):
+        ws = torch.full((nbytes + 4096,), 0x5a, dtype=torch.uint8, device=DEV)
+        y = torch.empty(ref.shape, dtype=torch.bfloat16, device=DEV)
+        rc = lib.tfk_conv2d_fwd(ops._ptr(x), ops.nhwc(x), ops._ptr(w), K, ops.window(k, k, s, pads), 1, ops._ptr(y), ops.nhwc(y),
+                                ops._ptr(ws), nbytes, ops._stream(None))
+        assert rc == 0
+        torch.cuda.synchronize()
+        assert_close(f64(y), ref, torch.bfloat16, label="%d bytes" % nbytes)
+        assert bool((ws[nbytes:] == 0x5a).all())
