@@ -133,9 +133,6 @@ static hipError_t conv_bwd_filter_t(const void *x, int64_t xs, const void *dy, i
     if (v2) {
         a.out = p.splits > 1 ? ws : (void *)dw;
         a.k_split = p.k_split;
-        // (each XCD runs a contiguous range of a split's tiles: they read the same pixel range of
-        // x and dy, from one L2; AlexNet conv2-5: 232 -> 228 us)
-        a.xcd_order = 1;
         const bool done = sizeof(T) == 4 ? igemm2_launch_f32<DIR_BWD_FILTER>(a, m, p.splits, p.t, st)
                                          : igemm2_launch<DIR_BWD_FILTER>(a, m, p.splits, p.t, st);
         e = done ? hipGetLastError() : hipErrorInvalidValue;

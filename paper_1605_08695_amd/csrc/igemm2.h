@@ -206,11 +206,18 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // (the launcher may keep the hardware order)
+    // (A whole launch renumbered: in a filter gradient an XCD's tiles of a split read the same pixel
+    // range of x and dy, from one L2; AlexNet conv2-5: 232 -> 228 us.  By phase: see igemm2_by_phase.)
     const int lin_hw = (int)(blockIdx.x + gridDim.x * blockIdx.z);
-    const int lin = a.xcd_order ? xcd_order(lin_hw, (int)(gridDim.x * gridDim.z)) : lin_hw;
-    const int bx = lin % (int)gridDim.x;
-    const int bz = lin / (int)gridDim.x;
+    int bx, bz;
+    if (DIR == DIR_BWD_DATA && a.by_phase) {
+        bx = xcd_order((int)blockIdx.x, (int)gridDim.x);
+        bz = (int)blockIdx.z;
+    } else {
+        const int lin = xcd_order(lin_hw, (int)(gridDim.x * gridDim.z));
+        bx = lin % (int)gridDim.x;
+        bz = lin / (int)gridDim.x;
+    }
     const int ti = bx % a.tiles_i;
     const int tj = bx / a.tiles_i;
     const int i0 = ti * BI;

@@ -124,6 +124,22 @@ static inline Igemm2Tile igemm2_tiles_f32(int ni, int mj, int zdim) {
     return {32, r32 / 32 * bj < 256 ? 32 : 64, 4, 3};
 }
 
+// Whether the blocks of each stride phase of an input gradient are dealt to all XCDs.  Renumbered as a
+// whole, an XCD runs blocks of one or two phases, and the phases' work is unequal: of a 1 x 1 filter's
+// four at stride 2 one has the tap and three none, of a 3 x 3 filter's they have 4, 2, 2 and 1.  By phase
+// every XCD has a part of each, but reads every phase's filter rows, which pays unless they outgrow its
+// 4 MiB of L2 over only a round of blocks (strided input gradients at stride 2, by phase against whole:
+// over 512 blocks 0.5-0.9 of the time, up to 1.04 with 7 x 7 filters over 16 MiB; 128-512 blocks 0.77-0.97
+// with smaller filters, 0.97-1.1 with larger; below 128 blocks, or 256 where the phases differ by less
+// than half (5 x 5, 7 x 7), 0.97-1.2: there each block has a CU to itself either way).
+static inline int igemm2_by_phase(const IgArgs &a, int64_t blocks, int es) {
+    const int most = ((a.KH + a.sh - 1) / a.sh) * ((a.KW + a.sw - 1) / a.sw) * a.sh * a.sw;
+    if (a.k_split > 0 || most == a.KH * a.KW) return 0;       // (one phase, or equal ones)
+    const int64_t filter = (int64_t)a.KH * a.KW * a.C * a.K * es;
+    const int least = 2 * most >= 3 * a.KH * a.KW ? 128 : 256;
+    return blocks > 512 || (blocks >= least && filter < (4 << 20)) ? 1 : 0;
+}
+
 template <typename T, int DIR, int BI, int BJ, int NW, int NS>
 static void igemm2_go(const IgArgs &a, dim3 grid, hipStream_t st) {
     hipLaunchKernelGGL((igemm2_kernel<T, DIR, BI, BJ, NW, NS>), grid, dim3(NW * 64), 0, st, a);
@@ -134,6 +150,7 @@ static bool igemm2_launch_f32(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, 
     a.tiles_i = (a.NI + t.bi - 1) / t.bi;
     const dim3 grid((unsigned)(a.tiles_i * ((mj + t.bj - 1) / t.bj)), 1, (unsigned)zdim);
     if (t.nw != 4 || t.ns != 3) return false;
+    if (DIR == DIR_BWD_DATA) a.by_phase = igemm2_by_phase(a, (int64_t)grid.x * grid.z, 4);
     if (t.bi == 64 && t.bj == 64) { igemm2_go<float, DIR, 64, 64, 4, 3>(a, grid, st); return true; }
     if (t.bi == 32 && t.bj == 64) { igemm2_go<float, DIR, 32, 64, 4, 3>(a, grid, st); return true; }
     if (t.bi == 32 && t.bj == 32) { igemm2_go<float, DIR, 32, 32, 4, 3>(a, grid, st); return true; }
@@ -149,6 +166,7 @@ static bool igemm2_launch(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipS
     const int tiles_j = (mj + t.bj - 1) / t.bj;
     const dim3 grid((unsigned)(a.tiles_i * tiles_j), 1, (unsigned)zdim);
     if (t.nw != 4) return false;
+    if (DIR == DIR_BWD_DATA) a.by_phase = igemm2_by_phase(a, (int64_t)grid.x * grid.z, 2);
     const int key = t.bi * 10000 + t.bj * 10 + t.ns;
     switch (key) {
     case 321282: igemm2_go<bf16_t, DIR, 32, 128, 4, 2>(a, grid, st); return true;
@@ -185,6 +203,7 @@ template <typename T, int DIR>
 static hipError_t igemm2_launch_rag(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipStream_t st) {
     a.tiles_i = (a.NI + t.bi - 1) / t.bi;
     const dim3 grid((unsigned)(a.tiles_i * ((mj + t.bj - 1) / t.bj)), 1, (unsigned)zdim), block(256);
+    if (DIR == DIR_BWD_DATA) a.by_phase = igemm2_by_phase(a, (int64_t)grid.x * grid.z, sizeof(T));
     if (t.bi == 64 && t.bj == 64)
         hipLaunchKernelGGL((igemm2_kernel<T, DIR, 64, 64, 4, 3, true>), grid, block, 0, st, a);
     else if constexpr (sizeof(T) == 2) {
@@ -253,9 +272,9 @@ static inline void fill_geom(IgArgs &a, const ConvShape &s) {
     a.dK.init((uint32_t)s.K);
     a.beta = 0.f;
     a.bias = nullptr;
-    a.xcd_order = 1;
     a.ni_store = 0;
     a.k_split = 0;
+    a.by_phase = 0;
     a.split_stride = 0;
     a.bytes_i = a.bytes_j = 0;
     a.relu_y = nullptr;

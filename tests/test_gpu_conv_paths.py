@@ -96,6 +96,24 @@ def test_conv_bf16_paths(case):
     _check_all(name, torch.bfloat16, N, H, W, C, K, KH, KW, s, pads, wide)
 
 
+# stride phases renumbered by themselves: with no taps in three of four, with 4, 2, 2 and 1, and 9, 6, 6
+# and 4, over block counts that are not multiples of the 8 XCDs, aligned and padded channels
+PHASE_CASES = [
+    ("phases_1x1_s2", torch.bfloat16, 20, 61, 61, 136, 64, 1, 1, 2, (0, 0, 0, 0), 8),
+    ("phases_3x3_s2", torch.bfloat16, 9, 45, 46, 72, 40, 3, 3, 2, (1, 0, 1, 0), 0),
+    ("phases_5x5_s2", torch.bfloat16, 24, 57, 57, 64, 8, 5, 5, 2, (2, 2, 2, 2), 0),
+    ("phases_1x3_s3", torch.bfloat16, 7, 40, 50, 96, 32, 1, 3, 3, (0, 0, 1, 1), 0),
+    ("phases_f32_3x3_s2", torch.float32, 6, 41, 41, 36, 20, 3, 3, 2, (1, 1, 1, 1), 0),
+    ("phases_pad_c37_s2", torch.bfloat16, 9, 45, 46, 37, 72, 3, 3, 2, (1, 1, 1, 1), 3),
+]
+
+
+@pytest.mark.parametrize("case", PHASE_CASES, ids=[c[0] for c in PHASE_CASES])
+def test_conv_stride_phases(case):
+    name, dtype, N, H, W, C, K, KH, KW, s, pads, wide = case
+    _check_all(name, dtype, N, H, W, C, K, KH, KW, s, pads, wide)
+
+
 # channel counts that are not multiples of a 16-byte chunk: padded copies in the workspace and the
 # element-wise epilogue (one or both counts odd, strided phases, channel slices at odd offsets, 64-
 # and 128-channel tiles)
