@@ -717,19 +717,64 @@ void set_bands(BandArgs &a, const ConvShape &s, int R, int slots) {
     set_runs(a, slots);
 }
 
-// Fewer rows per band where the highest bands would leave workgroup slots without one.
-int spread_rows(const ConvShape &s, int R, int slots) {
-    return (int)std::min<int64_t>(R, std::max<int64_t>(1, ((int64_t)s.N * s.OH + slots - 1) / slots));
-}
-
 // The small-filter forward form (half the LDS, two workgroups per CU).
 bool fwd_small(const ConvShape &s, const BandArgs &a) {
     return a.nks <= kMaxKStepsSmall && band_rows(s, a.wst, 0, kXBandSmall) >= 1;
 }
 
-// base: the plan of the filter gradient's required workspace (at least four tap groups, bands as high as
-// the LDS allows, staged columns from -pl).
-bool plan(const ConvShape &s, bool bwf, BandArgs &a, bool base = false) {
+// 16-byte band copies need pixel pairs that never straddle the image edge.
+bool pairs_aligned(const BandArgs &a) { return a.pl0 % 2 == 0 && a.W % 2 == 0; }
+
+constexpr int kBwfWaves = 8;
+
+// Time (us) of a plan beyond what every plan of the shape takes: the bands of the busiest workgroup -- their
+// reduction steps, the copies of their input and a constant -- and, for the filter gradient, the partials
+// that are written and read again.  Fitted to 7000 timings each of random first layers (3 x 3 to 11 x 11, stride 1
+// to 4, 16 to 128 channels; 5-95 % of them within 0.84-1.12 of the fit).
+double band_cost(const BandArgs &a, bool bwf, bool small) {
+    const int kb = (a.K + 63) / 64, pixels = a.R * a.OW, npix = a.rows_in * a.wst;
+    const int copies = ((pairs_aligned(a) ? (npix + 1) / 2 : 2 * npix) + 63) / 64;
+    const int places = (small ? 2 : 1) * kCUs, rounds = (band_grid(a) * kb + places - 1) / places;
+    if (bwf) {
+        const int groups = (a.KH * (a.kwp / 4) + kBwfWaves - 1) / kBwfWaves;
+        const double band = (pixels + 31) / 32 * (0.17 + 0.056 * groups) + 0.47 + 0.015 * copies;
+        return rounds * a.run * band + 0.62e-6 * band_grid(a) * ((double)a.KH * a.KW * a.C * a.K * 4);
+    }
+    const int gy = small ? 2 : 4, passes = ((pixels + 15) / 16 + 4 * gy - 1) / (4 * gy);
+    const double band = passes * (a.nks * (small ? 0.10 : 0.22) + 1.38) + (small ? 0.28 : 0.66) + 0.03 * copies;
+    return rounds * (a.run * band + 0.18 * a.nks);
+}
+
+// Bands of the plan of least cost: as even as they get for each number of bands per image from the
+// fewest that the LDS allows (R rows), over one round of workgroups, or, for the filter gradient, fewer
+// workgroups with longer runs and so fewer partials.  (One band per workgroup place, whatever it took, made
+// 13 x 32 x 16 x 4, 11 x 11, stride 2, filter gradient 12.0 -> 21.2 us; two 64-channel blocks in two rounds,
+// 89 x 11 x 11 x 3 -> 128, 11 x 11, forward 12.9 -> 35.9.)
+void choose_bands(BandArgs &a, const ConvShape &s, bool bwf, bool small, int R, int slots) {
+    BandArgs best = a;
+    double least = -1.0;
+    while (R >= 1) {
+        const int per_img = (s.OH + R - 1) / R, even = (s.OH + per_img - 1) / per_img;
+        if ((int64_t)s.N * per_img > (1 << 30)) break;
+        for (int m = 1; m <= (bwf ? 4 : 1); ++m) {
+            set_bands(a, s, even, slots);
+            a.run *= m;
+            // (filter gradient: the highest bands unless others gain more than the fit's error on short launches)
+            const double c = bwf && least >= 0.0 ? 1.03 * band_cost(a, bwf, small) + 0.25 : band_cost(a, bwf, small);
+            if (least < 0.0 || c < least) {
+                least = c;
+                best = a;
+            }
+        }
+        R = std::min(even - 1, (s.OH + per_img) / (per_img + 1));
+    }
+    a = best;
+}
+
+// What does not depend on the bands; *R: the highest band that the LDS allows.  base: the plan of the
+// filter gradient's required workspace (at least four tap groups, bands as high as the LDS allows, staged
+// columns from -pl).
+bool plan_shape(const ConvShape &s, bool bwf, BandArgs &a, bool base, int *R, bool *small) {
     if (s.C > 4 || s.K % 16 != 0) return false;
     const int kwp = bwf ? (s.KW + 3) / 4 * 4 : (s.KW + 1) / 2 * 2;
     // An even pl0 lets 16-byte copies fill the staged rows (the image's pixel pairs start on even
@@ -739,7 +784,11 @@ bool plan(const ConvShape &s, bool bwf, BandArgs &a, bool base = false) {
     int wst = (s.OW - 1) * s.sw + kwp + (a.pl0 - s.pl);
     wst += wst & 1;
     if (bwf) {
-        if (s.KH * (kwp / 4) > kBwfGroups || s.KH * (kwp / 4) < (base ? 4 : 2)) return false;
+        // Two or three tap groups (3 x 3) keep as many of the eight waves busy: up to 64 reduction steps per CU
+        // (over random images 0.75-0.95 of the fold's time; beyond, 37.9 -> 47.2 us for 119 x 91 x 39 x 3 -> 128).
+        const int groups = s.KH * (kwp / 4);
+        if (groups > kBwfGroups || groups < (base ? 4 : 2)) return false;
+        if (groups < 4 && (int64_t)s.N * s.OH * s.OW / 32 * ((s.K + 63) / 64) >= 64 * kCUs) return false;
     } else {
         const int nks = ((s.KH * kwp * 4 + 63) / 64) * 2;     // even: the loop runs two steps at a time
         if (nks > kMaxKSteps) return false;
@@ -748,25 +797,25 @@ bool plan(const ConvShape &s, bool bwf, BandArgs &a, bool base = false) {
     fill_band_args(a, s);
     a.kwp = kwp;
     a.wst = wst;
-    const bool small = !bwf && fwd_small(s, a);
-    const int slots = small ? 2 * kCUs : kCUs;
-    int R = band_rows(s, wst, bwf ? kDyBandPix : 0, small ? kXBandSmall : kXBand);
-    if (R < 1) return false;
-    if (!base) R = spread_rows(s, R, slots);
-    if ((int64_t)s.N * ((s.OH + R - 1) / R) > (1 << 30)) return false;
-    set_bands(a, s, R, slots);
-    a.dWst.init((uint32_t)wst);
+    *small = !bwf && fwd_small(s, a);
+    *R = band_rows(s, wst, bwf ? kDyBandPix : 0, *small ? kXBandSmall : kXBand);
+    return *R >= 1 && (int64_t)s.N * ((s.OH + *R - 1) / *R) <= (1 << 30);
+}
+
+bool plan(const ConvShape &s, bool bwf, BandArgs &a, bool base = false) {
+    int R;
+    bool small;
+    if (!plan_shape(s, bwf, a, base, &R, &small)) return false;
+    // (64-channel blocks of one band run side by side)
+    if (base) set_bands(a, s, R, kCUs);
+    else choose_bands(a, s, bwf, small, R, std::max(1, (small ? 2 : 1) * kCUs / ((s.K + 63) / 64)));
+    a.dWst.init((uint32_t)a.wst);
     a.dOW.init((uint32_t)s.OW);
-    a.dKwp.init((uint32_t)kwp);
+    a.dKwp.init((uint32_t)a.kwp);
     return true;
 }
 
 int bwf_splits(const BandArgs &a) { return band_grid(a); }
-
-// 16-byte band copies need pixel pairs that never straddle the image edge.
-bool pairs_aligned(const BandArgs &a) { return a.pl0 % 2 == 0 && a.W % 2 == 0; }
-
-constexpr int kBwfWaves = 8;
 
 template <bool X16>
 void launch_bwf(int ng, dim3 grid, const BandArgs &a, hipStream_t st) {
@@ -787,13 +836,17 @@ size_t conv_band_x_bytes(const ConvShape &s) { return ((size_t)s.N * s.H * s.W *
 
 bool conv_band_fwd_applies(const ConvShape &s) {
     BandArgs a;
-    return plan(s, false, a);
+    int R;
+    bool small;
+    return plan_shape(s, false, a, false, &R, &small);
 }
 
 // base: within the workspace that a call must be given (see plan).
 bool conv_band_bwf_applies(const ConvShape &s, bool base) {
     BandArgs a;
-    return plan(s, true, a, base);
+    int R;
+    bool small;
+    return plan_shape(s, true, a, base, &R, &small);
 }
 
 size_t conv_band_bwf_partial_bytes(const ConvShape &s, bool base) {

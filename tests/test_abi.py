@@ -506,6 +506,13 @@ def test_window_arguments_are_taken_by_value(lib):
     assert fields(ops._win(3, 3, 1, t))[4:] == (0, 1, 1, 1)
 
 
+def test_first_layer_filter_gradient_takes_one_round_of_workgroups(lib):
+    """Two 64-channel blocks share the 256 CUs: at most 128 workgroups' partials each (28 images of 11 x 11
+    x 4 into 128 channels, 7 x 7, were cut into 140 bands, 280 workgroups)."""
+    got = lib.tfk_conv2d_workspace_bytes(2, Nhwc(28, 11, 11, 4, 0), 128, Window(7, 7, 1, 1, 0, 0, 0, 0), BF16)
+    assert got <= 28 * 11 * 11 * 8 + 256 + 128 * (7 * 7 * 4 * 128 * 4)
+
+
 def test_first_layer_workspace_holds_the_padded_input(lib):
     """The forward query of first layers that the band kernels take covers their 4-channel copy of x, also
     where one or two channels fold into fewer than 4 per pixel (strides, pads and widths in multiples of

@@ -217,6 +217,13 @@ FIRST_CASES = [
     ("first_one_row", 1, 3, 250, 4, 64, 3, 1, (0, 0, 1, 1)),
     ("first_wide", 1, 6, 520, 3, 16, 3, 1, (1, 1, 1, 1)),
     ("first_many_bands", 90, 24, 24, 1, 16, 3, 1, (1, 1, 1, 1)),
+    # two channel blocks, bands of less than the LDS allows; more bands than workgroups; longer runs than that
+    ("first_two_blocks", 5, 33, 35, 3, 112, 11, 1, (5, 5, 5, 5)),
+    ("first_runs", 70, 21, 30, 4, 32, 5, 1, (2, 2, 2, 2)),
+    ("first_few_groups", 80, 15, 15, 4, 128, 7, 2, (3, 3, 3, 3)),
+    # 3 x 3 filter gradients on either side of 64 reduction steps per CU
+    ("first_3x3_steps_below", 20, 118, 110, 3, 80, 3, 1, (1, 1, 1, 1)),
+    ("first_3x3_steps_above", 20, 120, 110, 3, 80, 3, 1, (1, 1, 1, 1)),
 ]
 
 
