@@ -102,7 +102,10 @@ __global__ __launch_bounds__(256) void bias_relu_fwd_kernel(T *__restrict__ y, i
 // chunks cv = t % CVB (+ CVB, ...) and pixel rows t / CVB (+ R, ...).  It writes
 // dpre and keeps fp32 per-channel sums; the block then reduces its R row groups
 // in LDS in a fixed order and writes partial[c][b].
-template <typename T, bool VEC>
+// SUM: without a ReLU, in place: the gradient passes through as it is and is only summed (2560 x 1664 bf16
+// logits' gradient: with the second pass 12.6 -> 11.7 us; a test of the pointers in the one kernel kept the
+// other forms' loads from being batched, 119 of 397 random fp32 calls of odd channel counts 1.06-1.3 of the time).
+template <typename T, bool VEC, bool SUM>
 __global__ __launch_bounds__(256) void relu_bwd_partial_kernel(const T *__restrict__ y, const T *dy,
                                                                T *dpre, int64_t P, int C, int64_t ys,
                                                                int64_t ppb, float *__restrict__ partial) {
@@ -117,9 +120,6 @@ __global__ __launch_bounds__(256) void relu_bwd_partial_kernel(const T *__restri
     const int64_t p0 = (int64_t)blockIdx.x * ppb;
     const int64_t p1 = min(P, p0 + ppb);
     const bool active = row < R;
-    // (without a ReLU, in place: the gradient passes through as it is and is only summed;
-    // 2560 x 1664 bf16 logits' gradient: with the sum 12.6 -> 11.7 us)
-    const bool store = y != nullptr || dpre != dy;
     for (int cv = lane_cv; cv < CV; cv += CVB) {
         float s[EPC];
 #pragma unroll
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void relu_bwd_partial_kernel(const T *__restri
                         const int64_t pp = p + (int64_t)u * R;
                         if (pp < p1) {
                             const int64_t off = pp * ys + (int64_t)cv * EPC;
-                            if (y != nullptr) ly[u] = *reinterpret_cast<const U4 *>(y + off);
+                            if (!SUM && y != nullptr) ly[u] = *reinterpret_cast<const U4 *>(y + off);
                             ld[u] = *reinterpret_cast<const U4 *>(dy + off);
                         }
                     }
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void relu_bwd_partial_kernel(const T *__restri
                         if (pp >= p1) break;
                         const int64_t off = pp * ys + (int64_t)cv * EPC;
                         float fy[EPC], fd[EPC];
-                        if (y != nullptr) {
+                        if (!SUM && y != nullptr) {
                             chunk_to_f32<T>(ly[u], fy);
                         } else {
 #pragma unroll
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void relu_bwd_partial_kernel(const T *__restri
                             fd[e] = fy[e] > 0.f ? fd[e] : 0.f;
                             s[e] += fd[e];
                         }
-                        if (store) *reinterpret_cast<U4 *>(dpre + off) = f32_to_chunk<T>(fd);
+                        if (!SUM) *reinterpret_cast<U4 *>(dpre + off) = f32_to_chunk<T>(fd);
                     }
                 }
             }
@@ -167,10 +167,10 @@ __global__ __launch_bounds__(256) void relu_bwd_partial_kernel(const T *__restri
                 const int64_t off = p * ys + (int64_t)cv * EPC;
                 if constexpr (VEC) {
                 } else {
-                    const float fy = y != nullptr ? Elem<T>::load(y + off) : 1.f;
+                    const float fy = !SUM && y != nullptr ? Elem<T>::load(y + off) : 1.f;
                     const float fd = fy > 0.f ? Elem<T>::load(dy + off) : 0.f;
                     s[0] += fd;
-                    if (store) Elem<T>::store(dpre + off, fd);
+                    if (!SUM) Elem<T>::store(dpre + off, fd);
                 }
             }
             // The stored dpre equals the value summed here: with bf16 storage the
@@ -1536,12 +1536,14 @@ static hipError_t relu_bwd_t(const void *y, const void *dy, void *dpre, int64_t 
     const int CVB = CV < 256 ? CV : 256;
     const int R = 256 / CVB;
     const size_t smem = R == 1 ? 0 : (size_t)R * C * sizeof(float);
-    if (vec)
-        hipLaunchKernelGGL((relu_bwd_partial_kernel<T, true>), dim3(G), dim3(256), smem, st,
+    auto go = [&](auto V_, auto S_) {
+        hipLaunchKernelGGL((relu_bwd_partial_kernel<T, decltype(V_)::value, decltype(S_)::value>), dim3(G), dim3(256), smem, st,
                            (const T *)y, (const T *)dy, (T *)dpre, P, C, ys, ppb, ws);
-    else
-        hipLaunchKernelGGL((relu_bwd_partial_kernel<T, false>), dim3(G), dim3(256), smem, st,
-                           (const T *)y, (const T *)dy, (T *)dpre, P, C, ys, ppb, ws);
+    };
+    using BT = std::true_type;
+    using BF = std::false_type;
+    if (y == nullptr && dpre == dy) vec ? go(BT{}, BT{}) : go(BF{}, BT{});
+    else vec ? go(BT{}, BF{}) : go(BF{}, BF{});
     return finish_partials(ws, G, C, db, st, defer);
 }
 
