@@ -49,6 +49,8 @@ struct IgArgs {
     void *out;           // FWD: y          BWD_DATA: dx         BWD_FILTER: fp32 dw / partials
     float beta;          // BWD_DATA: 0 overwrite, 1 accumulate
     const float *bias;   // FWD: when set, y = max(conv + bias[co], +0) (bias + ReLU fused)
+    int xcd_order;       // pipelined kernel: 1 = give each XCD a contiguous range of logical blocks, 2 = of
+                         // each stride phase's
     // forward-convolution geometry
     int N, H, W, C;      // input extents
     int OH, OW, K;       // output extents, K = output channels
@@ -60,7 +62,6 @@ struct IgArgs {
     int ni_store;        // pipelined kernel, element-wise epilogue: channels that exist in the output
     int tiles_i;         // number of I tiles (blockIdx.x = tj * tiles_i + ti)
     int k_split;         // BWD_FILTER: reduction elements per split (multiple of the K tile)
-    int by_phase;        // pipelined BWD_DATA: renumber the blocks of each stride phase by themselves
     int64_t split_stride;// BWD_FILTER: floats between consecutive partial outputs
     FastDiv dC, dKW, dOW, dOH, dK;
     uint32_t bytes_i, bytes_j;   // pipelined kernel: byte spans of src_i / src_j (each < 2^31)

@@ -150,7 +150,7 @@ static bool igemm2_launch_f32(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, 
     a.tiles_i = (a.NI + t.bi - 1) / t.bi;
     const dim3 grid((unsigned)(a.tiles_i * ((mj + t.bj - 1) / t.bj)), 1, (unsigned)zdim);
     if (t.nw != 4 || t.ns != 3) return false;
-    if (DIR == DIR_BWD_DATA) a.by_phase = igemm2_by_phase(a, (int64_t)grid.x * grid.z, 4);
+    if (DIR == DIR_BWD_DATA) a.xcd_order = 1 + igemm2_by_phase(a, (int64_t)grid.x * grid.z, 4);
     if (t.bi == 64 && t.bj == 64) { igemm2_go<float, DIR, 64, 64, 4, 3>(a, grid, st); return true; }
     if (t.bi == 32 && t.bj == 64) { igemm2_go<float, DIR, 32, 64, 4, 3>(a, grid, st); return true; }
     if (t.bi == 32 && t.bj == 32) { igemm2_go<float, DIR, 32, 32, 4, 3>(a, grid, st); return true; }
@@ -166,7 +166,7 @@ static bool igemm2_launch(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipS
     const int tiles_j = (mj + t.bj - 1) / t.bj;
     const dim3 grid((unsigned)(a.tiles_i * tiles_j), 1, (unsigned)zdim);
     if (t.nw != 4) return false;
-    if (DIR == DIR_BWD_DATA) a.by_phase = igemm2_by_phase(a, (int64_t)grid.x * grid.z, 2);
+    if (DIR == DIR_BWD_DATA) a.xcd_order = 1 + igemm2_by_phase(a, (int64_t)grid.x * grid.z, 2);
     const int key = t.bi * 10000 + t.bj * 10 + t.ns;
     switch (key) {
     case 321282: igemm2_go<bf16_t, DIR, 32, 128, 4, 2>(a, grid, st); return true;
@@ -203,7 +203,7 @@ template <typename T, int DIR>
 static hipError_t igemm2_launch_rag(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipStream_t st) {
     a.tiles_i = (a.NI + t.bi - 1) / t.bi;
     const dim3 grid((unsigned)(a.tiles_i * ((mj + t.bj - 1) / t.bj)), 1, (unsigned)zdim), block(256);
-    if (DIR == DIR_BWD_DATA) a.by_phase = igemm2_by_phase(a, (int64_t)grid.x * grid.z, sizeof(T));
+    if (DIR == DIR_BWD_DATA) a.xcd_order = 1 + igemm2_by_phase(a, (int64_t)grid.x * grid.z, sizeof(T));
     if (t.bi == 64 && t.bj == 64)
         hipLaunchKernelGGL((igemm2_kernel<T, DIR, 64, 64, 4, 3, true>), grid, block, 0, st, a);
     else if constexpr (sizeof(T) == 2) {
@@ -272,9 +272,9 @@ static inline void fill_geom(IgArgs &a, const ConvShape &s) {
     a.dK.init((uint32_t)s.K);
     a.beta = 0.f;
     a.bias = nullptr;
+    a.xcd_order = 1;
     a.ni_store = 0;
     a.k_split = 0;
-    a.by_phase = 0;
     a.split_stride = 0;
     a.bytes_i = a.bytes_j = 0;
     a.relu_y = nullptr;
