@@ -31,13 +31,18 @@ BwfPlan bwf_plan(int dt, const ConvShape &s, bool v2) {
     // output channels a multiple of 64 but not of 128 (AlexNet conv2's 192): 64-channel tiles leave
     // none empty (128-channel ones would compute a quarter of the rows for nothing), and three of
     // their 48 KiB blocks fit a CU, so the splits fill one round of three (conv2: 95 -> 90 us)
-    // Small products (up to 10 GFLOP in at most 256 128 x 128 tiles): 64 x 64 tiles with three LDS stages; their splits reduce to
-    // fewer, shorter partials and their blocks overlap better (14 x 14 x 512 -> 128, 1 x 1, batch 128:
-    // 17.0 -> 14.3 us; 28 x 28 x 192 -> 176, batch 128: 28.2 -> 21.5; 8 x 28 x 28 x 192 -> 96: 13.2 -> 9.4; at
-    // 11.3 GFLOP, 14 x 14 x 112 -> 224, 3 x 3, batch 128: 28.7 against 31.0)
-    // (with more tiles there is no split and the output's bytes bound it: 9216 -> 4096 over 128
-    // rows 54 us with 64 x 64 tiles, 43 with 128 x 128)
-    const bool small = v2 && s.K > 32 && (int64_t)((s.K + 127) / 128) * ((m + 127) / 128) <= 256 && 2.0 * m * s.K * ((double)s.N * s.OH * s.OW) <= 1e10;
+    // Small products (up to 8 GFLOP over whole 64-channel tiles, 10 in 64 and more 128 x 128 tiles, of at most
+    // 256): 64 x 64 tiles with three LDS stages; their splits reduce to fewer, shorter partials and their blocks overlap better
+    // (14 x 14 x 512 -> 128, 1 x 1, batch 128: 17.0 -> 14.3 us; 28 x 28 x 192 -> 176, batch 128: 28.2 -> 21.5; over
+    // random shapes up to 4 GFLOP 0.72-0.89 of the time, 4-8 0.75-0.92, 8-10 in fewer tiles 1.04, at most 1.45:
+    // 7 x 95 x 95 x 112 -> 72, 3 x 3, 24.7 -> 35.8)
+    // (with more tiles, or 128 over a few hundred pixels, there is no split and the output's bytes bound it:
+    // 9216 -> 4096 over 128 rows 54 us with 64 x 64 tiles, 43 with 128 x 128; 126 x 7 x 3 x 800 -> 480, 3 x 3, 15.3
+    // against 12.4; over fewer pixels the launch is short either way: 112 x 6 x 6 x 232 -> 160, 6 x 6, 4.6 against 6.3)
+    const int64_t tiles128 = (int64_t)((s.K + 127) / 128) * ((m + 127) / 128);
+    const double pixels = (double)s.N * s.OH * s.OW, flops = 2.0 * m * ((s.K + 63) / 64 * 64) * pixels;
+    const bool small = v2 && s.K > 32 && tiles128 <= 256 && flops <= (tiles128 >= 64 ? 1e10 : 8e9) &&
+                       (tiles128 < 128 || flops >= 1e9 || pixels < 256);
     const bool by64 = v2 && !small && s.K > 64 && s.K % 128 != 0 && s.K % 64 == 0;
     if (v2) {
         p.t = small ? Igemm2Tile{64, 64, 4, 3}
