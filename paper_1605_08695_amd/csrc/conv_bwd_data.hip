@@ -9,15 +9,15 @@ namespace tfk {
 // 74.8 -> 71.3 us back to back, but the sustained two-stream step slower, 0.694 -> 0.705 ms, where
 // the filter gradient of the other stream shares the GPU with it; GoogLeNet and Inception-v3
 // steps are the same either way.)
-static Igemm2Tile bwd_data_tiles(int dt, int ni, int mj, int zdim) {
-    return dt == 0 ? igemm2_tiles_f32(ni, mj, zdim) : igemm2_tiles_narrow(ni, mj, zdim);
+static Igemm2Tile bwd_data_tiles(int dt, const ConvShape &s, int mj, int zdim) {
+    return dt == 0 ? igemm2_tiles_f32(s.C, mj, zdim) : igemm2_tiles_narrow(s.C, mj, zdim, (int64_t)s.KH * s.KW * s.K);
 }
 
 // Tiles of the kernel fused with the ReLU backward, whose partial sums of the bias gradient (a row
 // per block and wave column) go to the workspace: the rule's, where the workspace holds their
 // rows (`all`), else without the tiles of fewer than 96 pixels (twice as many rows as 64 x 128).
-static Igemm2Tile relu_tiles(int dt, int ni, int mj, int zdim, bool all) {
-    Igemm2Tile t = bwd_data_tiles(dt, ni, mj, zdim);
+static Igemm2Tile relu_tiles(int dt, const ConvShape &s, int mj, int zdim, bool all) {
+    Igemm2Tile t = bwd_data_tiles(dt, s, mj, zdim);
     if (dt == 1 && !all && t.bj < 96) t = Igemm2Tile{64, 128, 4, 2};
     return t;
 }
@@ -27,7 +27,7 @@ static Igemm2Tile relu_tiles(int dt, int ni, int mj, int zdim, bool all) {
 static int relu_partial_rows(int dt, const ConvShape &s, bool all) {
     const int mj = s.N * ((s.H + s.sh - 1) / s.sh) * ((s.W + s.sw - 1) / s.sw);
     const int z = s.sh * s.sw;
-    const Igemm2Tile t = relu_tiles(dt, s.C, mj, z, all);
+    const Igemm2Tile t = relu_tiles(dt, s, mj, z, all);
     return z * ((mj + t.bj - 1) / t.bj) * (t.nw / 2);
 }
 
@@ -83,7 +83,7 @@ static hipError_t conv_bwd_data_t(const void *dy, int64_t dys, const void *w, vo
                 a.k_split = ks;
                 a.split_stride = (int64_t)mj * a.NI;
                 a.out = ws;
-                if (!igemm2_launch<DIR_BWD_DATA>(a, mj, sp, igemm2_tiles_split(a.NI, mj, sp), st))
+                if (!igemm2_launch<DIR_BWD_DATA>(a, mj, sp, igemm2_tiles_split(a.NI, mj, sp, (int64_t)s.KH * s.KW * s.K), st))
                     return hipErrorInvalidValue;
                 const hipError_t e = hipGetLastError();
                 if (e != hipSuccess) return e;
@@ -111,7 +111,7 @@ static hipError_t conv_bwd_data_t(const void *dy, int64_t dys, const void *w, vo
                 *db_parts = a.db_rows;
                 *db_at = ws;
             }
-            const Igemm2Tile t = relu_y != nullptr ? relu_tiles(1, a.NI, mj, z, all) : bwd_data_tiles(1, a.NI, mj, z);
+            const Igemm2Tile t = relu_y != nullptr ? relu_tiles(1, s, mj, z, all) : bwd_data_tiles(1, s, mj, z);
             if (!igemm2_launch<DIR_BWD_DATA>(a, mj, z, t, st)) return hipErrorInvalidValue;
             return hipGetLastError();
         }
@@ -127,7 +127,7 @@ static hipError_t conv_bwd_data_t(const void *dy, int64_t dys, const void *w, vo
                 *db_parts = a.db_rows;
                 *db_at = ws;
             }
-            if (!igemm2_launch_f32<DIR_BWD_DATA>(a, mj, s.sh * s.sw, bwd_data_tiles(0, a.NI, mj, s.sh * s.sw), st))
+            if (!igemm2_launch_f32<DIR_BWD_DATA>(a, mj, s.sh * s.sw, bwd_data_tiles(0, s, mj, s.sh * s.sw), st))
                 return hipErrorInvalidValue;
             return hipGetLastError();
         }

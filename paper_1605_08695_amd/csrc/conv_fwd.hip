@@ -43,7 +43,8 @@ static hipError_t conv_fwd_t(const void *x, int64_t xs, const void *w, void *y, 
                 a.k_split = ks;
                 a.split_stride = (int64_t)mj * a.NI;
                 a.out = ws;
-                if (!igemm2_launch<DIR_FWD>(a, mj, sp, igemm2_tiles_split(a.NI, mj, sp), st)) return hipErrorInvalidValue;
+                if (!igemm2_launch<DIR_FWD>(a, mj, sp, igemm2_tiles_split(a.NI, mj, sp, (int64_t)s.KH * s.KW * s.C), st))
+                    return hipErrorInvalidValue;
                 const hipError_t e = hipGetLastError();
                 if (e != hipSuccess) return e;
                 SplitEpi ep{};
@@ -57,7 +58,8 @@ static hipError_t conv_fwd_t(const void *x, int64_t xs, const void *w, void *y, 
                 ep.bias = bias;
                 return launch_split_epilogue(ep, st);
             }
-            if (!igemm2_launch<DIR_FWD>(a, mj, 1, igemm2_tiles_narrow(a.NI, mj, 1), st)) return hipErrorInvalidValue;
+            if (!igemm2_launch<DIR_FWD>(a, mj, 1, igemm2_tiles_narrow(a.NI, mj, 1, (int64_t)s.KH * s.KW * s.C), st))
+                return hipErrorInvalidValue;
             return hipGetLastError();
         }
     }
@@ -134,7 +136,7 @@ bool conv_fwd_pool_fused(const void *x, int64_t xs, const void *w, void *y, int6
     // fused with 64-channel tiles, 322 and 292 us with 128-channel tiles)
     {
         const int mj_plain = s.N * s.OH * s.OW;
-        Igemm2Tile pt = igemm2_tiles_narrow(s.K, mj_plain, 1);
+        Igemm2Tile pt = igemm2_tiles_narrow(s.K, mj_plain, 1, (int64_t)s.KH * s.KW * s.C);
         if (pt.bj < 96) pt.bj = 128;         // (64 x 64 tiles: counted as the 64 x 128 ones they halve)
         const int64_t blocks = (int64_t)((s.K + pt.bi - 1) / pt.bi) * ((mj_plain + pt.bj - 1) / pt.bj);
         if (blocks > 2 * kFusedPoolCUs) return false;

@@ -116,7 +116,9 @@ size_t filter_bytes_padded(int dt, const ConvShape &p) {
 // Input-gradient grid: largest stride phase and tile.
 int phase_rows(const ConvShape &s) { return s.N * ((s.H + s.sh - 1) / s.sh) * ((s.W + s.sw - 1) / s.sw); }
 Igemm2Tile bwd_tiles(int dt, const ConvShape &p) {
-    return dt == 0 ? rag_tiles<float>(p.C, phase_rows(p), p.sh * p.sw) : rag_tiles<bf16_t>(p.C, phase_rows(p), p.sh * p.sw);
+    const int64_t kred = (int64_t)p.KH * p.KW * p.K;
+    return dt == 0 ? rag_tiles<float>(p.C, phase_rows(p), p.sh * p.sw, kred)
+                   : rag_tiles<bf16_t>(p.C, phase_rows(p), p.sh * p.sw, kred);
 }
 int relu_rows(int dt, const ConvShape &p) {
     const Igemm2Tile t = bwd_tiles(dt, p);
@@ -174,7 +176,7 @@ static bool fwd_pad_t(int dt, const void *x, int64_t xs, const void *w, void *y,
     a.ni_store = s.K;
     a.bias = bias;
     const int mj = s.N * s.OH * s.OW;
-    *err = igemm2_launch_rag<T, DIR_FWD>(a, mj, 1, rag_tiles<T>(a.NI, mj, 1), st);
+    *err = igemm2_launch_rag<T, DIR_FWD>(a, mj, 1, rag_tiles<T>(a.NI, mj, 1, (int64_t)p.KH * p.KW * p.C), st);
     return true;
 }
 

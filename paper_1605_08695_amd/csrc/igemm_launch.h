@@ -63,11 +63,13 @@ static inline double round_cost(int64_t blocks) {
 //    242 us (6.1 rounds), 160 210 (4.9), 192 223 (4.1); 28 x 28 x 512, batch 64: 238, 210 and 230; input
 //    gradient 256, 224, 248; 35 x 35 x 256 -> 384, batch 37: 94, 78, 85 and (input gradient) 95, 106, 76.
 //  * multiples of 192 likewise (AlexNet conv2 forward: 76 -> 64 us);
-//  * otherwise 64-channel tiles: 64 x 128, or 64 x 64 with three LDS stages up to 320 blocks, where
-//    64 x 128 leaves most CUs with one block whose barriers and copies nothing overlaps (17 x 17,
-//    160 -> 192, 1 x 7, batch 32: forward 12.9 -> 12.0 us, 28 x 28 x 192 -> 96, 1 x 1, batch 8: 6.7 -> 5.7; at
-//    614 blocks, 35 x 35 x 64 -> 96, 3 x 3, batch 32: 12.6 against 14.8, the other way).
-static inline Igemm2Tile igemm2_tiles(int ni, int mj, int zdim) {
+//  * otherwise 64-channel tiles: 64 x 128, or 64 x 64 with three LDS stages up to 256 blocks, where
+//    64 x 128 leaves every CU with one block whose barriers and copies nothing overlaps (17 x 17,
+//    160 -> 192, 1 x 7, batch 32: forward 12.9 -> 12.0 us, 28 x 28 x 192 -> 96, 1 x 1, batch 8: 6.7 -> 5.7; over
+//    random shapes 0.78-0.96 of the time), or 320 with reductions (per split or stride phase) below 1024
+//    (0.91-0.97; from 1024 on 0.8-1.3: 40 x 21 x 21 x 80 <- 120, 7 x 7, 52.0 -> 68.1).
+// kred: reduction elements of the whole product.
+static inline Igemm2Tile igemm2_tiles(int ni, int mj, int zdim, int64_t kred) {
     const int64_t blocks_j = (int64_t)((mj + 127) / 128) * zdim;
     if (ni % 128 == 0 && (ni / 128) * blocks_j >= 256) {
         // 128-row tiles that leave most CUs with one block (AlexNet conv4/conv5: 338 blocks)
@@ -98,15 +100,15 @@ static inline Igemm2Tile igemm2_tiles(int ni, int mj, int zdim) {
         if (zdim == 1 && fill(b96) > fill(b128) + 0.05) return {192, 96, 4, 2};
         return {192, 128, 4, 2};
     }
-    if ((int64_t)((ni + 63) / 64) * blocks_j <= 320) return {64, 64, 4, 3};
+    if ((int64_t)((ni + 63) / 64) * blocks_j <= (kred < 1024 * zdim ? 320 : 256)) return {64, 64, 4, 3};
     return {64, 128, 4, 2};
 }
 
 // At most 32 output rows (channels) on the I side: 32-row tiles, which keep every MFMA row in use
 // (a 64-row tile would compute half or more of its rows for nothing).
-static inline Igemm2Tile igemm2_tiles_narrow(int ni, int mj, int zdim) {
+static inline Igemm2Tile igemm2_tiles_narrow(int ni, int mj, int zdim, int64_t kred) {
     if (ni <= 32) return {32, 128, 4, 2};
-    return igemm2_tiles(ni, mj, zdim);
+    return igemm2_tiles(ni, mj, zdim, kred);
 }
 
 // fp32 tiles.  The fp32 matrix rate is a sixteenth of bf16's, so small tiles already keep the
@@ -190,11 +192,11 @@ static bool igemm2_launch(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipS
 
 // The kernel with the element-wise epilogue (RAG): the rule's tiles, of those compiled for it.
 template <typename T>
-static inline Igemm2Tile rag_tiles(int ni, int mj, int zdim) {
+static inline Igemm2Tile rag_tiles(int ni, int mj, int zdim, int64_t kred) {
     if constexpr (sizeof(T) == 4) {
         return Igemm2Tile{64, 64, 4, 3};
     } else {
-        const Igemm2Tile t = igemm2_tiles(ni, mj, zdim);
+        const Igemm2Tile t = igemm2_tiles(ni, mj, zdim, kred);
         return t.bi == 64 ? t : Igemm2Tile{128, 128, 4, 2};
     }
 }
@@ -238,10 +240,10 @@ static inline int gemm_split_plan(int ni, int mj, int64_t kred, int *k_split) {
 }
 
 // Tiles of a split reduction: one 128 x 128 block per CU where the split gives about that many.
-static inline Igemm2Tile igemm2_tiles_split(int ni, int mj, int sp) {
+static inline Igemm2Tile igemm2_tiles_split(int ni, int mj, int sp, int64_t kred) {
     const int64_t blocks = (int64_t)((ni + 127) / 128) * ((mj + 127) / 128) * sp;
     if (ni % 128 == 0 && blocks >= 192 && blocks <= 256) return {128, 128, 4, 3};
-    return igemm2_tiles_narrow(ni, mj, sp);
+    return igemm2_tiles_narrow(ni, mj, sp, kred);
 }
 
 // Bytes from the first element of a pixel-major operand (es bytes per element) to the end of its
