@@ -275,3 +275,45 @@ def test_first_layer_narrow_fold(N, H, W, C, K, k, s, pads):
         torch.cuda.synchronize()
         assert_close(f64(y), ref, torch.bfloat16, label="%d bytes" % nbytes)
         assert bool((ws[nbytes:] == 0x5a).all())
+
+
+def _kernels_of(call):
+    """Kernel launches of one call, from a stream capture of it."""
+    lib = load()
+    for name in ("hipStreamBeginCapture", "hipStreamEndCapture", "hipGraphGetNodes", "hipGraphDestroy"):
+        getattr(lib, name).restype = ctypes.c_int
+    s = torch.cuda.Stream()
+    call(s)                                  # (outside the capture once: code objects load)
+    torch.cuda.synchronize()
+    st, graph, n = ctypes.c_void_p(s.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t(0)
+    assert lib.hipStreamBeginCapture(st, ctypes.c_int(1)) == 0            # (thread-local mode)
+    try:
+        call(s)
+    finally:
+        assert lib.hipStreamEndCapture(st, ctypes.byref(graph)) == 0
+    assert lib.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    assert lib.hipGraphDestroy(graph) == 0
+    return n.value
+
+
+# one round of two 128-row blocks per CU with the pool in the kernel; more rounds, counted in 128-row tiles
+# whatever tile the convolution alone takes (VGG-16's conv10 + pool4 and conv7 + pool3 at small batches)
+@pytest.mark.parametrize("N,H,C,K,ps,pk,kernels", [(128, 13, 256, 256, 2, 3, 1), (12, 56, 128, 256, 2, 2, 2), (24, 28, 256, 512, 2, 2, 2),
+                                                   (20, 28, 256, 512, 2, 2, 1)])
+def test_pool_in_the_convolution_for_one_round(N, H, C, K, ps, pk, kernels):
+    rng = np.random.default_rng(2)
+    x, w = _mk((N, H, H, C), torch.bfloat16, rng), _mk((3, 3, C, K), torch.bfloat16, rng, 0.03)
+    bias = torch.zeros(K, device=DEV)
+    y = torch.empty((N, H, H, K), dtype=torch.bfloat16, device=DEV)
+    o = (H - pk) // ps + 1
+    py = torch.empty((N, o, o, K), dtype=torch.bfloat16, device=DEV)
+    taps = torch.empty((N, o, o, K), dtype=torch.uint8, device=DEV)
+    assert ops.conv2d_workspace_bytes(0, x, K, 3, 3, 1, (1, 1, 1, 1)) == 0
+
+    def call(s):
+        ops.conv2d_fwd_bias_relu_maxpool(x, w, bias, 1, (1, 1, 1, 1), (pk, pk), ps, (0, 0, 0, 0), y=y, py=py, taps=taps, stream=s)
+    assert _kernels_of(call) == kernels
+    ref_y = ops.conv2d_fwd_bias_relu(x, w, bias, 1, (1, 1, 1, 1))
+    ref_py, ref_taps = ops.maxpool_fwd(ref_y, (pk, pk), ps, (0, 0, 0, 0), taps=True)
+    torch.cuda.synchronize()
+    assert torch.equal(y, ref_y) and torch.equal(py, ref_py) and torch.equal(taps, ref_taps)
