@@ -242,7 +242,7 @@ size_t conv_need(int op, int dti, const ConvShape &s) {
 size_t conv_want(int op, int dti, const ConvShape &s) {
     const size_t band = op == 2 ? conv_band_bwf_want_bytes(dti, s)
                                 : (op == 0 && dti == 1 && conv_band_fwd_applies(s) ? conv_band_x_bytes(s) : 0);
-    return std::max(conv_pad_applies(dti, s) ? conv_pad_ws_bytes(op, dti, s) : 0, band);
+    return std::max(conv_pad_applies(op, dti, s) ? conv_pad_ws_bytes(op, dti, s) : 0, band);
 }
 
 // Bytes of the caller's workspace that a call may use: all that the query asks for (want) when it holds

@@ -117,7 +117,12 @@ static hipError_t conv_bwd_data_t(const void *dy, int64_t dys, const void *w, vo
         }
     }
     if constexpr (sizeof(T) == 4) {
-        if (vi && vj && s.C % EPC == 0 && dxs % EPC == 0 && aligned16p(dx) &&
+        // (large tensors with short reductions, per stride phase on average, are bound by their stores, which the
+        // register-staged kernel's wider tiles make in longer runs: 95 x 46 x 46 x 92 <- 12, 1 x 1, stride 2, 20.1
+        // against 32.8 us.  With the ReLU backward the fused pass pays all the same.)
+        const bool stores = relu_y == nullptr && (int64_t)s.KH * s.KW * s.K < 64 * s.sh * s.sw &&
+                            (int64_t)s.N * s.H * s.W * s.C >= (4 << 20);
+        if (!stores && vi && vj && s.C % EPC == 0 && dxs % EPC == 0 && aligned16p(dx) &&
             (relu_y == nullptr || aligned16p(relu_y)) &&
             igemm2_fits(a, (int64_t)s.KH * s.KW * s.C * s.K * 4, span_bytes((int64_t)s.N * s.OH * s.OW, dys, s.K, 4))) {
             if (relu_y != nullptr) {
@@ -149,13 +154,13 @@ size_t conv_bwd_data_relu_ws_bytes(int dt, const ConvShape &s, int64_t dxs) {
 // the query asks for room for them, and a call given less takes other tiles (fp32: the unfused pair).
 size_t conv_bwd_data_relu_ws_want(int dt, const ConvShape &s, int64_t dxs) {
     return std::max({conv_bwd_data_relu_ws_bytes(dt, s, dxs), (size_t)relu_partial_rows(dt, s, true) * s.C * sizeof(float),
-                     conv_pad_applies(dt, s) ? conv_pad_ws_bytes(3, dt, s) : 0});
+                     conv_pad_applies(3, dt, s) ? conv_pad_ws_bytes(3, dt, s) : 0});
 }
 
 hipError_t launch_conv_bwd_data_relu(int dt, const void *dy, int64_t dys, const void *w, void *dpre, int64_t dxs,
                                      const void *y, float beta, float *db, float *ws, size_t ws_bytes,
                                      const ConvShape &s, hipStream_t st, BiasPartials *defer) {
-    if (conv_pad_applies(dt, s) && ws_bytes >= conv_pad_ws_bytes(3, dt, s)) {
+    if (conv_pad_applies(3, dt, s) && ws_bytes >= conv_pad_ws_bytes(3, dt, s)) {
         hipError_t e;
         BiasPartials bp{nullptr, 0};
         if (conv_bwd_data_padded(dt, dy, dys, w, dpre, dxs, beta, s, y, ws, st, &e, &bp)) {
@@ -192,7 +197,7 @@ hipError_t launch_conv_bwd_data_relu(int dt, const void *dy, int64_t dys, const 
 
 hipError_t launch_conv_bwd_data(int dt, const void *dy, int64_t dys, const void *w, void *dx, int64_t dxs,
                                 float beta, const ConvShape &s, float *ws, size_t ws_bytes, hipStream_t st) {
-    if (conv_pad_applies(dt, s) && ws_bytes >= conv_pad_ws_bytes(1, dt, s)) {
+    if (conv_pad_applies(1, dt, s) && ws_bytes >= conv_pad_ws_bytes(1, dt, s)) {
         hipError_t e;
         if (conv_bwd_data_padded(dt, dy, dys, w, dx, dxs, beta, s, nullptr, ws, st, &e, nullptr)) return e;
     }

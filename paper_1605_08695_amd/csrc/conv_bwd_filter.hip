@@ -166,7 +166,7 @@ hipError_t launch_conv_bwd_filter(int dt, const void *x, int64_t xs, const void 
     }
     if (conv_fold_applies(dt, s) && dys % 8 == 0 && ((uintptr_t)dy & 15) == 0 && ((uintptr_t)ws & 15) == 0)
         return launch_conv_bwd_filter_folded(x, xs, dy, dys, dw, s, ws, st);
-    if (conv_pad_applies(dt, s) && !conv_fold_applies(dt, s) && ws_bytes >= conv_pad_ws_bytes(2, dt, s)) {
+    if (conv_pad_applies(2, dt, s) && !conv_fold_applies(dt, s) && ws_bytes >= conv_pad_ws_bytes(2, dt, s)) {
         hipError_t e;
         if (conv_bwd_filter_padded(dt, x, xs, dy, dys, dw, s, ws, st, &e)) return e;
     }

@@ -188,7 +188,7 @@ hipError_t launch_conv_fwd(int dt, const void *x, int64_t xs, const void *w, voi
     }
     if (ws != nullptr && conv_fold_applies(dt, s) && ((uintptr_t)y & 15) == 0 && ys % 8 == 0)
         return launch_conv_fwd_folded(x, xs, w, y, ys, s, bias, ws, st);
-    if (conv_pad_applies(dt, s) && !conv_fold_applies(dt, s) && ws_bytes >= conv_pad_ws_bytes(0, dt, s)) {
+    if (conv_pad_applies(0, dt, s) && !conv_fold_applies(dt, s) && ws_bytes >= conv_pad_ws_bytes(0, dt, s)) {
         hipError_t e;
         if (conv_fwd_padded(dt, x, xs, w, y, ys, s, bias, ws, st, &e)) return e;
     }

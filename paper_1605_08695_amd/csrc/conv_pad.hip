@@ -133,11 +133,33 @@ int relu_rows(int dt, const ConvShape &p) {
 // 108 x 29 x 29 x 1152 -> 74, 3 x 3, stride 2: 1082 -> 146.
 constexpr double kPadFlops = 1e6;
 
-bool conv_pad_applies(int dt, const ConvShape &s) {
+// The copies and the element-wise stores cost by the sizes of the tensors, the gather that they save by the
+// reduction of each output (per stride phase on average).  Random calls, padded against gathered:
+//  * forward: fp32, and bf16 that copies x alone, below 64 elements 0.9-1.15 of the time (to 1.9; under 1M outputs
+//    0.7-1), from there on 0.8 falling to 0.1; bf16 with ragged output channels gathers the filter too: 0.8 from
+//    the shortest on;
+//  * input gradient: fp32 below 64 0.95-1.4 (to 2.5), then 0.85 falling to 0.2; bf16 that copies dy below 64 0.9-1.1
+//    (to 2.2; under 1M outputs 0.4-0.9), then 0.65 falling to 0.08; bf16 whose dy is whole loses its vector
+//    stores for nothing but the filter: 1.0-1.3 below 512, then 0.8 falling;
+//  * fused with the ReLU backward it saves that pass: small tensors (4M elements) and bf16 with both counts ragged
+//    gain from the shortest on, others from 64;
+//  * filter gradient: below 32 pixels there is little to gather (0.95-2.2), then 0.9 falling to 0.3.
+static bool pad_pays(int op, int dt, const ConvShape &s) {
+    const bool ck = s.C % chunk_of(dt) != 0, kk = s.K % chunk_of(dt) != 0;
+    const int64_t taps = (int64_t)s.KH * s.KW, px = (int64_t)s.N * s.H * s.W, py = (int64_t)s.N * s.OH * s.OW;
+    if (op == 0) return (dt == 1 && kk) || taps * s.C >= 64 || py * s.K < (1 << 20);
+    if (op == 2) return py >= 32;
+    const int64_t red = taps * s.K / (s.sh * s.sw);
+    if (op == 3) return (dt == 1 && ck && kk) || red >= 64 || px * s.C < (1 << 22);
+    if (dt == 1 && !kk) return red >= 512;
+    return red >= 64 || (dt == 1 && px * s.C < (1 << 20));
+}
+
+bool conv_pad_applies(int op, int dt, const ConvShape &s) {
     const int e = chunk_of(dt);
     const ConvShape p = padded(dt, s);
     if ((s.C % e == 0 && s.K % e == 0) || s.C < e || s.KH > 31 || s.KW > 31) return false;
-    if (2.0 * s.N * s.OH * s.OW * s.KH * s.KW * (double)s.C * s.K < kPadFlops) return false;
+    if (2.0 * s.N * s.OH * s.OW * s.KH * s.KW * (double)s.C * s.K < kPadFlops || !pad_pays(op, dt, s)) return false;
     constexpr int64_t kLim = int64_t(1) << 31;
     const int64_t es = 16 / e;
     return (int64_t)s.N * s.H * s.W * p.C * es < kLim && (int64_t)s.N * s.OH * s.OW * p.K * es < kLim &&

@@ -97,7 +97,7 @@ hipError_t noalloc_scratch(void **ptr, hipStream_t stream);
 // Channel counts that are not multiples of a 16-byte chunk, on padded copies in the workspace
 // (conv_pad.hip).  The launchers return false, launching nothing, when an operand that is not copied is
 // misaligned.  op: 0 forward, 1 input gradient, 2 filter gradient, 3 input gradient with the ReLU backward.
-bool conv_pad_applies(int dt, const ConvShape &s);
+bool conv_pad_applies(int op, int dt, const ConvShape &s);
 size_t conv_pad_ws_bytes(int op, int dt, const ConvShape &s);
 bool conv_fwd_padded(int dt, const void *x, int64_t xs, const void *w, void *y, int64_t ys, const ConvShape &s,
                      const float *bias, void *ws, hipStream_t st, hipError_t *err);

@@ -522,3 +522,19 @@ def test_first_layer_workspace_holds_the_padded_input(lib):
                                       (4, 48, 48, 1, 16, 5, 4, 4)]:
         got = lib.tfk_conv2d_workspace_bytes(0, Nhwc(n, h, w, c, 0), k, Window(kk, kk, s, s, pad, pad, pad, pad), BF16)
         assert got >= n * h * w * 8, (n, h, w, c)
+
+
+@pytest.mark.parametrize("op,dt,c,k,kh,pays", [
+    (0, F32, 21, 64, 1, False), (0, F32, 21, 64, 3, True), (0, BF16, 21, 64, 1, False), (0, BF16, 21, 63, 1, True),
+    (1, F32, 42, 10, 1, False), (1, F32, 42, 10, 3, True), (1, BF16, 42, 72, 1, False), (1, BF16, 42, 72, 3, True),
+    (1, BF16, 42, 10, 1, False), (1, BF16, 42, 70, 1, True), (3, BF16, 42, 72, 1, True), (3, BF16, 48, 10, 1, False)])
+def test_padded_copies_where_the_reduction_pays(lib, op, dt, c, k, kh, pays):
+    """Over 108 x 42 x 42 pixels the query asks for padded copies of x or dy from reductions of 64 elements on
+    (512 where bf16 dy is whole), or none: then what the operation must have suffices."""
+    es, e = (4, 4) if dt == F32 else (2, 8)
+    got = lib.tfk_conv2d_workspace_bytes(op, Nhwc(108, 42, 42, c, 0), k, Window(kh, kh, 1, 1, *[kh // 2] * 4), dt)
+    copy = 108 * 42 * 42 * (-(-(c if op == 0 else k) // e) * e) * es
+    ragged = (c if op == 0 else k) % e != 0
+    assert got < copy if not pays or not ragged else got >= copy
+    if pays and not ragged:                       # (the filter alone is copied)
+        assert got >= kh * kh * c * k * es

@@ -138,6 +138,21 @@ def test_conv_padded_channels(case):
     _check_all(name, dtype, N, H, W, C, K, KH, KW, s, pads, wide)
 
 
+# short reductions over large tensors: gathered (or, fp32 with whole chunks, register-staged) instead
+SHORT_CASES = [
+    ("short_c33_k64", torch.bfloat16, 30, 33, 31, 33, 64, 1, 1, 1, (0, 0, 0, 0), 0),
+    ("short_c64_k9", torch.bfloat16, 30, 33, 31, 64, 9, 1, 1, 1, (0, 0, 0, 0), 0),
+    ("short_f32_c42_k10", torch.float32, 30, 33, 31, 42, 10, 1, 1, 1, (0, 0, 0, 0), 3),
+    ("short_f32_c100_k32_s2", torch.float32, 44, 31, 31, 100, 32, 1, 1, 2, (0, 0, 0, 0), 0),
+]
+
+
+@pytest.mark.parametrize("case", SHORT_CASES, ids=[c[0] for c in SHORT_CASES])
+def test_conv_short_reductions(case):
+    name, dtype, N, H, W, C, K, KH, KW, s, pads, wide = case
+    _check_all(name, dtype, N, H, W, C, K, KH, KW, s, pads, wide)
+
+
 def test_conv_padded_channels_least_workspace():
     """Without the workspace that the padded copies need (none is required here) the same shapes run
     on the register-staged kernel."""
