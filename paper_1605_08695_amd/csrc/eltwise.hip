@@ -510,9 +510,10 @@ __global__ __launch_bounds__(256) void maxpool_fwd_win_kernel(const T *__restric
 // 18.  A sign bit in any tap leaves the thread's outputs, and a NaN maximum its output, to
 // pool_scan_row, the float scan.  128 x 28 x 28 x 256: forward 42.0 -> 31.9 us, backward 51.3 -> 36.5
 // (strips of 2, 3, 6, 8 rows: 35.2, 33.4, 32.5, 33.1 and 38.5, 36.7, 41.6, 43.5).  Below kStripThreads
-// strips the one-output kernels keep more waves in flight (16 x 14 x 14 x 512: 5.5 against 5.7 us).
+// strips the one-output kernels keep more waves in flight (random pools of 65 to 92 thousand strips: forward
+// 1.06 of the time in strips, up to 1.19, backward 0.99; of 92 to 131 thousand 0.93 and 0.83).
 constexpr int kPoolStrip = 4;
-constexpr int64_t kStripThreads = 1 << 16;
+constexpr int64_t kStripThreads = 3 << 15;
 
 // One output row's chunk by the float scan (first maximum in kh, kw order; padded taps skipped).
 __device__ __forceinline__ void pool_scan_row(const bf16_t *__restrict__ x, const PoolGeom &g, int n, int oh, int ow, int c,

@@ -13,13 +13,14 @@ DEV = "cuda"
 
 # N, H, W, C, pads: row counts on both sides of a multiple of the strip, one row, VALID and uneven pads
 CASES = [
-    (32, 29, 31, 72, (1, 1, 1, 1)),
-    (64, 28, 28, 40, (1, 1, 1, 1)),
-    (128, 7, 9, 256, (1, 1, 1, 1)),
-    (40, 22, 35, 80, (0, 0, 0, 0)),
-    (512, 1, 20, 64, (1, 1, 1, 1)),
-    (48, 13, 33, 96, (2, 1, 0, 2)),
+    (48, 29, 31, 72, (1, 1, 1, 1)),
+    (104, 28, 28, 40, (1, 1, 1, 1)),
+    (176, 7, 9, 256, (1, 1, 1, 1)),
+    (64, 22, 35, 80, (0, 0, 0, 0)),
+    (640, 1, 20, 64, (1, 1, 1, 1)),
+    (64, 13, 33, 96, (2, 1, 0, 2)),
 ]
+STRIPS = 3 << 15                                     # fewer strips run the one-output kernels
 
 
 def _data(kind, shape, rng):
@@ -43,10 +44,15 @@ def test_pool_strips(case, kind):
     N, H, W, C, pads = case
     say("pool strips", case, kind)
     rng = np.random.default_rng(3)
-    x = torch.from_numpy(_data(kind, (N, H, W, C), rng)).to(torch.bfloat16).to(DEV)
-    y8, taps = ops.maxpool_fwd(x, (3, 3), 1, pads, taps=True)
+    # (the forward reads and writes channel slices)
+    x = torch.from_numpy(_data(kind, (N, H, W, C + 8), rng)).to(torch.bfloat16).to(DEV)[..., 8:]
+    oh, ow = H + pads[0] + pads[1] - 2, W + pads[2] + pads[3] - 2
+    assert N * -(-oh // 4) * ow * (C // 8) >= STRIPS and N * -(-H // 4) * W * (C // 8) >= STRIPS
+    yb = torch.full((N, oh, ow, C + 16), 7.0, dtype=torch.bfloat16, device=DEV)
+    y8, taps = ops.maxpool_fwd(x, (3, 3), 1, pads, y=yb[..., 8:8 + C], taps=True)
     y, am = ops.maxpool_fwd(x, (3, 3), 1, pads)
     torch.cuda.synchronize()
+    assert bool((yb[..., :8] == 7.0).all()) and bool((yb[..., 8 + C:] == 7.0).all())
     ref_y, ref_am = oracle.maxpool_fwd(f64(x), (3, 3), 1, pads)
     for got in (y8, y):
         assert np.array_equal(f64(got), ref_y, equal_nan=True)
