@@ -181,6 +181,16 @@ def _device_streams(dev, n: int) -> List["torch.cuda.Stream"]:
         return list(made)
 
 
+def _capture_stream(dev, shared) -> "torch.cuda.Stream":
+    """A side stream for captured steps that is none of ``shared``: work that other replicas put on one of
+    those meanwhile would be captured too.  (torch hands out its streams from a pool of 32 in turn.)"""
+    taken = {s.cuda_stream for s in shared}
+    while True:
+        s = torch.cuda.Stream(device=dev)
+        if s.cuda_stream not in taken:
+            return s
+
+
 class Replica:
     """Device state of one replica of ``net`` and its training step."""
 
@@ -444,7 +454,7 @@ class Replica:
         self.ws_side = torch.zeros(max(16, (need + 15) // 16 * 16), dtype=torch.uint8, device=dev)
         streams = _device_streams(dev, max(self.kFwdLanes - 1, self.kBwdLanes))
         self.side = streams[0]
-        self.capture_side = torch.cuda.Stream(device=dev)    # (a captured step joins no shared stream)
+        self.capture_side = _capture_stream(dev, streams)
         # ---- the forward pass's independent branches run on up to kFwdLanes streams (lane 0 is
         # the step's stream, lane 1 the side stream, idle in the forward pass: with the step's
         # stream, four streams, as many as the hardware queues a process gets by default), each

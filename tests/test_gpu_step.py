@@ -21,7 +21,7 @@ import torch
 
 import oracle
 from oracle import net as onet
-from paper_1605_08695_amd import workloads as W
+from paper_1605_08695_amd import step, workloads as W
 from paper_1605_08695_amd.step import Replica
 from tests.gpu_parity import ParityTracer, SampledParityTracer, err, f64, say, ulp_diff_f32
 from tests.test_step_workspace import two_branches
@@ -502,6 +502,18 @@ def test_output_concat_relu_backward_is_one_pass(lanes):
             # fp32 sums of P terms in any order: |error| <= P eps sum |term|
             bound = want[..., 0].numel() * 2.0 ** -24 * want.double().abs().sum(dim=(0, 1, 2)) + 1e-30
             assert bool(((rep.db[c.name].double() - s).abs() <= bound).all()), c.name
+
+
+def test_captured_steps_join_no_shared_stream():
+    """A replica's side stream for captures is none of the streams that the replicas share, however many
+    streams torch's pool has handed out before."""
+    net = W.single_layer(batch=1, hw=8)
+    inp = W.make_inputs(net, seed=0)
+    rep = Replica(net, inp)
+    shared = {s.cuda_stream for s in step._device_streams(rep.device, 3)}
+    assert len(shared) == 3 and rep.side.cuda_stream in shared
+    for _ in range(40):
+        assert Replica(net, inp).capture_side.cuda_stream not in shared
 
 
 def test_replicas_share_lane_streams():

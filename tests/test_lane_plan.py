@@ -109,3 +109,21 @@ def test_lane_plan_catches_a_missing_wait():
     bad[k] = (op, lane, [j for j in waits if j == "start"])
     with pytest.raises(AssertionError):
         _check(nodes, outs, bad, joins, 4)
+
+
+def test_capture_stream_is_none_of_the_shared(monkeypatch):
+    """torch hands out 32 streams in turn: from any point of that cycle, a captured step's side stream is
+    none of those that the replicas share."""
+    import itertools
+    from types import SimpleNamespace
+
+    import torch
+
+    from paper_1605_08695_amd import step
+    for start in range(32):
+        pool = itertools.cycle(range(32))
+        for _ in range(start):
+            next(pool)
+        monkeypatch.setattr(torch.cuda, "Stream", lambda device=None: SimpleNamespace(cuda_stream=next(pool)))
+        shared = [SimpleNamespace(cuda_stream=k) for k in (3, 4, 5)]
+        assert step._capture_stream(torch.device("cuda", 0), shared).cuda_stream not in (3, 4, 5)

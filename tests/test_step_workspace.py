@@ -56,7 +56,7 @@ def cpu_replica(monkeypatch):
     monkeypatch.setattr(ops, "load", _Lib)
     monkeypatch.setattr(ops, "_stream", lambda stream: 0)
     monkeypatch.setattr(step, "_device_streams", lambda dev, n: [_Stream() for _ in range(n)])
-    monkeypatch.setattr(torch.cuda, "Stream", lambda **kw: _Stream())
+    monkeypatch.setattr(step, "_capture_stream", lambda dev, shared: _Stream())
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: _Stream())
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
 
