@@ -59,13 +59,20 @@ def _check_all(name, dtype, N, H, W, C, K, KH, KW, s, pads, wide=0):
 
 # N, H, W, C, K, KH, KW, stride, pads, extra channels of the buffers
 F32_CASES = [
+    # few blocks: 32 x 32 tiles
     ("f32_c4_k4", 1, 5, 7, 4, 4, 3, 3, 1, (1, 1, 1, 1), 0),
     ("f32_c12_k20", 2, 9, 8, 12, 20, 3, 3, 1, (1, 1, 1, 1), 4),             # multiples of 4, not of 8
-    ("f32_c96_k100_s2", 2, 15, 14, 96, 100, 3, 3, 2, (0, 0, 0, 0), 0),      # 32-row tiles, stride phases
-    ("f32_c64_k68", 3, 8, 11, 64, 68, 1, 3, 1, (0, 0, 1, 1), 8),            # 64-row tiles and a remainder
-    ("f32_c160_k32_tail", 1, 13, 5, 160, 32, 5, 1, 1, (2, 2, 0, 0), 0),     # 65 pixels: one past a tile
+    ("f32_c96_k100_s2", 2, 15, 14, 96, 100, 3, 3, 2, (0, 0, 0, 0), 0),      # remainders, stride phases
+    ("f32_c64_k68", 3, 8, 11, 64, 68, 1, 3, 1, (0, 0, 1, 1), 8),            # remainders, channel slices
+    ("f32_c160_k32_tail", 1, 13, 5, 160, 32, 5, 1, 1, (2, 2, 0, 0), 0),     # 65 pixels: one past two tiles
     ("f32_1x1_k1_tile", 1, 8, 8, 32, 64, 1, 1, 1, (0, 0, 0, 0), 0),         # one reduction tile
     ("f32_2tiles", 1, 8, 8, 40, 32, 1, 1, 1, (0, 0, 0, 0), 0),              # two, the second partial
+    # 256 blocks and more: 64 x 64 tiles with a channel and a pixel remainder, forward (124 out of K) and input
+    # gradient (124 out of C), and 32 x 64 ones (100 channels fill little of a second 64), in channel slices
+    ("f32_64x64_k124", 6, 39, 37, 40, 124, 3, 3, 1, (1, 1, 1, 1), 4),
+    ("f32_64x64_c124", 6, 39, 37, 124, 40, 3, 3, 1, (1, 1, 1, 1), 12),
+    ("f32_32x64_k100", 3, 39, 37, 36, 100, 3, 3, 1, (1, 1, 1, 1), 8),
+    ("f32_32x64_c100", 3, 39, 37, 100, 36, 3, 3, 1, (1, 1, 1, 1), 4),
     ("f32_c6_k10", 2, 6, 5, 6, 10, 3, 3, 1, (1, 1, 1, 1), 0),               # register-staged kernel
 ]
 
@@ -136,6 +143,26 @@ def test_conv_padded_channels(case):
     # (the query asks for the padded copies; their filter alone is more than nothing)
     assert ops.conv2d_workspace_bytes(0, x, K, KH, KW, s, pads) >= KH * KW * C * K * x.element_size()
     _check_all(name, dtype, N, H, W, C, K, KH, KW, s, pads, wide)
+
+
+@pytest.mark.parametrize("dtype,C,K", [(torch.bfloat16, 45, 131), (torch.bfloat16, 64, 37), (torch.float32, 30, 66)])
+def test_conv_padded_channels_deferred_bias(dtype, C, K):
+    """The fused input gradient over padded copies with its bias partials left for a later sum: the
+    partials lie in the workspace it was given, and their sum has the bits of the immediate form."""
+    rng = np.random.default_rng(C)
+    N, H, W, p = 5, 23, 21, (1, 1, 1, 1)
+    y = torch.from_numpy(np.maximum(rng.standard_normal((N, H, W, C)), 0.0)).to(dtype).to(DEV)
+    w, dy = _mk((3, 3, C, K), dtype, rng, 0.05), _mk((N, H, W, K), dtype, rng)
+    need = ops.conv2d_workspace_bytes(3, y, K, 3, 3, 1, p)
+    assert need >= 9 * C * K * y.element_size()                             # (the padded filter at least)
+    dp, db = ops.conv2d_bwd_input_relu_bwd(dy, w, y, torch.empty_like(y), 1, p)
+    ws = torch.empty((need + 15) // 16 * 16, dtype=torch.uint8, device=DEV)
+    dp2, job = ops.conv2d_bwd_input_relu_bwd(dy, w, y, torch.empty_like(y), 1, p, ws=ws, defer=True)
+    assert ws.data_ptr() <= job.part and job.part + job.rows * C * 4 <= ws.data_ptr() + need
+    db2 = torch.full((C,), 3.0, device=DEV)
+    ops.bias_grad_finish([(job, db2)])
+    torch.cuda.synchronize()
+    assert torch.equal(dp, dp2) and torch.equal(db, db2)
 
 
 # short reductions over large tensors: gathered (or, fp32 with whole chunks, register-staged) instead
@@ -242,13 +269,18 @@ FIRST_CASES = [
 ]
 
 
-@pytest.mark.parametrize("rgbx", [False, True], ids=["copied", "in_place"])
+# (in place also one pixel into its buffer: a multiple of 8 bytes, not of 16)
+@pytest.mark.parametrize("rgbx", [0, 1, 2], ids=["copied", "in_place", "in_place_8"])
 @pytest.mark.parametrize("case", FIRST_CASES, ids=[c[0] for c in FIRST_CASES])
 def test_first_layer_paths(case, rgbx):
     name, N, H, W, C, K, k, s, pads = case
     say("first layer", name, rgbx)
     rng = np.random.default_rng(zlib.crc32(name.encode()))
-    x = _mk((N, H, W, 4), torch.bfloat16, rng)[..., :C] if rgbx else _mk((N, H, W, C), torch.bfloat16, rng)
+    if rgbx:
+        x = _mk((N * H * W + rgbx - 1, 4), torch.bfloat16, rng)[rgbx - 1:].view(N, H, W, 4)[..., :C]
+        assert x.data_ptr() % 16 == 8 * (rgbx - 1)
+    else:
+        x = _mk((N, H, W, C), torch.bfloat16, rng)
     w = _mk((k, k, C, K), torch.bfloat16, rng, np.sqrt(2.0 / (k * k * C)))
     bias = torch.from_numpy(rng.standard_normal(K) * 0.5).to(torch.float32).to(DEV)
     y = ops.conv2d_fwd_bias_relu(x, w, bias, s, pads)

@@ -289,6 +289,7 @@ def test_two_stream_step_matches_one_stream(make):
     net.lr = 1e-6
     inp = W.make_inputs(net, seed=3)
     one, two = Replica(net, inp), Replica(net, inp)
+    two.use_streams = True                   # (also where the step's own rule takes one stream)
     for r in range(3):
         one.step(concurrent=False)
         two.step(concurrent=True)
@@ -330,15 +331,16 @@ def test_full_size_lanes_match_one_stream(make):
 @pytest.mark.parametrize("make", [lambda: W.alexnet(batch=8), lambda: W.googlenet(batch=4)],
                          ids=["alexnet_b8", "googlenet_b4"])
 def test_graph_capture_replays_match_eager(make):
-    """The whole step captured once in a HIP graph; every replay (with eager steps and
-    synchronisations in between) must equal the eager step from the same state.  (A network
-    with branches runs its forward and backward passes without the lane streams under capture;
-    its eager steps use them.)"""
+    """The whole step captured once in a HIP graph, filter gradients forked to a side stream; every replay
+    (with eager steps and synchronisations in between) must equal the eager step from the same state.
+    (A network with branches runs its forward and backward passes without the lane streams under
+    capture; its eager steps use them.)"""
     net = make()
     net.lr = 1e-6            # keep the linear surrogate loss from driving values to inf
     inp = W.make_inputs(net, seed=2)
     eager = Replica(net, inp)
     graphed = Replica(net, inp)
+    eager.use_streams = graphed.use_streams = True
     s = torch.cuda.Stream()
     s.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(s):
@@ -374,6 +376,7 @@ def test_program_replays_match_eager(make, opt):
     net.lr = 1e-6
     inp = W.make_inputs(net, seed=4)
     eager, prog_rep = Replica(net, inp, optimizer=opt), Replica(net, inp, optimizer=opt)
+    eager.use_streams = prog_rep.use_streams = True
     eager.step()
     prog = prog_rep.record_step()
     torch.cuda.synchronize()
@@ -421,13 +424,14 @@ def test_program_writes_only_the_steps_own_memory(k):
                                   lambda: W.alexnet(batch=4, classifier=True)],
                          ids=["alexnet_b8", "googlenet_b4", "alexnet_cls_b4"])
 def test_deferred_bias_gradients_match_immediate(make):
-    """The untraced step leaves every main-stream bias gradient's partials in a workspace of its
-    own and sums them all in one launch before the update; it must equal, bit for bit, the step
+    """The untraced step leaves every bias gradient's partials (of the main stream and the lanes) in a
+    workspace of its own and sums them all in one launch before the update; it must equal, bit for bit, the step
     that sums each one as it is formed (the same per-channel order), over two steps."""
     net = make()
     net.lr = 1e-6
     inp = W.make_inputs(net, seed=8)
     a, b = Replica(net, inp), Replica(net, inp)
+    a.use_streams = b.use_streams = True
     b.defer_bias = False
     for r in range(2):
         a.step()
