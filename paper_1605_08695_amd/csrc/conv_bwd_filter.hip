@@ -8,7 +8,7 @@ namespace {
 
 struct BwfPlan {
     int bi, bj, splits, k_split;
-    Igemm2Tile t;      // configuration of the pipelined bf16 kernel
+    Igemm2Tile t;      // configuration of the pipelined kernel
 };
 
 BwfPlan bwf_plan_f32(const ConvShape &s);

@@ -125,8 +125,7 @@ __device__ __forceinline__ U4 lds_tr_pair(const unsigned char *p0, const unsigne
 // k-rows start alternately at bank 0 and bank 32: bit 1 of k moves k-rows 2 and 3 of a
 // group by one chunk pair and bit 3 of k the second group by two, which keeps every chunk
 // inside its aligned group of eight.  32-row k-rows are 64 bytes: the 4 k-rows of a group already
-// cover every bank once, and bit 3 of k moves the second group to the other chunk pair; so do
-// 160-row k-rows, whose 320 bytes start the 4 k-rows of a group a quarter of the banks apart.
+// cover every bank once, and bit 3 of k moves the second group to the other chunk pair.
 //
 // fp32: a fragment read touches 16 consecutive rows (64 bytes, four chunks) of the k-rows
 // 4g + e, g = 0..3 the lane group; (k >> 2) & 3 moves each group to its own 64 bytes of the
@@ -137,10 +136,10 @@ __device__ __forceinline__ int kmajor_swz(int k) {
         static_assert(R == 32 || R % 64 == 0, "k-major tile rows");
         return R == 32 ? ((k >> 2) & 1) << 2 : ((k >> 2) & 3) << 2;
     } else {
-        static_assert(R == 32 || R == 64 || R == 128 || R == 160 || R == 192 || R == 256, "k-major tile rows");
-        if constexpr (R == 32 || R == 160) return ((k >> 3) & 1) << 1;
+        static_assert(R == 32 || R == 64 || R == 128 || R == 192, "k-major tile rows");
+        if constexpr (R == 32) return ((k >> 3) & 1) << 1;
         else if constexpr (R == 64) return ((k & 3) ^ ((k >> 3) & 1)) << 1;
-        else if constexpr (R != 192) return ((k & 3) << 1) ^ (((k >> 3) & 1) << 3);
+        else if constexpr (R == 128) return ((k & 3) << 1) ^ (((k >> 3) & 1) << 3);
         else return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2);
     }
 }
@@ -177,10 +176,9 @@ __device__ __forceinline__ int xcd_order(int linear, int total) {
     return x * q + min(x, r) + linear / kXcd;
 }
 
-// BI x BJ output tile, NW waves (a 2 x NW/2 grid of wave tiles), NS LDS stages.  Every
-// SIMD runs two waves: one 8-wave block per CU, or two 4-wave blocks per CU when NS
-// stages fit twice in the 160 KiB of LDS.  Two independent blocks keep a CU's MFMAs busy
-// while the other block waits at its barrier for a slow copy.
+// BI x BJ output tile, NW = 4 waves (a 2 x NW/2 grid of wave tiles), NS LDS stages.  Every
+// SIMD runs two waves, of two blocks per CU where NS stages fit twice in the 160 KiB of LDS:
+// two independent blocks keep a CU's MFMAs busy while one waits at its barrier for a slow copy.
 // RAG: the output's channel count (a.ni_store <= a.NI) or addresses do not allow vector stores:
 // the epilogue reads and writes single elements.
 template <typename T, int DIR, int BI, int BJ, int NW, int NS, bool RAG = false>
@@ -194,7 +192,7 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     constexpr int NLI = BI / (8 * NW), NLJ = BJ / (8 * NW), NL = NLI + NLJ;   // copies per thread per tile
     constexpr int WI = BI / 2, WJ = BJ / WGJ;
     constexpr int MI = WI / 16, MJ = WJ / 16;
-    static_assert(NW == 4 || NW == 8, "waves");
+    static_assert(NW == 4, "waves");
     static_assert(NS == 2 || NS == 3, "stages");
     static_assert(NLI >= 1 && NLJ >= 1 && MI >= 1 && MJ >= 1, "tile");
     static_assert(NS * SB <= 160 * 1024, "LDS");

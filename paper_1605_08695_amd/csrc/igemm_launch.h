@@ -39,7 +39,7 @@ static hipError_t igemm_launch(IgArgs &a, int mj, int zdim, bool vi, bool vj, hi
     return hipGetLastError();
 }
 
-// Tile configuration of the pipelined bf16 kernel: BI x BJ output tile, waves per block,
+// Tile configuration of the pipelined kernel: BI x BJ output tile, waves per block,
 // LDS stages.
 struct Igemm2Tile {
     int bi, bj, nw, ns;
@@ -176,9 +176,11 @@ static bool igemm2_launch(IgArgs &a, int mj, int zdim, const Igemm2Tile &t, hipS
     case 641282: igemm2_go<bf16_t, DIR, 64, 128, 4, 2>(a, grid, st); return true;
     case 1281282: igemm2_go<bf16_t, DIR, 128, 128, 4, 2>(a, grid, st); return true;
     }
+    if constexpr (DIR == DIR_FWD) {          // (64 x 192: the row bands of a pool inside the convolution)
+        if (key == 641922) { igemm2_go<bf16_t, DIR, 64, 192, 4, 2>(a, grid, st); return true; }
+    }
     if constexpr (DIR != DIR_BWD_FILTER) {
         switch (key) {
-        case 641922: igemm2_go<bf16_t, DIR, 64, 192, 4, 2>(a, grid, st); return true;
         case 1281283: igemm2_go<bf16_t, DIR, 128, 128, 4, 3>(a, grid, st); return true;
         case 1280962: igemm2_go<bf16_t, DIR, 128, 96, 4, 2>(a, grid, st); return true;
         case 1281602: igemm2_go<bf16_t, DIR, 128, 160, 4, 2>(a, grid, st); return true;
