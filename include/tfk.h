@@ -174,8 +174,9 @@ TFK_API tfk_status tfk_conv2d_bwd_filter(const void *x, tfk_nhwc xd, const void 
  * device memory, 128 MiB per GPU, held from the library's load on that GPU until the process
  * ends.  The call allocates nothing.
  *   stream : must belong to the calling thread's current device (else TFK_ERR_HIP).
- * Errors: as tfk_conv2d_bwd_filter; TFK_ERR_WORKSPACE when the shape needs more scratch than
- * 128 MiB (tfk_conv2d_workspace_bytes(2, ...) tells how much it needs).
+ * Errors: as tfk_conv2d_bwd_filter; TFK_ERR_WORKSPACE when the shape's plainest form needs more
+ * scratch than 128 MiB.  tfk_conv2d_workspace_bytes(2, ...) tells how much the fastest form uses:
+ * where that is more than 128 MiB, a form that needs less runs if there is one.
  * Every call on one GPU uses that GPU's one scratch array: calls that overlap in time on one
  * GPU (on different streams, or from different threads) race and give wrong results; calls
  * ordered on one stream do not.  No scratch content needs to start at zero.

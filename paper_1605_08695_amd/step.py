@@ -484,12 +484,13 @@ class Replica:
     # A fork to another stream and its join cost 6-13 us of host time (an event recorded and waited
     # for) and drain the stream they are recorded on, whatever the kernels do.  Recorded steps by the
     # mean work of the filter gradients that would run on the side stream, one stream / side stream /
-    # side stream and lanes (us): inception modules 28 x 28 at batch 8 (0.8 GFLOP) 189 / 205 / 250, batch
-    # 16 (1.6) 244 / 250 / 257, batch 32 (3.2) 320 / 297 / 288, batch 128 (13) 796 / 732 / 736; 14 x 14 at
-    # batch 32 (1.1) 220 / 213 / 263, batch 63 (2.1) 277 / 279 / 266, batch 128 (4.3) 375 / 348 / 348; 7 x 7 at
-    # batch 64 (1.5) 237 / 245 / 273; the AlexNet stack at batch 8 (2.4) 250 / 232, batch 32 (9.7) 400 / 385;
-    # GoogLeNet batch 2 (0.1) 943 / 1078 / 1392, batch 128 (4.9) 3387 / 3082 / 2894; Inception-v3 batch 4
-    # (0.5) 2354 / 2983 / 3045.
+    # side stream and lanes (us): inception modules 28 x 28 at batch 8 (0.4 GFLOP) 148 / 192 / 245, batch
+    # 16 (0.8) 172 / 189 / 248, batch 32 (1.6) 211 / 189 / 244; 14 x 14 at batch 32 (1.1) 198 / 182 / 189,
+    # batch 63 (2.2) 260 / 230 / 224, batch 128 (4.5) 372 / 338 / 306; 7 x 7 at batch 64 (1.3) 193 / 175 /
+    # 192, batch 128 (2.6) 245 / 220 / 249; the AlexNet stack at batch 8 (2.3) 250 / 224, batch 32 (9.4)
+    # 404 / 352; GoogLeNet batch 32 (1.9) 1706 / 1401 / 1791, batch 64 (3.8) 2319 / 1985 / 1998, batch 2
+    # (0.1) 943 / 1078 / 1392.  One line for both keeps the calls that lose on it few: the side stream
+    # alone would already win from about 1.1 GFLOP, the lanes only from about 4.
     kStreamFlops = 1.8e9
 
     def _stream_rule(self) -> bool:
