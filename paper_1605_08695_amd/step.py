@@ -183,11 +183,11 @@ def _device_streams(dev, n: int) -> List["torch.cuda.Stream"]:
 
 def _capture_stream(dev, shared) -> "torch.cuda.Stream":
     """A side stream for captured steps that is none of ``shared``: work that other replicas put on one of
-    those meanwhile would be captured too.  (torch hands out its streams from a pool of 32 in turn.)"""
-    taken = {s.cuda_stream for s in shared}
+    those meanwhile would be captured too.  (torch hands out its streams from a pool of 32 in turn, and makes
+    one when its handle is first asked for, 0.3 ms: their ids are compared.)"""
     while True:
         s = torch.cuda.Stream(device=dev)
-        if s.cuda_stream not in taken:
+        if s not in shared:
             return s
 
 
@@ -489,8 +489,8 @@ class Replica:
     # batch 63 (2.2) 260 / 230 / 224, batch 128 (4.5) 372 / 338 / 306; 7 x 7 at batch 64 (1.3) 193 / 175 /
     # 192, batch 128 (2.6) 245 / 220 / 249; the AlexNet stack at batch 8 (2.3) 250 / 224, batch 32 (9.4)
     # 404 / 352; GoogLeNet batch 32 (1.9) 1706 / 1401 / 1791, batch 64 (3.8) 2319 / 1985 / 1998, batch 2
-    # (0.1) 943 / 1078 / 1392.  One line for both keeps the calls that lose on it few: the side stream
-    # alone would already win from about 1.1 GFLOP, the lanes only from about 4.
+    # (0.1) 943 / 1078 / 1392.  (One line for both: the side stream alone already wins from about 1.1 GFLOP,
+    # and up to about 4 the lanes add little to it or lose.)
     kStreamFlops = 1.8e9
 
     def _stream_rule(self) -> bool:

@@ -115,15 +115,28 @@ def test_capture_stream_is_none_of_the_shared(monkeypatch):
     """torch hands out 32 streams in turn: from any point of that cycle, a captured step's side stream is
     none of those that the replicas share."""
     import itertools
-    from types import SimpleNamespace
 
     import torch
 
     from paper_1605_08695_amd import step
+
+    class Stream:
+        """Streams with one id are one stream; asking for its handle would create it."""
+
+        def __init__(self, k):
+            self.k = k
+
+        def __eq__(self, other):
+            return self.k == other.k
+
+        @property
+        def cuda_stream(self):
+            raise AssertionError("a stream that may never be used is created")
+
     for start in range(32):
         pool = itertools.cycle(range(32))
         for _ in range(start):
             next(pool)
-        monkeypatch.setattr(torch.cuda, "Stream", lambda device=None: SimpleNamespace(cuda_stream=next(pool)))
-        shared = [SimpleNamespace(cuda_stream=k) for k in (3, 4, 5)]
-        assert step._capture_stream(torch.device("cuda", 0), shared).cuda_stream not in (3, 4, 5)
+        monkeypatch.setattr(torch.cuda, "Stream", lambda device=None: Stream(next(pool)))
+        shared = [Stream(k) for k in (3, 4, 5)]
+        assert step._capture_stream(torch.device("cuda", 0), shared).k not in (3, 4, 5)
