@@ -14,15 +14,14 @@ struct BwfPlan {
 BwfPlan bwf_plan_f32(const ConvShape &s);
 
 // Tiles and split-K of one bwd-filter launch, chosen from sweeps over the AlexNet/VGG
-// shapes: 128 x 128 tiles (even for 192 output channels, where the second channel tile
-// is half empty) and the pixel reduction split into as many parts as keep the blocks within
-// one full round of two blocks per CU (512 blocks): a last round with only a few blocks
+// shapes: 128 x 128 tiles and the pixel reduction split into as many parts as keep the blocks
+// within one full round of two blocks per CU (512 blocks): a last round with only a few blocks
 // costs a whole block time, and more splits only add partial-sum traffic (AlexNet conv2-5:
 // 357 us with four-block rounds, 297 us with this rule; the sustained two-stream AlexNet step
-// 0.686 ms, against 0.694 with 384 blocks for the short launches).
-// 64-channel layers take 64 x 128
-// tiles, layers of at most 32 output channels 32 x 128, multiples of 64 that are not of 128 64 x 128.  (192-channel tiles, which pay in the
-// forward pass, need more registers here than two waves per SIMD have and spill.)
+// 0.686 ms, against 0.694 with 384 blocks for the short launches).  64-channel layers, and
+// multiples of 64 that are not of 128, take 64 x 128 tiles, layers of at most 32 output channels
+// 32 x 128.  (192-channel tiles, which pay in the forward pass, need more registers here than two
+// waves per SIMD have and spill.)
 BwfPlan bwf_plan(int dt, const ConvShape &s, bool v2) {
     BwfPlan p;
     if (dt == 0 && v2) return bwf_plan_f32(s);
