@@ -134,25 +134,42 @@ int relu_rows(int dt, const ConvShape &p) {
 constexpr double kPadFlops = 1e6;
 
 // The copies and the element-wise stores cost by the sizes of the tensors, the gather that they save by the
-// reduction of each output (per stride phase on average).  Random calls, padded against gathered:
+// reduction of each output, and in fp32 1 x 1 products by the arithmetic per element copied.  Random calls, padded
+// against gathered:
 //  * forward: fp32, and bf16 that copies x alone, below 64 elements 0.9-1.15 of the time (to 1.9; under 1M outputs
 //    0.7-1), from there on 0.8 falling to 0.1; bf16 with ragged output channels gathers the filter too: 0.8 from
-//    the shortest on;
-//  * input gradient: fp32 below 64 0.95-1.4 (to 2.5), then 0.85 falling to 0.2; bf16 that copies dy below 64 0.9-1.1
-//    (to 2.2; under 1M outputs 0.4-0.9), then 0.65 falling to 0.08; bf16 whose dy is whole loses its vector
-//    stores for nothing but the filter: 1.0-1.3 below 512, then 0.8 falling;
+//    the shortest on.  fp32 1 x 1 that copies x, below 64 products per element: 0.95 under 8M elements, from there on
+//    1.05-1.3, from 16M 1.1-1.45, from 32M 1.25-2.2 (3.1); larger filters 0.6-0.8, below 8 products from 32M 1.2;
+//  * filter gradient: over few pixels there is little to gather, and the padded filter is copied out again: below 64
+//    pixels 0.91-1.3 (to 1.9; 1M outputs and more 1.25-2.2, 128 pixels 1.1-1.5), then 0.85 falling to 0.3; bf16 with
+//    ragged x 0.6-0.85 from 8 pixels on, over 2M outputs and more 1.07-1.35 below 64.  fp32 1 x 1 as in the forward
+//    pass: 0.76-0.98 under 16M elements, 0.91-1.34 from there on, 1.09-2 from 32M;
+//  * input gradient, by the largest stride phase's reduction: fp32 below 64 0.95-1.4 (to 2.5; under 1M outputs and
+//    ragged dy 0.83-0.93 from 32 on), then 0.85 falling to 0.3; over 1M outputs it is the phases' average that
+//    counts (the other phases only store): below 64 1.05-2.6; bf16 that copies dy under 1M outputs 0.75-0.87 from the
+//    shortest on, over them below 64 0.87-1.8, then 0.98 falling to 0.2; bf16 whose dy is whole loses its vector
+//    stores for nothing but the filter: 1-1.25 below 256, then 0.9 falling; over 1M outputs 1.15-2.2 below 512 on
+//    average, then 0.8-1.15;
 //  * fused with the ReLU backward it saves that pass: small tensors (4M elements) and bf16 with both counts ragged
-//    gain from the shortest on, others from 64;
-//  * filter gradient: below 32 pixels there is little to gather (0.95-2.2), then 0.9 falling to 0.3.
+//    gain from the shortest on, others from 64.
 static bool pad_pays(int op, int dt, const ConvShape &s) {
     const bool ck = s.C % chunk_of(dt) != 0, kk = s.K % chunk_of(dt) != 0;
     const int64_t taps = (int64_t)s.KH * s.KW, px = (int64_t)s.N * s.H * s.W, py = (int64_t)s.N * s.OH * s.OW;
+    if (op == 0 || op == 2) {
+        const bool few = taps * s.K < (taps == 1 ? 64 : 8) * (int64_t)s.sh * s.sw;
+        if (dt == 0 && ck && few && px * s.C >= (taps > 1 ? 32 : op == 0 ? 8 : 16) * (int64_t)(1 << 20)) return false;
+    }
     if (op == 0) return (dt == 1 && kk) || taps * s.C >= 64 || py * s.K < (1 << 20);
-    if (op == 2) return py >= 32;
+    if (op == 2) {
+        const int64_t out = taps * s.C * s.K;
+        return py >= (dt == 1 && ck ? (out < (2 << 20) ? 8 : 64) : (out < (1 << 20) ? 64 : 128));
+    }
     const int64_t red = taps * s.K / (s.sh * s.sw);
     if (op == 3) return (dt == 1 && ck && kk) || red >= 64 || px * s.C < (1 << 22);
-    if (dt == 1 && !kk) return red >= 512;
-    return red >= 64 || (dt == 1 && px * s.C < (1 << 20));
+    const int64_t most = (int64_t)((s.KH + s.sh - 1) / s.sh) * ((s.KW + s.sw - 1) / s.sw) * s.K;
+    const bool big = px * s.C >= (1 << 20);
+    if (dt == 0) return big ? red >= 64 : most >= (kk ? 32 : 64);
+    return kk ? most >= 64 || !big : (big ? red >= 512 : most >= 256);
 }
 
 bool conv_pad_applies(int op, int dt, const ConvShape &s) {

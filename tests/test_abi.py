@@ -538,3 +538,39 @@ def test_padded_copies_where_the_reduction_pays(lib, op, dt, c, k, kh, pays):
     assert got < copy if not pays or not ragged else got >= copy
     if pays and not ragged:                       # (the filter alone is copied)
         assert got >= kh * kh * c * k * es
+
+
+@pytest.mark.parametrize("dt,n,hw,c,k,kh,s,pays", [
+    (BF16, 108, 42, 42, 70, 1, 2, True), (BF16, 108, 42, 42, 62, 1, 2, False), (BF16, 9, 42, 42, 7, 1, 1, True),
+    (BF16, 9, 42, 42, 256, 1, 2, True), (BF16, 9, 42, 42, 248, 1, 2, False), (F32, 9, 42, 42, 34, 1, 2, True),
+    (F32, 9, 42, 42, 30, 1, 2, False), (F32, 9, 42, 42, 64, 1, 2, True), (F32, 9, 42, 42, 60, 1, 2, False),
+    (F32, 108, 42, 42, 70, 1, 2, False), (F32, 108, 42, 42, 70, 3, 2, True)])
+def test_padded_input_gradients_by_stride_phase(lib, dt, n, hw, c, k, kh, s, pays):
+    """The largest phase's reduction decides (of a 1 x 1 filter at stride 2 one phase of four has the tap), in fp32
+    over large tensors the average phase's."""
+    es, e = (4, 4) if dt == F32 else (2, 8)
+    o = (hw + 2 * (kh // 2) - kh) // s + 1
+    got = lib.tfk_conv2d_workspace_bytes(1, Nhwc(n, hw, hw, c, 0), k, Window(kh, kh, s, s, *[kh // 2] * 4), dt)
+    copy = (n * o * o if k % e else kh * kh) * (-(-k // e) * e) * es * (1 if k % e else c)
+    assert got >= copy if pays else got < copy
+
+
+@pytest.mark.parametrize("dt,c,k,hw,pays", [
+    (BF16, 171, 96, 3, True), (BF16, 171, 96, 2, False), (BF16, 64, 75, 7, False), (F32, 75, 64, 7, False),
+    (BF16, 64, 75, 8, True), (F32, 75, 64, 8, True)])
+def test_padded_filter_gradients_of_few_pixels(lib, dt, c, k, hw, pays):
+    """From 64 pixels on, bf16 with ragged input channels from 8 on.  (The partial or padded filter is the
+    workspace then: none without.)"""
+    got = lib.tfk_conv2d_workspace_bytes(2, Nhwc(1, hw + 2, hw + 2, c, 0), k, Window(3, 3, 1, 1, 0, 0, 0, 0), dt)
+    assert got >= 9 * c * k * 4 if pays else got == 0
+
+
+@pytest.mark.parametrize("op,c,k,kh,pays", [
+    (0, 81, 20, 1, False), (0, 81, 64, 1, True), (0, 81, 20, 3, True), (0, 79, 20, 1, True),
+    (2, 159, 20, 1, False), (2, 159, 64, 1, True), (2, 157, 20, 1, True), (2, 159, 20, 3, True)])
+def test_padded_copies_of_large_fp32_inputs(lib, op, c, k, kh, pays):
+    """1 x 1 products of few outputs over 60 x 42 x 42 pixels read x once either way: no copy from 8M elements on,
+    16M for the filter gradient."""
+    got = lib.tfk_conv2d_workspace_bytes(op, Nhwc(60, 42, 42, c, 0), k, Window(kh, kh, 1, 1, *[kh // 2] * 4), F32)
+    copy = 60 * 42 * 42 * (-(-c // 4) * 4) * 4
+    assert got >= copy if pays else got < copy

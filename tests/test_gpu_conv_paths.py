@@ -171,6 +171,11 @@ SHORT_CASES = [
     ("short_c64_k9", torch.bfloat16, 30, 33, 31, 64, 9, 1, 1, 1, (0, 0, 0, 0), 0),
     ("short_f32_c42_k10", torch.float32, 30, 33, 31, 42, 10, 1, 1, 1, (0, 0, 0, 0), 3),
     ("short_f32_c100_k32_s2", torch.float32, 44, 31, 31, 100, 32, 1, 1, 2, (0, 0, 0, 0), 0),
+    ("few_pixels_c75_k88", torch.bfloat16, 1, 5, 5, 75, 88, 3, 3, 1, (0, 0, 0, 0), 0),
+    ("phase_c35_k66_s2", torch.bfloat16, 34, 31, 31, 35, 66, 1, 1, 2, (0, 0, 0, 0), 3),
+    ("phase_f32_c35_k33_s2", torch.float32, 5, 31, 31, 35, 33, 1, 1, 2, (0, 0, 0, 0), 0),
+    ("large_f32_c81_k12", torch.float32, 30, 59, 59, 81, 12, 1, 1, 1, (0, 0, 0, 0), 0),
+    ("large_f32_c165_k4_s2", torch.float32, 30, 59, 59, 165, 4, 1, 1, 2, (0, 0, 0, 0), 0),
 ]
 
 
