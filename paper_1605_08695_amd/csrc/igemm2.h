@@ -207,16 +207,14 @@ __global__ __launch_bounds__(NW * 64, 2) void igemm2_kernel(const IgArgs a) {
     // (A whole launch renumbered: in a filter gradient an XCD's tiles of a split read the same pixel
     // range of x and dy, from one L2; AlexNet conv2-5: 232 -> 228 us.  By phase: see igemm2_by_phase.)
     const int lin_hw = (int)(blockIdx.x + gridDim.x * blockIdx.z);
-    int bx, bz;
-    if (DIR == DIR_BWD_DATA && a.xcd_order == 2) {
-        bx = xcd_order((int)blockIdx.x, (int)gridDim.x);
-        bz = (int)blockIdx.z;
-    } else {
-        // (the filter gradient's loop comes out 4 % slower without the test)
-        const int lin = DIR == DIR_BWD_DATA || a.xcd_order ? xcd_order(lin_hw, (int)(gridDim.x * gridDim.z)) : lin_hw;
-        bx = lin % (int)gridDim.x;
-        bz = lin / (int)gridDim.x;
-    }
+    // (selects: a branch between the two cost an input gradient of 25 us 0.12)
+    const bool phase = DIR == DIR_BWD_DATA && a.xcd_order == 2;
+    const int first = phase ? (int)(gridDim.x * blockIdx.z) : 0;
+    const int of = phase ? (int)gridDim.x : (int)(gridDim.x * gridDim.z);
+    // (the filter gradient's loop comes out 4 % slower without the test)
+    const int lin = DIR == DIR_BWD_DATA || a.xcd_order ? first + xcd_order(lin_hw - first, of) : lin_hw;
+    const int bx = lin % (int)gridDim.x;
+    const int bz = lin / (int)gridDim.x;
     const int ti = bx % a.tiles_i;
     const int tj = bx / a.tiles_i;
     const int i0 = ti * BI;
